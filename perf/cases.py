@@ -119,21 +119,28 @@ def _weights(N, K, gen, dtype=torch.bfloat16):
     return w.to(dtype)
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """(activations or None, weights) of a case, from the seed alone."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
+    if case["kind"] in ("convert", "roundtrip"):
+        return None, _weights(case["rows"], case["K"], gen, DTYPES[case["src"]])
+    dt = DTYPES[case.get("src", "bf16")]
+    W = _weights(case["N"], case["K"], gen, dt)
+    return _activations(case["M"], case["K"], gen, dt), W
+
+
+def prepare(case, seed):
     s = dict(case)
     kind = case["kind"]
+    A, W = _inputs(case, seed)
     if kind == "operands":
-        dt = DTYPES[case["src"]]
-        s["A"], s["W"] = _activations(case["M"], case["K"], gen, dt), _weights(case["N"], case["K"], gen, dt)
+        s["A"], s["W"] = A, W
     elif kind in ("convert", "roundtrip"):
-        x = _weights(case["rows"], case["K"], gen, DTYPES[case["src"]])
-        s["X"] = x.t().contiguous() if case.get("strided") else x
+        s["X"] = W.t().contiguous() if case.get("strided") else W
     else:
         M, N, K, w = case["M"], case["N"], case["K"], fmt(case["w"])
-        qw = mxp.quantize(_weights(N, K, gen), w)
-        A = _activations(M, K, gen, torch.bfloat16)
+        qw = mxp.quantize(W, w)
         if kind == "decode":
             s["A"] = A
             if case["w"] == "MXFP4":
@@ -193,6 +200,64 @@ def run(s):
     if kind == "convert":
         return _canonical(q, f)
     return _canonical(q, f), mxp.dequantize(q, fmt(f), DTYPES[s["dst"]])
+
+
+# Element grid of a format: significand bits behind the point, smallest exponent, largest magnitude, e_max; and the bits that
+# the + forms give the block maximum (its exponent is e_max).
+GRID = {"MXFP4": (1, 0, 6.0, 2), "MXFP6": (3, 0, 7.5, 2), "MXFP8": (3, -6, 448.0, 8)}
+BM_BITS = {"MXFP4": 3, "MXFP6": 5, "MXFP8": 7}
+
+
+def _exponent(v):
+    """floor(log2 |v|), far down for zero."""
+    return torch.where(v == 0, -1000, torch.frexp(v)[1] - 1)
+
+
+def _scaled(v, e):
+    """v * 2^e, from the exponent's bits (exact for results in the normal range)."""
+    return v * ((e.long().clamp(-1022, 1023) + 1023) << 52).view(torch.float64)
+
+
+def _represented(x, f):
+    """The values, in 64 bits, that a tensor has in format f: blocks of 32 along the rows with the shared exponent
+    floor(log2 max) - e_max, elements to the nearest (ties to even, saturating); in the + forms the first element of
+    largest magnitude keeps the block's exponent and more significand bits; in the ++ form the others take a scale of
+    their own, up to seven steps finer, that keeps the largest of them below 4."""
+    base = f.rstrip("P")
+    bits, low, top, e_max = GRID[base]
+    v = x.double().view(x.shape[0], -1, 32)
+    at = v.abs().max(dim=2, keepdim=True).values
+    is_bm = torch.arange(32, device=v.device) == (v.abs() == at).to(torch.uint8).argmax(dim=2, keepdim=True)
+    e = _exponent(at)
+    shared = e - e_max
+    scale = shared
+    if f.endswith("PP"):
+        rest = _exponent(v.abs().masked_fill(is_bm, 0.0).max(dim=2, keepdim=True).values)
+        scale = torch.minimum(torch.maximum(torch.maximum(rest - 1, shared - 7), torch.full_like(shared, -126)), shared)
+    u = _scaled(v, -scale)
+    step = _exponent(u).clamp(min=low) - bits
+    q = _scaled(_scaled(torch.round(_scaled(u, -step)), step).clamp(-top, top), scale)
+    if f.endswith("P"):
+        n = BM_BITS[base]
+        m = torch.round(_scaled(v, n - e)).clamp(-(2.0 ** (n + 1) - 1), 2.0 ** (n + 1) - 1)
+        q = torch.where(is_bm, _scaled(m, e - n), q)
+    return torch.where(e <= e_max - 127, 0.0, q).view(x.shape)
+
+
+def exact(case, seed):
+    """What run() computes, in 64 bits and without the package; None for bytes, which have no such value."""
+    kind = case["kind"]
+    if kind == "convert":
+        return None
+    A, W = _inputs(case, seed)
+    none3 = (None, None, None)
+    if kind == "roundtrip":
+        return _canonical(none3, case["f"]), _represented(W, case["f"])
+    a = A.double() if kind == "weight_only" else _represented(A, case.get("a", "MXFP4P"))
+    D = a @ _represented(W, case.get("w", "MXFP4P")).t()
+    if kind == "operands":
+        return none3, none3, D, a
+    return (none3, D, a) if kind == "step" else D
 
 
 def _operand_bytes(rows, K, f):
