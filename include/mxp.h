@@ -256,10 +256,10 @@ size_t mxp_gemm_workspace_bytes_e4m3(int64_t M, int64_t N, int64_t K);   /* when
  * (see mxp_prepack_fp6 for the cost), MXFP6 or MXFP6+ with MXFP4 or MXFP4+ on the other side (plain MXFP6: one E2M3
  * image each, at the rate of the MXFP4+ product; MXFP6+: its two K segments against the four-bit operand's image laid out
  * twice, twice the work).  Pairs with an eight-bit format, and a six-bit format next to MXFP4++, are multiplied from
- * de-converted operands: the size returned for them, 2 M K bytes rounded up to 256, is room for A as bf16 and is
- * optional -- with it A is de-converted once ahead of the product (1.3 - 1.65x faster; the same products, and above 128
- * rows the same summation order, i.e. identical bits), with a smaller or no workspace both operands are de-converted
- * inside the kernel.  0 for unknown formats. */
+ * de-converted operands: the size returned for them, 2 M K bytes rounded up to 256 for A as bf16 and, behind it,
+ * mxp_gemm_w4a16_workspace_bytes(M, N, K, fmtB) for B, is optional -- with it each operand is de-converted once ahead of
+ * the product (the same products, and above 128 rows the same summation order, i.e. identical bits), with room for A
+ * only B is de-converted inside the kernel, with less or none both are.  0 for unknown formats. */
 size_t mxp_gemm_workspace_bytes_fmt(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB);
 size_t mxp_gemm_workspace_size(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB);   /* the same function under its short name */
 int mxp_gemm(int64_t M, int64_t N, int64_t K,
@@ -326,6 +326,14 @@ int mxp_gemm_decode_bf16a(int64_t M, int64_t N, int64_t K, const void* A, int a_
 int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
                    const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW,
                    void* D, int d_dtype, int64_t ldd, void* stream);
+/* The same with room for W as bf16: many activation rows then de-convert W once, ahead of the product (in slabs of as
+ * many rows of W as fit; the same products in the same order), instead of once per row of output tiles inside it.
+ * mxp_gemm_w4a16_workspace_bytes: the room worth giving, at most 256 MiB (or 256 rows of W); 0 where it would not be used.
+ * workspace may be NULL or smaller: the call then runs as mxp_gemm_w4a16 does. */
+size_t mxp_gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K, int fmtW);
+int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
+                      const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW,
+                      void* D, int d_dtype, int64_t ldd, void* workspace, size_t workspace_bytes, void* stream);
 
 const char* mxp_status_string(int status);
 int mxp_version(void);

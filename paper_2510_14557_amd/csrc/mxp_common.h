@@ -32,6 +32,10 @@ int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K
 int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows,
                            int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t stream);
 
+// canonical operand -> dense bf16 rows that a product reads next (arguments already checked)
+int dequantize_bf16_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows, int64_t K, void* dst,
+                           hipStream_t s);
+
 int prepack_fp6_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows, int64_t K,
                        int n_seg, uint32_t res_mask, void* image, hipStream_t stream);
 int prepack_seg_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows, int64_t K, int n_seg,
@@ -43,6 +47,11 @@ int prepack_fp8_launch(const uint8_t* elems, const uint8_t* scales, int64_t rows
 int deconv_gemm_launch(int64_t M, int64_t N, int64_t K, const uint8_t* ae, const uint8_t* as, const uint8_t* ai, int fmtA,
                        const uint8_t* be, const uint8_t* bs, const uint8_t* bi, int fmtB, void* D, int d_dtype, int64_t ldd,
                        hipStream_t s);
+
+// the product of two bf16 matrices in memory (mxp_bf16.hip): rows 16-byte aligned, K a multiple of 32
+bool bf16_gemm_takes(int64_t M, int64_t N, int64_t K, int64_t lda);
+int bf16_gemm_launch(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* D, int d_dtype,
+                     int64_t ldd, hipStream_t s);
 
 // Longest reduction the product entry points take: the tiled kernel addresses an 8-tile run of an operand image with a
 // 32-bit lane offset, and a six-bit + product lays up to four K segments side by side.

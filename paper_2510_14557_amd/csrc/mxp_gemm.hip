@@ -10,6 +10,7 @@
 // of operand row l % 32, K-block l / 32, plus that block's scale byte; accumulator register r of lane l is element
 // [8 * (r / 4) + 4 * (l / 32) + r % 4][l % 32] of (first operand) x (second operand)^T.
 #include "mxp_common.h"
+#include "mxp_tile.h"
 #include <atomic>
 #include <mutex>
 #include <type_traits>
@@ -77,9 +78,6 @@ namespace {
 
 using namespace mxp;
 typedef int v8i __attribute__((ext_vector_type(8)));
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kFmtE2M3 = 2;  // cbsz / blgp code of the f8f6f4 MFMA for FP6 E2M3 operands
 constexpr int kFmtE4M3 = 0;  // ... for FP8 E4M3 operands (32 bytes per lane; the instruction then runs at half rate)
@@ -152,15 +150,6 @@ __device__ __forceinline__ void mma_all(v16f (&acc)[C::WM][C::WN], const v8i (&a
 // Epilogue.  Lane l holds row m = l % 32 of the tile; register quad g holds columns 8g + 4(l / 32) .. +3.  With an
 // aligned D each quad is one 16-byte (fp32) or 8-byte (bf16) store: 64 stores per wavefront tile instead of 256, which
 // keeps the whole epilogue inside one window of the 6-bit vmcnt counter.
-// fp32 -> bf16, round to nearest even, NaN stays NaN: the CDNA4 pack-convert instruction (one per two values).
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-  union { bf16x2 v; uint32_t u; } c;
-  c.v = __builtin_convertvector((f32x2){lo, hi}, bf16x2);
-  return c.u;
-}
-__device__ __forceinline__ uint32_t f32_to_bf16_rne(float v) { return pack_bf16x2(v, 0.0f) & 0xFFFFu; }
 
 template <int TWM, int TWN, bool OUT_BF16>
 __device__ __forceinline__ void store_tile(const v16f (&acc)[TWM][TWN], int64_t tile_m, int64_t tile_n, int lane, int64_t M,
@@ -187,94 +176,6 @@ __device__ __forceinline__ void store_tile(const v16f (&acc)[TWM][TWN], int64_t 
           }
         } else {
           const float v[4] = {v0, v1, v2, v3};
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            if (col + q < N) {
-              if (OUT_BF16) static_cast<uint16_t*>(Dv)[row * ldd + col + q] = (uint16_t)f32_to_bf16_rne(v[q]);
-              else static_cast<float*>(Dv)[row * ldd + col + q] = v[q];
-            }
-          }
-        }
-      }
-    }
-  }
-}
-
-// Epilogue through LDS for the large kernel.  Stored straight from the accumulator layout, a store instruction touches
-// 64 different 128-byte lines with 16 bytes each, and the L2 then sees 4096 partial-line writes per wavefront tile.
-// Each 32 x 32 tile is therefore passed through a private 32 x 36-float LDS patch (rows padded by 16 bytes against bank
-// conflicts; LDS operations of one wavefront execute in order, so no wait is needed between the write and the read)
-// and comes back with 8 consecutive lanes holding the 128 contiguous bytes of one row: every store instruction
-// writes 8 full lines.  `patch` is this wavefront's scratch, two patches of kPatchBytes.
-constexpr int kPatchStride = 144;                 // bytes per patch row: 32 floats + 16
-constexpr int kPatchBytes = 32 * kPatchStride;
-
-template <int TWM, int TWN, bool OUT_BF16>
-__device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int64_t tile_m, int64_t tile_n, int lane, int64_t M,
-                                               int64_t N, void* __restrict__ Dv, int64_t ldd, uint8_t* patch) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  const bool vec_ok = (ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(Dv) & 15u) == 0);
-  const int wr = (lane & 31) * kPatchStride + 16 * (lane >> 5);   // + 32 g
-  const int rd = (lane >> 3) * kPatchStride + (lane & 7) * 16;    // + 8 k rows
-  if (OUT_BF16 && vec_ok && TWN % 2 == 0) {
-    // bf16: a row of one tile is only 64 bytes.  Two neighbouring tiles go through the two patches together and 16
-    // consecutive lanes then hold the 128 contiguous bytes of one row (64 columns), so every store writes whole lines.
-    const int rd2 = (lane >> 4) * kPatchStride + (lane & 7) * 16;  // + 4 k rows; patch (lane & 15) >> 3
-    const uint8_t* pr = patch + ((lane & 15) >> 3) * kPatchBytes;
-#pragma unroll
-    for (int i = 0; i < TWM; ++i) {
-#pragma unroll
-      for (int j = 0; j < TWN; j += 2) {
-#pragma unroll
-        for (int t = 0; t < 2; ++t)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            f32x4 q = {acc[i][j + t][4 * g], acc[i][j + t][4 * g + 1], acc[i][j + t][4 * g + 2], acc[i][j + t][4 * g + 3]};
-            *reinterpret_cast<f32x4*>(patch + t * kPatchBytes + wr + 32 * g) = q;
-          }
-        const int64_t col = (tile_n + j) * 32 + 4 * (lane & 15);
-#pragma unroll
-        for (int k = 0; k < 8; ++k) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(pr + rd2 + 4 * k * kPatchStride);
-          const int64_t row = (tile_m + i) * 32 + 4 * k + (lane >> 4);
-          if (row >= M || col >= N) continue;
-          if (col + 3 < N) {
-            u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
-          } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              if (col + q < N) static_cast<uint16_t*>(Dv)[row * ldd + col + q] = (uint16_t)f32_to_bf16_rne(v[q]);
-          }
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int i = 0; i < TWM; ++i) {
-#pragma unroll
-    for (int j = 0; j < TWN; ++j) {
-      uint8_t* pb = patch + ((i * TWN + j) & 1) * kPatchBytes;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        f32x4 q = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
-        *reinterpret_cast<f32x4*>(pb + wr + 32 * g) = q;
-      }
-      const int64_t col = (tile_n + j) * 32 + 4 * (lane & 7);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(pb + rd + 8 * k * kPatchStride);
-        const int64_t row = (tile_m + i) * 32 + 8 * k + (lane >> 3);
-        if (row >= M || col >= N) continue;
-        if (vec_ok && col + 3 < N) {
-          if (OUT_BF16) {
-            u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
-          } else {
-            __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(static_cast<float*>(Dv) + row * ldd + col));
-          }
-        } else {
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
             if (col + q < N) {
@@ -757,16 +658,6 @@ __device__ __forceinline__ void run_tile(uint8_t* lds, const uint8_t* __restrict
 // positions = an 8 x 4 block of tiles sharing 8 A panels and 4 B panels through that XCD's L2.  The workgroups of even
 // XCDs start with one half tile and do their other half tiles last; those of odd XCDs do all their full tiles first: two
 // phase groups whose output bursts do not coincide.
-constexpr int kBand = 4;
-
-__device__ __forceinline__ void band_decode(int p, int rows, int cols, int& r, int& c, int band_cols = kBand) {
-  const int per_band = band_cols * rows;
-  const int band = p / per_band, q = p - band * per_band;
-  const int c0 = band * band_cols;
-  const int w = cols - c0 < band_cols ? cols - c0 : band_cols;
-  r = q / w;
-  c = c0 + (q - r * w);
-}
 
 template <class C, int S, bool DEEP, bool OUT_BF16>
 __global__ void __launch_bounds__(C::THREADS) gemm_kernel_dma(const uint8_t* __restrict__ a_el, const uint8_t* __restrict__ a_sc,
@@ -1909,7 +1800,7 @@ extern "C" size_t mxp_gemm_workspace_bytes_fmt(int64_t M, int64_t N, int64_t K, 
     const bool valid = fmtA >= MXP_FMT_MXFP4 && fmtA <= MXP_FMT_MXFP8P && fmtB >= MXP_FMT_MXFP4 && fmtB <= MXP_FMT_MXFP8P;
     const bool eight = fmtA == MXP_FMT_MXFP8 || fmtA == MXP_FMT_MXFP8P || fmtB == MXP_FMT_MXFP8 || fmtB == MXP_FMT_MXFP8P;
     const bool six_pp = (is_fp6(fmtA) && fmtB == MXP_FMT_MXFP4PP) || (fmtA == MXP_FMT_MXFP4PP && is_fp6(fmtB));
-    if (valid && (eight || six_pp)) return align_up((size_t)M * (size_t)K * 2);
+    if (valid && (eight || six_pp)) return align_up((size_t)M * (size_t)K * 2) + mxp_gemm_w4a16_workspace_bytes(M, N, K, fmtB);
   }
   if (is_fp6(fmtA) && is_fp6(fmtB)) {
     const int n = fp6_plan(fmtA, fmtB).n_seg;
@@ -1984,9 +1875,10 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
     // Without it, both operands are de-converted inside the kernel.
     const size_t a_bf16 = align_up((size_t)M * (size_t)K * 2);
     if (workspace && aligned16(workspace) && workspace_bytes >= a_bf16) {
-      rc8 = mxp_dequantize(A_elems, A_scales, A_idx, fmtA, M, K, workspace, MXP_BF16, K, stream);
+      rc8 = dequantize_bf16_launch(A_elems, A_scales, A_idx, fmtA, M, K, workspace, s8);
       if (rc8 != MXP_OK) return rc8;
-      return mxp_gemm_w4a16(M, N, K, workspace, MXP_BF16, K, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd, stream);
+      return mxp_gemm_w4a16_ws(M, N, K, workspace, MXP_BF16, K, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd,
+                               static_cast<uint8_t*>(workspace) + a_bf16, workspace_bytes - a_bf16, stream);
     }
     return deconv_gemm_launch(M, N, K, A_elems, A_scales, A_idx, fmtA, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd, s8);
   }
@@ -2137,8 +2029,8 @@ extern "C" int mxp_gemm_static(int64_t M, int64_t N, int64_t K, const uint8_t* A
   if (M < 0 || N < 0 || K < 0) return MXP_ERR_SHAPE;
   // (the size functions saturate nowhere near these limits: image bytes of 2^31 x 2^21 elements still fit a size_t)
   if (M > ((int64_t)1 << 31) || N > ((int64_t)1 << 31) || K > mxp::kMaxGemmK) return MXP_ERR_SCRATCH;
-  // pairs multiplied from de-converted operands use the workspace only as an option (A as bf16): too large a product of
-  // that kind runs without it instead of being refused
+  // pairs multiplied from de-converted operands use the workspace only as an option (what fits of A and B as bf16): too
+  // large a product of that kind runs without it instead of being refused
   const bool optional_ws = fmtA >= MXP_FMT_MXFP8 || fmtB >= MXP_FMT_MXFP8 || (is_fp6(fmtA) && fmtB == MXP_FMT_MXFP4PP) ||
                            (fmtA == MXP_FMT_MXFP4PP && is_fp6(fmtB));
   const bool fits = mxp_gemm_workspace_bytes_fmt(M, N, K, fmtA, fmtB) <= kStaticScratchBytes;
@@ -2146,8 +2038,7 @@ extern "C" int mxp_gemm_static(int64_t M, int64_t N, int64_t K, const uint8_t* A
   void* ws = nullptr;
   const int rc = static_scratch(&ws);
   if (rc != MXP_OK) return rc;
-  return mxp_gemm(M, N, K, A_elems, A_scales, A_idx, fmtA, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd, ws, fits ? kStaticScratchBytes : 0,
-                  stream);
+  return mxp_gemm(M, N, K, A_elems, A_scales, A_idx, fmtA, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd, ws, kStaticScratchBytes, stream);
 }
 
 extern "C" size_t mxp_gemm_bf16a_workspace_bytes(int64_t M, int64_t K) {

@@ -542,6 +542,7 @@ inline int kind_of(int fmt) {
     default: return kFp8;
   }
 }
+inline int64_t block_bytes(int fmt) { return fmt < MXP_FMT_MXFP6 ? 16 : fmt < MXP_FMT_MXFP8 ? 24 : 32; }   // codes of one block
 inline int plus_of(int fmt) { return fmt == MXP_FMT_MXFP6P || fmt == MXP_FMT_MXFP8P; }
 
 // un-quantized bf16 activations x weights of any block format
@@ -599,9 +600,40 @@ int deconv_gemm_launch(int64_t M, int64_t N, int64_t K, const uint8_t* ae, const
 }
 }  // namespace mxp
 
+namespace {
+// Rows of W that are de-converted at a time: at most this many bytes of bf16 (the size of the last-level cache, which the
+// product then reads them from), in whole tiles.
+constexpr int64_t kSlabBytes = (int64_t)256 << 20;
+int64_t slab_rows(int64_t N, int64_t K, int64_t bytes) {
+  const int64_t r = bytes / (2 * K);
+  return r >= N ? N : r / 256 * 256;
+}
+// Where W is de-converted once, as bf16, ahead of a plain bf16 product (de-converted per row of tiles -> once, us, bf16 out):
+//   MXFP4+, 14336 x 4096: 160 rows 88.6 -> 60.5, 1024 131 -> 115, 4096 501 -> 363; 4096 x 14336: 160 rows 296 -> 110, 2048 331 -> 205
+//   MXFP8+, 14336 x 4096:  16 rows 162 -> 58.6, 1024 170 -> 119, 4096 668 -> 374; 4096 x 14336:  16 rows 544 -> 105
+// Four-bit W up to 128 rows stays with the few-row kernel (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60); six- and
+// eight-bit W have none.  K = 256 is where the second launch has paid for itself (MXFP4+ 160 x 300: 11.6 -> 11.4).
+bool de_convert_once(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW) {
+  return (M > 128 || fmtW >= MXP_FMT_MXFP6) && K >= 256 && mxp::bf16_gemm_takes(M, N, K, lda);
+}
+}  // namespace
+
+extern "C" size_t mxp_gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K, int fmtW) {
+  if (M <= 0 || N <= 0 || K <= 0 || fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P || !de_convert_once(M, N, K, K, fmtW)) return 0;
+  int64_t r = slab_rows(N, K, kSlabBytes);
+  if (r < 256) r = N < 256 ? N : 256;
+  return ((size_t)r * (size_t)K * 2 + 255) / 256 * 256;
+}
+
 extern "C" int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
                               const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW, void* D,
                               int d_dtype, int64_t ldd, void* stream) {
+  return mxp_gemm_w4a16_ws(M, N, K, A, a_dtype, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, nullptr, 0, stream);
+}
+
+extern "C" int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
+                                 const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW, void* D,
+                                 int d_dtype, int64_t ldd, void* workspace, size_t workspace_bytes, void* stream) {
   using namespace mxp;
   if (fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P) return MXP_ERR_FORMAT;
   const bool wide_w = fmtW >= MXP_FMT_MXFP6;
@@ -615,6 +647,21 @@ extern "C" int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, in
   if (a_dtype != MXP_BF16) return MXP_ERR_UNSUPPORTED;      // the activations are multiplied as bf16
   if (!aligned16(A) || !aligned16(W_elems) || !aligned16(W_scales) || (W_idx && !aligned16(W_idx)) || (lda * 2) % 16 != 0)
     return MXP_ERR_ALIGN;
+  if (workspace && aligned16(workspace) && de_convert_once(M, N, K, lda, fmtW)) {
+    const int64_t slab = slab_rows(N, K, (int64_t)workspace_bytes);
+    if (slab == N || slab >= 2048) {
+      const int64_t nbk = K / kBlock, esz = d_dtype == MXP_BF16 ? 2 : 4, row_bytes = nbk * block_bytes(fmtW);
+      for (int64_t n0 = 0; n0 < N; n0 += slab) {
+        const int64_t nr = N - n0 < slab ? N - n0 : slab;
+        int rc = dequantize_bf16_launch(W_elems + n0 * row_bytes, W_scales + n0 * nbk, W_idx ? W_idx + n0 * nbk : nullptr, fmtW, nr, K,
+                                        workspace, s);
+        if (rc != MXP_OK) return rc;
+        rc = bf16_gemm_launch(M, nr, K, A, lda, workspace, K, static_cast<uint8_t*>(D) + n0 * esz, d_dtype, ldd, s);
+        if (rc != MXP_OK) return rc;
+      }
+      return MXP_OK;
+    }
+  }
   // six- and eight-bit weights: the tiled kernel at any number of rows
   if (wide_w) return dispatch_tiled(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
   if (M > 64 && M <= 128) {

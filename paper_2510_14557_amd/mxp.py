@@ -22,7 +22,7 @@ LIB_PATH = os.path.join(_HERE, "libmxp.so")
 
 EXPORTS = ("mxp_quantize", "mxp_quantize_t", "mxp_quantize_gather", "mxp_dequantize", "mxp_image_bytes", "mxp_prepack", "mxp_quantize_image",
            "mxp_image_bytes_e2m1", "mxp_prepack_e2m1", "mxp_image_bytes_e2m1r", "mxp_prepack_e2m1r", "mxp_prepack_e2m1x", "mxp_image_bytes_e4m3", "mxp_prepack_e4m3", "mxp_gemm_workspace_bytes", "mxp_gemm_workspace_bytes_e4m3", "mxp_gemm_workspace_bytes_fmt", "mxp_image_bytes_fp6", "mxp_prepack_fp6", "mxp_quantize_image_fp6", "mxp_prepack_seg", "mxp_prepack_fp8", "mxp_gemm", "mxp_gemm_prepacked", "mxp_gemm_bf16a_workspace_bytes", "mxp_gemm_decode", "mxp_gemm_decode_bf16a",
-           "mxp_gemm_bf16a", "mxp_gemm_w4a16", "mxp_convert_operands", "mxp_gemm_workspace_size", "mxp_gemm_static", "mxp_gemm_static_capacity", "mxp_status_string", "mxp_version")
+           "mxp_gemm_bf16a", "mxp_gemm_w4a16", "mxp_gemm_w4a16_workspace_bytes", "mxp_gemm_w4a16_ws", "mxp_convert_operands", "mxp_gemm_workspace_size", "mxp_gemm_static", "mxp_gemm_static_capacity", "mxp_status_string", "mxp_version")
 
 _lib = None
 
@@ -87,6 +87,10 @@ def lib():
     L.mxp_gemm_bf16a.argtypes = [i64, i64, i64, vp, i32, i64, i32, vp, i32, vp, i32, i64, vp, sz, vp]
     L.mxp_gemm_w4a16.argtypes = [i64, i64, i64, vp, i32, i64, vp, vp, vp, i32, vp, i32, i64, vp]
     L.mxp_gemm_w4a16.restype = i32
+    L.mxp_gemm_w4a16_workspace_bytes.argtypes = [i64, i64, i64, i32]
+    L.mxp_gemm_w4a16_workspace_bytes.restype = sz
+    L.mxp_gemm_w4a16_ws.argtypes = [i64, i64, i64, vp, i32, i64, vp, vp, vp, i32, vp, i32, i64, vp, sz, vp]
+    L.mxp_gemm_w4a16_ws.restype = i32
     L.mxp_convert_operands.argtypes = [vp, i32, i64, i64, i64, i32, vp, vp, vp, vp, sz, vp, vp, vp, i32, i64, vp, sz, vp]
     L.mxp_convert_operands.restype = i32
     L.mxp_gemm_static.argtypes = [i64, i64, i64, vp, vp, vp, i32, vp, vp, vp, i32, vp, i32, i64, vp]
@@ -379,7 +383,13 @@ def gemm(qa, fmt_a, qb, fmt_b, out_dtype: torch.dtype = torch.float32, out: torc
     if out is None:
         out = torch.empty((M, N), dtype=out_dtype, device=ae.device)
     if workspace is None:
-        workspace = torch.empty(max(gemm_workspace_bytes(M, N, K, fmt_a, fmt_b), 16), dtype=torch.uint8, device=ae.device)
+        nbytes = max(gemm_workspace_bytes(M, N, K, fmt_a, fmt_b), 16)
+        pair = (fmt_a, fmt_b)
+        if max(pair) >= MXFP8 or (MXFP4PP in pair and max(pair) >= MXFP6):
+            workspace = _optional_workspace(nbytes, ae.device)   # both operands as bf16; A alone, or neither, also does
+            nbytes = 2 * M * K
+        if workspace is None:
+            workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=ae.device)
     ldd = out.stride(0) if M > 1 else max(N, 1)
     _check(lib().mxp_gemm(M, N, K, _p(ae), _p(as_), _p(ai), fmt_a, _p(be), _p(bs), _p(bi), fmt_b, _p(out), _dt(out), ldd,
                           _p(workspace), workspace.numel(), _stream()), "mxp_gemm")
@@ -443,6 +453,16 @@ def gemm_decode_bf16a(a: torch.Tensor, fmt_a: int, qw, fmt_w: int = MXFP4P, out_
     return out
 
 
+def _optional_workspace(nbytes: int, device):
+    """Room that a call can do without: None where there is none to give."""
+    if nbytes == 0:
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.cuda.OutOfMemoryError:
+        return None
+
+
 def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None):
     """Un-quantized bf16 activations x canonical weights of any block format, de-converted inside the kernel (4-bit weights:
     few-row kernel for M <= 64; otherwise 256 x 256 tiles on the bf16 MFMA)."""
@@ -456,8 +476,10 @@ def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype 
         out = torch.empty((M, N), dtype=out_dtype, device=a.device)
     lda = a.stride(0) if M > 1 else max(K, 1)
     ldd = out.stride(0) if M > 1 else max(N, 1)
-    _check(lib().mxp_gemm_w4a16(M, N, K, _p(a), _dt(a), lda, _p(we), _p(ws), _p(wi), fmt_w, _p(out), _dt(out), ldd, _stream()),
-           "mxp_gemm_w4a16")
+    nbytes = int(lib().mxp_gemm_w4a16_workspace_bytes(M, N, K, fmt_w))
+    workspace = _optional_workspace(nbytes, a.device)
+    _check(lib().mxp_gemm_w4a16_ws(M, N, K, _p(a), _dt(a), lda, _p(we), _p(ws), _p(wi), fmt_w, _p(out), _dt(out), ldd, _p(workspace),
+                                   nbytes if workspace is not None else 0, _stream()), "mxp_gemm_w4a16")
     return out
 
 

@@ -2066,3 +2066,30 @@ def test_calls_from_two_threads_on_two_streams():
         qa_o, qw_o = oracle.quantize(data[i][0], oracle.MXFP4P), oracle.quantize(data[i][1], oracle.MXFP4P)
         ref, S = oracle.gemm(qa_o, oracle.MXFP4P, qw_o, oracle.MXFP4P)
         check_gemm(got[i][1], ref, S, "thread %d" % i)
+
+
+@pytest.mark.parametrize("M,N,K", [(129, 300, 256), (200, 65, 288), (130, 2500, 320), (257, 129, 352), (1100, 4500, 256), (4100, 4100, 288)])
+@pytest.mark.parametrize("fmt", ["mxfp4", "mxfp4pp", "mxfp6p", "mxfp8p"])
+def test_gemm_w4a16_weights_deconverted_once(fmt, M, N, K):
+    """W as bf16 in a workspace ahead of the product: the same products in the same order as de-conversion inside the kernel,
+    so identical bits -- blocks of 128 x 128, full and half tiles, an odd number of K steps, a last step of one block, W in
+    one piece and in slabs, both output types, into padded rows."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    code = {n: c for n, (c, _) in {**FMT, **WIDE}.items()}[fmt]
+    a = torch.randn((M, K + 8), generator=gen, device="cuda").to(torch.bfloat16)[:, :K]
+    qw = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16), code)
+    L = mxp.lib()
+    need = L.mxp_gemm_w4a16_workspace_bytes(M, N, K, code)
+    assert need >= 2 * N * K
+    for dt in (torch.float32, torch.bfloat16):
+        outs = []
+        for nbytes in (0, need, 2048 * K * 2):
+            ws = torch.full((max(nbytes, 16),), 255, dtype=torch.uint8, device="cuda")
+            d = torch.full((M, N + 4), float("nan"), dtype=dt, device="cuda")
+            rc = L.mxp_gemm_w4a16_ws(M, N, K, a.data_ptr(), mxp.BF16, a.stride(0), qw[0].data_ptr(), qw[1].data_ptr(), qw[2].data_ptr(), code,
+                                     d.data_ptr(), mxp._dt(d), N + 4, ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+            assert rc == 0 and bool(d[:, N:].isnan().all())
+            outs.append(d[:, :N])
+        assert bool(outs[0].isfinite().all())
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (fmt, M, N, K, dt)
