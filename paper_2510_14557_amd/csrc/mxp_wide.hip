@@ -108,9 +108,11 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(uint32_t bits) {
   return (bits + 0x7FFFu + ((bits >> 16) & 1u)) >> 16;
 }
 
+constexpr int kDequantUnroll = 4;                    // groups per lane and pass of the de-conversion
+
 // ---- quantize -------------------------------------------------------------------------------------------------
 // nq = number of 8-element groups (4 per block); a quad of lanes is one block, so a quad is inside or outside as a whole.
-template <bool BF16, int BITS, bool PLUS>
+template <bool BF16, int BITS, bool PLUS, bool DENSE>
 __global__ void __launch_bounds__(256) quantize_wide_kernel(const void* __restrict__ src, int64_t nbk, int64_t ld, int64_t nq,
                                                             uint8_t* __restrict__ elems, uint8_t* __restrict__ scales,
                                                             uint8_t* __restrict__ bm_idx) {
@@ -119,8 +121,11 @@ __global__ void __launch_bounds__(256) quantize_wide_kernel(const void* __restri
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; (q & ~(int64_t)3) < nq; q += stride) {
     const int64_t g = q >> 2;                       // block
-    const int64_t row = g / nbk;
-    const int64_t off = row * ld + (g - row * nbk) * 32 + part * 8;
+    int64_t off = q * 8;
+    if (!DENSE) {                                   // rows with a gap between them
+      const int64_t row = g / nbk;
+      off = row * ld + (g - row * nbk) * 32 + part * 8;
+    }
     uint32_t a[8], sg[8], raw[8];
     if (BF16) {
       const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(src) + off);
@@ -246,7 +251,7 @@ typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v32f __attribute__((ext_vector_type(32)));
 constexpr int kQuadLane0 = 0x00, kQuadLane1 = 0x55, kQuadLane2 = 0xAA, kQuadLane3 = 0xFF;   // quad_perm broadcasts
 
-template <bool BF16, bool PLUS>
+template <bool BF16, bool PLUS, bool DENSE>
 __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restrict__ src, int64_t nbk, int64_t ld, int64_t nq,
                                                            uint8_t* __restrict__ elems, uint8_t* __restrict__ scales,
                                                            uint8_t* __restrict__ bm_idx) {
@@ -255,19 +260,20 @@ __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restric
   const uint32_t part = threadIdx.x & 3u;
   const int64_t stride = (int64_t)gridDim.x * 256;
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; (q & ~(int64_t)3) < nq; q += stride) {
-    const int64_t g = q >> 2;
-    const int64_t row = g / nbk;
-    const int64_t off = row * ld + (g - row * nbk) * 32 + part * 8;
-    uint32_t w[NW], a[8], sg[8];
+    const int64_t g = q >> 2;                       // block
+    int64_t off = q * 8;
+    if (!DENSE) {                                   // rows with a gap between them
+      const int64_t row = g / nbk;
+      off = row * ld + (g - row * nbk) * 32 + part * 8;
+    }
+    uint32_t w[NW], a[8];
     if (BF16) {
       const u32x4 v = *reinterpret_cast<const u32x4*>(static_cast<const uint16_t*>(src) + off);
       w[0] = v.x; w[1] = v.y; w[2] = v.z; w[3] = v.w;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         a[2 * j] = (w[j] << 16) & 0x7FFF0000u;
-        sg[2 * j] = (w[j] >> 15) & 1u;
         a[2 * j + 1] = w[j] & 0x7FFF0000u;
-        sg[2 * j + 1] = w[j] >> 31;
       }
     } else {
       const u32x4* p = reinterpret_cast<const u32x4*>(static_cast<const float*>(src) + off);
@@ -277,7 +283,6 @@ __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restric
       for (int i = 0; i < 8; ++i) {
         w[i] = t[i];
         a[i] = t[i] & 0x7FFFFFFFu;
-        sg[i] = t[i] >> 31;
       }
     }
     uint32_t mx = a[0];
@@ -285,19 +290,11 @@ __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restric
     for (int i = 1; i < 8; ++i) mx = umax(mx, a[i]);
     mx = umax(mx, dpp_mov<kQuadSwap1>(mx));
     mx = umax(mx, dpp_mov<kQuadSwap2>(mx));
-    uint32_t pos = 32u, bm_sign = 0;
+    uint32_t pos = 32u;                             // lowest position holding the maximum
 #pragma unroll
-    for (int i = 7; i >= 0; --i) {
-      const bool hit = a[i] == mx;
-      pos = hit ? part * 8u + (uint32_t)i : pos;
-      bm_sign = hit ? sg[i] : bm_sign;                // sign at this lane's lowest hit
-    }
-    // lowest position over the quad, and the sign that goes with it
-    uint32_t key = (pos << 1) | bm_sign;
-    key = umin(key, dpp_mov<kQuadSwap1>(key));
-    key = umin(key, dpp_mov<kQuadSwap2>(key));
-    pos = key >> 1;
-    bm_sign = key & 1u;
+    for (int i = 7; i >= 0; --i) pos = a[i] == mx ? part * 8u + (uint32_t)i : pos;
+    pos = umin(pos, dpp_mov<kQuadSwap1>(pos));
+    pos = umin(pos, dpp_mov<kQuadSwap2>(pos));
     const uint32_t E = mx >> 23;
     const bool flush = E <= (uint32_t)F::EMAX, nonfinite = E == 255u;
     const int sbyte = (int)E - F::EMAX;
@@ -330,12 +327,13 @@ __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restric
     uint32_t s0 = part == 0u ? r[0] : (part == 1u ? r[2] : r[4]);
     uint32_t s1 = part == 0u ? r[1] : (part == 1u ? r[3] : r[5]);
     if (PLUS) {
-      // BM code sign | mmmmm at bit 6 pos of the block's string = bit rel of this share (may hang over either edge)
-      const uint32_t code = (bm_sign << 5) | bm_code<6>(mx);
+      // the BM's magnitude mmmmm at bit 6 pos of the block's string = bit rel of this share (may hang over either edge); its
+      // sign is there already: a BM is at least 4 X, and the conversion keeps the sign
+      const uint32_t code = bm_code<6>(mx);
       const int rel = (int)(6u * pos) - 64 * (int)part;
       uint64_t share = ((uint64_t)s1 << 32) | s0;
       if (rel > -6 && rel < 64) {
-        const uint64_t m = rel >= 0 ? ((uint64_t)0x3Fu << rel) : ((uint64_t)0x3Fu >> (-rel));
+        const uint64_t m = rel >= 0 ? ((uint64_t)0x1Fu << rel) : ((uint64_t)0x1Fu >> (-rel));
         const uint64_t c = rel >= 0 ? ((uint64_t)code << rel) : ((uint64_t)code >> (-rel));
         share = (share & ~m) | c;
       }
@@ -357,160 +355,162 @@ __global__ void __launch_bounds__(256) quantize_fp6_kernel(const void* __restric
 }
 
 // ---- de-conversion (Eq. 2) ------------------------------------------------------------------------------------
-template <int BITS, bool PLUS, bool OUT_BF16>
+// Any codes and scale bytes, from integer fields: the blocks whose results can be below the normal range, overflow or
+// special.  f: this lane's eight values as fp32 patterns.
+template <int BITS>
+__device__ __forceinline__ void decode_any(uint32_t lo, uint32_t hi, uint32_t sbyte, uint32_t bm_in_part, uint32_t (&f)[8]) {
+  using F = Elem<BITS>;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int b = i * BITS;
+    uint32_t c = b < 32 ? (lo >> b) : (hi >> (b - 32));
+    if (b < 32 && b + BITS > 32) c |= hi << (32 - b);
+    c &= (1u << BITS) - 1u;
+    const uint32_t sign = c >> (BITS - 1), mag = c & ((1u << (BITS - 1)) - 1u);
+    uint32_t bits;
+    if (bm_in_part == (uint32_t)i) {
+      // BM: 2^e_max * 1.m with BITS - 1 fraction bits
+      bits = make_f32(sign, (1u << (BITS - 1)) | mag, F::EMAX - (BITS - 1) + (int)sbyte - 127);
+    } else {
+      const uint32_t e = mag >> F::MB, m = mag & ((1u << F::MB) - 1u);
+      const uint32_t M = e ? ((1u << F::MB) | m) : m;            // subnormal: 0.m at the first binade's exponent
+      bits = make_f32(sign, M, (int)(e ? e : 1u) - F::BIAS - F::MB + (int)sbyte - 127);
+    }
+    if (sbyte == 0u) bits = 0u;                                  // reserved all-zero code, tested before anything else
+    if (sbyte == 255u) bits = 0x7FC00000u;
+    f[i] = bits;
+  }
+}
+
+// A quad of lanes is a block, a lane gives eight of its values (one or two 16-byte stores).  Bound by the vector ALU
+// rather than by memory unless the instructions per lane are few: no 64-bit division where rows follow each other without
+// a gap (DENSE), the BM's bits put together from fields, general blocks out of line.  A lane takes U groups 256 apart, all
+// loads of them ahead of the first use, so that scale, index and code bytes are one round trip and not three.
+template <int BITS, bool PLUS, bool OUT_BF16, bool DENSE>
 __global__ void __launch_bounds__(256) dequantize_wide_kernel(const uint8_t* __restrict__ elems, const uint8_t* __restrict__ scales,
                                                               const uint8_t* __restrict__ bm_idx, int64_t nbk, int64_t ld,
                                                               int64_t nq, void* __restrict__ dst) {
   using F = Elem<BITS>;
-  const uint32_t part = threadIdx.x & 3u;
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < nq; q += stride) {
-    const int64_t g = q >> 2;
-    const int64_t row = g / nbk;
-    const int64_t off = row * ld + (g - row * nbk) * 32 + part * 8;
-    // Common case (no result below the normal range, no overflow, no E4M3 NaN code): the CDNA4 unpack-convert
-    // instructions, value * X exact in both output types; the lane that holds the BM then writes it over its element.
-    {
-      const uint32_t sb = scales[g];
-      if (sb >= 16u && sb <= 240u) {
+  constexpr int U = kDequantUnroll, NR = BITS == 8 ? 2 : 6;
+  const uint32_t tid = threadIdx.x, part = tid & 3u;
+  const int64_t ng = nq >> 2;
+  for (int64_t q0 = (int64_t)blockIdx.x * (256 * U); q0 < nq; q0 += (int64_t)gridDim.x * (256 * U)) {
+    uint32_t sbs[U], bms[U], raw[U][NR];
+    int64_t gs[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int64_t g = (q0 >> 2) + 64 * u + (tid >> 2);
+      g = g < ng ? g : ng - 1;                       // past the end: the last block again, not stored
+      gs[u] = g;
+      sbs[u] = scales[g];
+      bms[u] = PLUS ? (uint32_t)bm_idx[g] : 0u;
+      if constexpr (BITS == 8) {
+        const u32x2 v = *reinterpret_cast<const u32x2*>(elems + g * 32 + part * 8);
+        raw[u][0] = v.x; raw[u][1] = v.y;
+      } else {
+        const u32x2* in = reinterpret_cast<const u32x2*>(elems + g * 24);
+        const u32x2 d0 = in[0], d1 = in[1], d2 = in[2];
+        raw[u][0] = d0.x; raw[u][1] = d0.y; raw[u][2] = d1.x; raw[u][3] = d1.y; raw[u][4] = d2.x; raw[u][5] = d2.y;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t sb = sbs[u];
+      const uint32_t bm = PLUS ? (bms[u] & 31u) - part * 8u : 64u;     // the BM's place among this lane's eight; above 7: not here
+      // this lane's own code bits: 48 (lo, hi[15:0]) or 64
+      uint32_t lo, hi;
+      if constexpr (BITS == 8) {
+        lo = raw[u][0];
+        hi = raw[u][1];
+      } else {
+        const uint32_t w0 = part == 0u ? raw[u][0] : (part == 1u ? raw[u][1] : (part == 2u ? raw[u][3] : raw[u][4]));
+        const uint32_t w1 = part == 0u ? raw[u][1] : (part == 1u ? raw[u][2] : (part == 2u ? raw[u][4] : raw[u][5]));
+        const uint64_t both = (((uint64_t)w1 << 32) | w0) >> (16u * (part & 1u));
+        lo = (uint32_t)both;
+        hi = (uint32_t)(both >> 32) & 0xFFFFu;
+      }
+      // Common case (no result below the normal range, no overflow, no E4M3 NaN code among the ordinary elements): the CDNA4
+      // unpack-convert instructions, value * X exact in both output types; the lane that holds the BM then writes it over
+      // its element.
+      bool plain = sb >= 16u && sb <= 240u;
+      if (BITS == 8) {
+        uint64_t nanlike = ((uint64_t)(((hi & 0x7F7F7F7Fu) + 0x01010101u) & 0x80808080u) << 32) | (((lo & 0x7F7F7F7Fu) + 0x01010101u) & 0x80808080u);
+        if (PLUS && bm < 8u) nanlike &= ~((uint64_t)0x80u << (8u * bm));          // the BM's byte is all mantissa
+        plain = plain && nanlike == 0u;
+      }
+      uint32_t f[8], hb[4];
+      if (plain) {
         const float X = __uint_as_float(sb << 23);
-        const uint32_t bmq = PLUS ? (bm_idx[g] & 31u) : 64u;
-        const bool mine = PLUS && (bmq >> 3) == part;
-        const uint32_t pi = bmq & 7u;
-        uint32_t f[8], hb[4];
-        bool done = true;
-        if (BITS == 8) {
-          const u32x2 v = *reinterpret_cast<const u32x2*>(elems + g * 32 + part * 8);
-          // bytes whose low seven bits are all ones (S.1111.111) take the general path below
-          const uint32_t nanlike = (((v.x & 0x7F7F7F7Fu) + 0x01010101u) | ((v.y & 0x7F7F7F7Fu) + 0x01010101u)) & 0x80808080u;
-          done = nanlike == 0u;
-          if (done) {
-            const uint32_t code = ((pi < 4u ? v.x : v.y) >> (8u * (pi & 3u))) & 0xFFu;
-            const uint32_t bmbits = make_f32(code >> 7, 128u | (code & 127u), F::EMAX - 7 + (int)sb - 127);
-            if (OUT_BF16) {
-              union { v2bf v; uint32_t u; } c0, c1, c2, c3;
-              c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.x, X, false);
-              c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.x, X, true);
-              c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.y, X, false);
-              c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(v.y, X, true);
-              hb[0] = c0.u; hb[1] = c1.u; hb[2] = c2.u; hb[3] = c3.u;
-            } else {
-              const v2f f0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v.x, X, false), f1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v.x, X, true);
-              const v2f f2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v.y, X, false), f3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v.y, X, true);
-              f[0] = __float_as_uint(f0[0]); f[1] = __float_as_uint(f0[1]); f[2] = __float_as_uint(f1[0]); f[3] = __float_as_uint(f1[1]);
-              f[4] = __float_as_uint(f2[0]); f[5] = __float_as_uint(f2[1]); f[6] = __float_as_uint(f3[0]); f[7] = __float_as_uint(f3[1]);
-            }
-            if (mine) {
-              if (OUT_BF16) {
-                const uint32_t sh = (pi & 1u) * 16u;
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                  if ((pi >> 1) == (uint32_t)j) hb[j] = (hb[j] & ~(0xFFFFu << sh)) | ((bmbits >> 16) << sh);
-              } else {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                  if (pi == (uint32_t)i) f[i] = bmbits;
-              }
-            }
-          }
-        } else {
-          const u32x2* in = reinterpret_cast<const u32x2*>(elems + g * 24);
-          const u32x2 d0 = in[0], d1 = in[1], d2 = in[2];
-          const v6u str = {d0.x, d0.y, d1.x, d1.y, d2.x, d2.y};
-          // the BM's code, from this lane's own 48 bits
-          const uint32_t first = (part >> 1) * 3u + (part & 1u);
-          const uint32_t w0 = first == 0u ? d0.x : (first == 1u ? d0.y : (first == 3u ? d1.y : d2.x));
-          const uint32_t w1 = first == 0u ? d0.y : (first == 1u ? d1.x : (first == 3u ? d2.x : d2.y));
-          const uint64_t mine48 = (part & 1u) ? (((uint64_t)w1 << 16) | (w0 >> 16)) : (((uint64_t)(w1 & 0xFFFFu) << 32) | w0);
-          const uint32_t code = (uint32_t)(mine48 >> (6u * pi)) & 0x3Fu;
-          const uint32_t bmbits = make_f32(code >> 5, 32u | (code & 31u), F::EMAX - 5 + (int)sb - 127);
-          if (OUT_BF16) {
+        const uint32_t code = (uint32_t)((((uint64_t)hi << 32) | lo) >> (((uint32_t)BITS * bm) & 63u)) & ((1u << BITS) - 1u);
+        // 2^e_max * 1.m * X: sign | exponent field sb + e_max | BITS - 1 mantissa bits, left-aligned
+        const uint32_t bmh = ((code >> (BITS - 1)) << 15) | ((sb + (uint32_t)F::EMAX) << 7) | ((code & ((1u << (BITS - 1)) - 1u)) << (8 - BITS));
+        if (OUT_BF16) {
+          if constexpr (BITS == 8) {
+            union { v2bf v; uint32_t u; } c0, c1, c2, c3;
+            c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, X, false);
+            c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(lo, X, true);
+            c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, X, false);
+            c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, X, true);
+            hb[0] = c0.u; hb[1] = c1.u; hb[2] = c2.u; hb[3] = c3.u;
+          } else {
+            const v6u str = {raw[u][0], raw[u][1], raw[u][2], raw[u][3], raw[u][4], raw[u][5]};
             union { v32bf v; uint32_t u[16]; } c;
             c.v = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(str, X);
 #pragma unroll
             for (int j = 0; j < 4; ++j)
               hb[j] = part == 0u ? c.u[j] : (part == 1u ? c.u[4 + j] : (part == 2u ? c.u[8 + j] : c.u[12 + j]));
-            if (mine) {
-              const uint32_t sh = (pi & 1u) * 16u;
+          }
+          if (PLUS) {
+            const uint32_t mask = (bm & 1u) ? 0xFFFF0000u : 0xFFFFu, put = bmh | (bmh << 16);
 #pragma unroll
-              for (int j = 0; j < 4; ++j)
-                if ((pi >> 1) == (uint32_t)j) hb[j] = (hb[j] & ~(0xFFFFu << sh)) | ((bmbits >> 16) << sh);
+            for (int j = 0; j < 4; ++j) {
+              const uint32_t m = (bm >> 1) == (uint32_t)j ? mask : 0u;
+              hb[j] = (hb[j] & ~m) | (put & m);
             }
+          }
+        } else {
+          if constexpr (BITS == 8) {
+            const v2f f0 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, X, false), f1 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(lo, X, true);
+            const v2f f2 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, X, false), f3 = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(hi, X, true);
+            f[0] = __float_as_uint(f0[0]); f[1] = __float_as_uint(f0[1]); f[2] = __float_as_uint(f1[0]); f[3] = __float_as_uint(f1[1]);
+            f[4] = __float_as_uint(f2[0]); f[5] = __float_as_uint(f2[1]); f[6] = __float_as_uint(f3[0]); f[7] = __float_as_uint(f3[1]);
           } else {
+            const v6u str = {raw[u][0], raw[u][1], raw[u][2], raw[u][3], raw[u][4], raw[u][5]};
             union { v32f v; uint32_t u[32]; } c;
             c.v = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(str, X);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
               f[i] = part == 0u ? c.u[i] : (part == 1u ? c.u[8 + i] : (part == 2u ? c.u[16 + i] : c.u[24 + i]));
-            if (mine) {
+          }
+          if (PLUS) {
 #pragma unroll
-              for (int i = 0; i < 8; ++i)
-                if (pi == (uint32_t)i) f[i] = bmbits;
-            }
+            for (int i = 0; i < 8; ++i) f[i] = bm == (uint32_t)i ? bmh << 16 : f[i];
           }
         }
-        if (done) {
-          if (OUT_BF16) {
-            *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst) + off) = u32x4{hb[0], hb[1], hb[2], hb[3]};
-          } else {
-            u32x4* o = reinterpret_cast<u32x4*>(static_cast<float*>(dst) + off);
-            o[0] = u32x4{f[0], f[1], f[2], f[3]};
-            o[1] = u32x4{f[4], f[5], f[6], f[7]};
-          }
-          continue;
+      } else {
+        decode_any<BITS>(lo, hi, sb, bm, f);
+        if (OUT_BF16) {
+          uint32_t h[8];
+#pragma unroll
+          for (int i = 0; i < 8; ++i) h[i] = sb == 255u ? 0x7FC0u : f32_to_bf16_rne(f[i]);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) hb[j] = h[2 * j] | (h[2 * j + 1] << 16);
         }
       }
-    }
-    uint32_t lo, hi;
-    if (BITS == 8) {
-      const u32x2 v = *reinterpret_cast<const u32x2*>(elems + g * 32 + part * 8);
-      lo = v.x;
-      hi = v.y;
-    } else {
-      const uint32_t* in = reinterpret_cast<const uint32_t*>(elems + g * 24);
-      const uint32_t first = (part >> 1) * 3u + (part & 1u);       // dwords 0,1 / 1,2 / 3,4 / 4,5
-      const uint32_t w0 = in[first], w1 = in[first + 1];
-      if (part & 1u) {
-        lo = (w0 >> 16) | (w1 << 16);
-        hi = w1 >> 16;
-      } else {
-        lo = w0;
-        hi = w1 & 0xFFFFu;
+      if (q0 + 256 * u + tid < nq) {
+        int64_t off = q0 * 8 + (256 * u + tid) * 8u;
+        if (!DENSE) {
+          const int64_t row = gs[u] / nbk;
+          off = row * ld + (gs[u] - row * nbk) * 32 + part * 8;
+        }
+        if (OUT_BF16) {
+          *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst) + off) = u32x4{hb[0], hb[1], hb[2], hb[3]};
+        } else {
+          u32x4* o = reinterpret_cast<u32x4*>(static_cast<float*>(dst) + off);
+          o[0] = u32x4{f[0], f[1], f[2], f[3]};
+          o[1] = u32x4{f[4], f[5], f[6], f[7]};
+        }
       }
-    }
-    const uint32_t sbyte = scales[g];
-    const uint32_t bm = PLUS ? (bm_idx[g] & 31u) : 64u;
-    uint32_t f[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int b = i * BITS;
-      uint32_t c = b < 32 ? (lo >> b) : (hi >> (b - 32));
-      if (b < 32 && b + BITS > 32) c |= hi << (32 - b);
-      c &= (1u << BITS) - 1u;
-      const uint32_t sign = c >> (BITS - 1), mag = c & ((1u << (BITS - 1)) - 1u);
-      uint32_t bits;
-      if (PLUS && bm == part * 8u + (uint32_t)i) {
-        // BM: 2^e_max * 1.m with BITS - 1 fraction bits
-        bits = make_f32(sign, (1u << (BITS - 1)) | mag, F::EMAX - (BITS - 1) + (int)sbyte - 127);
-      } else {
-        const uint32_t e = mag >> F::MB, m = mag & ((1u << F::MB) - 1u);
-        const uint32_t M = e ? ((1u << F::MB) | m) : m;            // subnormal: 0.m at the first binade's exponent
-        bits = make_f32(sign, M, (int)(e ? e : 1u) - F::BIAS - F::MB + (int)sbyte - 127);
-      }
-      if (sbyte == 0u) bits = 0u;                                  // reserved all-zero code, tested before anything else
-      if (sbyte == 255u) bits = 0x7FC00000u;
-      f[i] = bits;
-    }
-    if (OUT_BF16) {
-      uint32_t h[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) h[i] = sbyte == 255u ? 0x7FC0u : f32_to_bf16_rne(f[i]);
-      *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst) + off) =
-          u32x4{h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16)};
-    } else {
-      u32x4* o = reinterpret_cast<u32x4*>(static_cast<float*>(dst) + off);
-      o[0] = u32x4{f[0], f[1], f[2], f[3]};
-      o[1] = u32x4{f[4], f[5], f[6], f[7]};
     }
   }
 }
@@ -768,10 +768,20 @@ int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K
                          uint8_t* scales, uint8_t* bm_idx, hipStream_t s) {
   const int64_t nbk = K / kBlock, nq = rows * nbk * 4;
   const dim3 grid = grid_for(nq);
-  const bool bf = src_dtype == MXP_BF16;
-#define MXP_LAUNCH_QW(B, BT, P) hipLaunchKernelGGL((quantize_wide_kernel<B, BT, P>), grid, dim3(256), 0, s, src, nbk, ld_src, nq, elems, scales, bm_idx)
+  const bool bf = src_dtype == MXP_BF16, dense = rows == 1 || ld_src == K;
+#define MXP_LAUNCH_QK(KERNEL) hipLaunchKernelGGL((KERNEL), grid, dim3(256), 0, s, src, nbk, ld_src, nq, elems, scales, bm_idx)
+#define MXP_COMMA ,
+#define MXP_LAUNCH_QW(B, BT, P)                                                            \
+  do {                                                                                     \
+    if (dense) MXP_LAUNCH_QK(quantize_wide_kernel<B MXP_COMMA BT MXP_COMMA P MXP_COMMA true>);  \
+    else MXP_LAUNCH_QK(quantize_wide_kernel<B MXP_COMMA BT MXP_COMMA P MXP_COMMA false>);       \
+  } while (0)
   switch (fmt) {
-#define MXP_LAUNCH_Q6(B, P) hipLaunchKernelGGL((quantize_fp6_kernel<B, P>), grid, dim3(256), 0, s, src, nbk, ld_src, nq, elems, scales, bm_idx)
+#define MXP_LAUNCH_Q6(B, P)                                                     \
+  do {                                                                          \
+    if (dense) MXP_LAUNCH_QK(quantize_fp6_kernel<B MXP_COMMA P MXP_COMMA true>);    \
+    else MXP_LAUNCH_QK(quantize_fp6_kernel<B MXP_COMMA P MXP_COMMA false>);         \
+  } while (0)
     case MXP_FMT_MXFP6: if (bf) MXP_LAUNCH_Q6(true, false); else MXP_LAUNCH_Q6(false, false); break;
     case MXP_FMT_MXFP6P: if (bf) MXP_LAUNCH_Q6(true, true); else MXP_LAUNCH_Q6(false, true); break;
 #undef MXP_LAUNCH_Q6
@@ -780,15 +790,23 @@ int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K
     default: return MXP_ERR_FORMAT;
   }
 #undef MXP_LAUNCH_QW
+#undef MXP_COMMA
+#undef MXP_LAUNCH_QK
   return launch_status();
 }
 
 int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows,
                            int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t s) {
   const int64_t nbk = K / kBlock, nq = rows * nbk * 4;
-  const dim3 grid = grid_for(nq);
-  const bool bf = dst_dtype == MXP_BF16;
-#define MXP_LAUNCH_DW(BT, P, O) hipLaunchKernelGGL((dequantize_wide_kernel<BT, P, O>), grid, dim3(256), 0, s, elems, scales, bm_idx, nbk, ld_dst, nq, dst)
+  const int64_t want = (nq + 256 * kDequantUnroll - 1) / (256 * kDequantUnroll), cap = (int64_t)1 << 24;
+  const dim3 grid((unsigned)(want < cap ? want : cap));
+  const bool bf = dst_dtype == MXP_BF16, dense = rows == 1 || ld_dst == K;
+#define MXP_LAUNCH_DWD(BT, P, O, DN) hipLaunchKernelGGL((dequantize_wide_kernel<BT, P, O, DN>), grid, dim3(256), 0, s, elems, scales, bm_idx, nbk, ld_dst, nq, dst)
+#define MXP_LAUNCH_DW(BT, P, O)                      \
+  do {                                               \
+    if (dense) MXP_LAUNCH_DWD(BT, P, O, true);       \
+    else MXP_LAUNCH_DWD(BT, P, O, false);            \
+  } while (0)
   switch (fmt) {
     case MXP_FMT_MXFP6: if (bf) MXP_LAUNCH_DW(6, false, true); else MXP_LAUNCH_DW(6, false, false); break;
     case MXP_FMT_MXFP6P: if (bf) MXP_LAUNCH_DW(6, true, true); else MXP_LAUNCH_DW(6, true, false); break;
@@ -796,6 +814,7 @@ int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const ui
     case MXP_FMT_MXFP8P: if (bf) MXP_LAUNCH_DW(8, true, true); else MXP_LAUNCH_DW(8, true, false); break;
     default: return MXP_ERR_FORMAT;
   }
+#undef MXP_LAUNCH_DWD
 #undef MXP_LAUNCH_DW
   return launch_status();
 }

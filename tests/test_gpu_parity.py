@@ -827,6 +827,28 @@ def test_wide_round_trip_full_size(fmt):
     assert (back[torch.from_numpy(rows).cuda()].float().cpu().numpy().astype(np.float64) == ref).all()
 
 
+@pytest.mark.parametrize("fmt", list(WIDE))
+@pytest.mark.parametrize("rows,K", [(1, 32), (255, 32), (51, 160), (257, 32), (1, 8192 + 32), (7, 4704)])
+def test_wide_pass_edges_dense_and_strided(fmt, rows, K):
+    """Block counts just below, at and above what a workgroup takes per pass (256 blocks), in rows without and with a gap
+    between them: bytes of the conversion and values of the de-conversion are the oracle's either way."""
+    x = synth.activations(rows, K, config_id=2, tensor_id=91, dtype="bf16")
+    want = oracle.wide.quantize(x, WIDE[fmt][1])
+    ref = torch.from_numpy(oracle.wide.dequantize(want, WIDE[fmt][1]).astype(np.float32)).cuda()
+    gap = torch.zeros((rows, K + 32), dtype=torch.bfloat16, device="cuda")
+    gap[:, :K] = to_dev(x)
+    for src in (to_dev(x), gap[:, :K], to_dev(x).float()):
+        got = mxp.quantize(src, WIDE[fmt][0])
+        for g, w in list(zip(got, want))[: 3 if fmt.endswith("p") else 2]:
+            assert (g.cpu().numpy() == w).all()
+        for dt in (torch.float32, torch.bfloat16):
+            assert torch.equal(mxp.dequantize(got, WIDE[fmt][0], dt).float(), ref.to(dt).float())
+            out = torch.full((rows + 1, K + 32), 5.0, dtype=dt, device="cuda")
+            mxp.dequantize(got, WIDE[fmt][0], out=out[:rows, :K])
+            assert torch.equal(out[:rows, :K].float(), ref.to(dt).float())
+            assert (out[:rows, K:] == 5.0).all() and (out[rows] == 5.0).all()
+
+
 # ---- products of six- and eight-bit operands (Sec. 4.2 formats) -------------------------------------------------------
 # MXFP6(+): E2M3 images; the MXFP6+ BM enters as BM_H + BM_L over K segments, every product is exact in the MFMA, so the
 # bound of the main path applies.  MXFP8: E4M3 images, the FP8 dot product's bound (see check_gemm_e4m3 below).
