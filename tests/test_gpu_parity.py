@@ -491,6 +491,28 @@ def test_gemm_w4a16_few_rows(M, N, K, w_fmt):
 
 
 @pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp"])
+@pytest.mark.parametrize("M,N,K", [(33, 12256, 96), (40, 12257, 288), (64, 12300, 2080)])
+def test_gemm_w4a16_two_row_tiles_many_columns(M, N, K, w_fmt):
+    """Two row tiles on both sides of the change from eight to four wavefronts (384 column tiles); K that ends inside a
+    super-step and inside a wavefront's round, rows of activations that end inside the second tile."""
+    a = synth.activations(M, K, config_id=1, tensor_id=92)
+    qw = oracle.quantize(synth.weights(N, K, config_id=1, tensor_id=93, t3_frac=0.001), FMT[w_fmt][1])
+    ref, S = oracle.gemm_w4a16(a, qw, FMT[w_fmt][1])
+    check_gemm(mxp.gemm_w4a16(to_dev(a), q_dev(qw), FMT[w_fmt][0]), ref, S, "w4a16 %s %dx%dx%d" % (w_fmt, M, N, K))
+
+
+@pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p"])
+@pytest.mark.parametrize("M,N,K", [(1, 12830, 256), (8, 12800, 1280), (32, 6431, 2304), (5, 25601, 512), (40, 12830, 1280)])
+def test_gemm_decode_canonical_many_columns(M, N, K, w_fmt):
+    """Canonical weights with more column tiles than compute units: fewer chunks of K than wavefronts, one chunk for some
+    of them more than for the rest, a ragged last tile."""
+    a = synth.activations(M, K, config_id=1, tensor_id=94)
+    qw = oracle.quantize(synth.weights(N, K, config_id=1, tensor_id=95, t3_frac=0.001), FMT[w_fmt][1])
+    ref, S = oracle.gemm(oracle.quantize(a, oracle.MXFP4P), oracle.MXFP4P, qw, FMT[w_fmt][1])
+    check_gemm(mxp.gemm_decode_bf16a(to_dev(a), mxp.MXFP4P, q_dev(qw), FMT[w_fmt][0]), ref, S, "canonical %s %dx%dx%d" % (w_fmt, M, N, K))
+
+
+@pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp"])
 @pytest.mark.parametrize("M,N,K", [(65, 40, 64), (100, 200, 416), (257, 300, 1024), (300, 520, 2048), (512, 1100, 640),
                                    (129, 70, 4160)])
 def test_gemm_w4a16_many_rows(M, N, K, w_fmt):
