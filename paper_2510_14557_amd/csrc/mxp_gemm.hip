@@ -1552,11 +1552,12 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
 
   const int n_chunks = (k_tiles + CHUNK - 1) / CHUNK;
   const int first = (int)((blockIdx.x * 5u) % (uint32_t)n_chunks);
-  for (int ci = wave; ci < n_chunks; ci += WAVES) {
+  // one chunk of weights as it lies in memory; the next one's loads fly while this one is multiplied
+  u32x4 raw[CT][4];
+  u32x2 s8n[CT], i8n[CT];
+  auto load_weights = [&](int ci) {
     const int q = ci + first < n_chunks ? ci + first : ci + first - n_chunks;
     const int64_t kb0 = (int64_t)q * 8;                       // first block of the chunk
-    u32x4 raw[CT][4];
-    u32x2 s8[CT], i8[CT];
 #pragma unroll
     for (int j = 0; j < CT; ++j) {
       const int64_t row0 = 32 * (ct + j);
@@ -1567,13 +1568,20 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
         if (row < N && kb0 + ld_piece < nbk) raw[j][r] = __builtin_nontemporal_load(w_el + row * nbk + kb0 + ld_piece);
       }
       const int64_t orow = row0 + n_in;
-      s8[j] = (u32x2){0, 0};
-      i8[j] = (u32x2){0, 0};
+      s8n[j] = (u32x2){0, 0};
+      i8n[j] = (u32x2){0, 0};
       if (orow < N) {                                         // nbk % 8 == 0: the 8 bytes exist and are aligned
-        s8[j] = *reinterpret_cast<const u32x2*>(w_sc + orow * nbk + kb0);
-        if (PLUS) i8[j] = *reinterpret_cast<const u32x2*>(w_ix + orow * nbk + kb0);
+        s8n[j] = *reinterpret_cast<const u32x2*>(w_sc + orow * nbk + kb0);
+        if (PLUS) i8n[j] = *reinterpret_cast<const u32x2*>(w_ix + orow * nbk + kb0);
       }
     }
+  };
+  if (wave < n_chunks) load_weights(wave);
+  for (int ci = wave; ci < n_chunks; ci += WAVES) {
+    const int q = ci + first < n_chunks ? ci + first : ci + first - n_chunks;
+    u32x2 s8[CT], i8[CT];
+#pragma unroll
+    for (int j = 0; j < CT; ++j) { s8[j] = s8n[j]; i8[j] = i8n[j]; }
     v8i a[CHUNK][TMR];
     uint32_t sa[CHUNK];
 #pragma unroll
@@ -1598,6 +1606,7 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         *reinterpret_cast<u32x4*>(patch + (8 * r + ld_row) * kCanonPatchStride + ld_piece * 16) = raw[j][r];
+      if (j == CT - 1 && ci + WAVES < n_chunks) load_weights(ci + WAVES);
 #pragma unroll
       for (int c = 0; c < CHUNK; ++c) {
         const u32x4 nib = *reinterpret_cast<const u32x4*>(patch + n_in * kCanonPatchStride + (2 * c + h) * 16);
@@ -1699,9 +1708,11 @@ int launch_canon(const uint8_t* Ai, const uint8_t* we, const uint8_t* ws, const 
   const bool bf = d_dtype == MXP_BF16, wide = kt >= 64;
   constexpr int64_t kEnough = 200;
   if (M <= 32) {
-    if (ct / 4 >= kEnough) launch_canon_cfg<1, 4, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
-    else if (ct / 2 >= kEnough) launch_canon_cfg<1, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
-    else if (wide) launch_canon_cfg<1, 1, PLUS, 16>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
+    // One column tile per workgroup: 36 KiB of LDS, so that several workgroups share a compute unit and one's loads run under
+    // another's products.  (8 x 28672 x 8192: 43.8 us against 48.1 with two tiles and 48.4 with four; 1 x 14336 x 4096: 17.4
+    // against 18.5 / 27.3.)  Sixteen wavefronts where K has a chunk for each and the column tiles are fewer than the compute
+    // units (8 x 4096 x 4096: 11.4 against 11.8; 32 x 8192 x 28672, as many tiles as units: 50.1 against 49.3).
+    if (wide && ct < kEnough) launch_canon_cfg<1, 1, PLUS, 16>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
     else launch_canon_cfg<1, 1, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
   } else {
     if (ct / 2 >= kEnough) launch_canon_cfg<2, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
