@@ -40,13 +40,6 @@ __device__ __forceinline__ v8bf as_v8bf(const uint32_t (&d)[4]) {
 // (8 lanes per row: 128 contiguous bytes), passes them through a private LDS patch, and picks them up in operand order.
 constexpr int kW4RowStride = 144;                            // 8 blocks x 16 B + 16 B padding against bank conflicts
 constexpr int kW4PatchBytes = 32 * kW4RowStride + 256 + 256; // elements, scale bytes [32][8], index bytes [32][8]
-// More than 32 activation rows (two row tiles): a super-step's activations take the same way, 128 contiguous bytes per row,
-// 8 lanes each, through a second patch, one super-step ahead.  Read in operand order, a load of a wavefront is 64 pieces of
-// 16 bytes in 32 rows, and eight such loads per super-step were what these sizes waited for: 48 x 14336 x 4096 37.3 -> 29.6 us,
-// 64 x 4096 x 14336 66.8 -> 43.6, 40 x 28672 x 4096 64.2 -> 51.0.  One row tile of few rows is faster without (13 x
-// 14336 x 4096: 19.9 us against 21.9 - 25.6): most lanes of its operand-order loads are idle, and the patch is LDS for nothing.
-template <int TMR>
-constexpr int kW4WaveBytes = kW4PatchBytes + (TMR == 2 ? 32 * TMR * kW4RowStride : 0);
 
 // 32 codes -> 32 bf16 (16 dwords of pairs), Eq. 2.  The unpack-convert instruction runs over the whole block with the
 // NBM scale, the BM is overwritten once, and the reserved scale codes are a select (0: zeros, 255: NaN).  Only when some
@@ -102,11 +95,9 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint8_t* patch = lds_raw + wave * kW4WaveBytes<TMR>;      // private to this wavefront (LDS operations of a wavefront run in order)
+  uint8_t* patch = lds_raw + wave * kW4PatchBytes;          // private to this wavefront (LDS operations of a wavefront run in order)
   uint8_t* p_sc = patch + 32 * kW4RowStride;
   uint8_t* p_ix = p_sc + 256;
-  uint8_t* p_a = p_ix + 256;
-  constexpr bool STAGED = TMR == 2;
   const int h = lane >> 5, nl = lane & 31;
   const int64_t n0 = (int64_t)blockIdx.x * 32;
   const int64_t groups = (nbk + 7) / 8;
@@ -121,19 +112,6 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
     a_ok[i] = 32 * i + nl < M;
     a_row[i] = A + (a_ok[i] ? (int64_t)(32 * i + nl) * lda : 0) + h * 32;
   }
-
-  // STAGED: the activations of super-step t of group g, rows 8 i + lane / 8, 16-byte piece lane % 8
-  u32x4 a_next[STAGED ? 4 * TMR : 1];
-  auto load_a = [&](int64_t g, int t) {
-    const int64_t k = g * 256 + t * 64 + (lane & 7) * 8;
-    const bool k_ok = k < nbk * 32;
-#pragma unroll
-    for (int i = 0; i < 4 * TMR; ++i) {
-      const int64_t m = 8 * i + (lane >> 3);
-      a_next[i] = (u32x4){0, 0, 0, 0};
-      if (m < M && k_ok) a_next[i] = *reinterpret_cast<const u32x4*>(A + m * lda + k);
-    }
-  };
 
   // loads of one group in memory order: elements, 8 lanes per row; scale and index bytes, 2 lanes per row
   u32x4 q[4];
@@ -165,10 +143,7 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
       }
     }
   };
-  if (wave < groups) {
-    load_group(wave);
-    if constexpr (STAGED) load_a(wave, 0);
-  }
+  if (wave < groups) load_group(wave);
   for (int64_t g = wave; g < groups; g += WAVES) {
     const int64_t kb0 = 8 * g;
     // ---- through the patch into operand order
@@ -178,31 +153,19 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
     *reinterpret_cast<uint32_t*>(p_sc + (lane >> 1) * 8 + 4 * (lane & 1)) = sc4;
     if (MODE >= 1) *reinterpret_cast<uint32_t*>(p_ix + (lane >> 1) * 8 + 4 * (lane & 1)) = ix4;
     if (g + WAVES < groups) load_group(g + WAVES);          // the next group's loads fly while this one is multiplied
-#pragma unroll(STAGED ? 1 : 4)                               // unrolled, the staged form spills
+#pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int bl = 2 * t + h;                             // block of the group this lane de-converts
       // activations: lane (m, h) needs, for MFMA s, eight k of the same block (they stay in cache: A is small)
       u32x4 a[TMR][4];
-      if constexpr (STAGED) {
 #pragma unroll
-        for (int i = 0; i < 4 * TMR; ++i)
-          *reinterpret_cast<u32x4*>(p_a + (8 * i + (lane >> 3)) * kW4RowStride + (lane & 7) * 16) = a_next[i];
-        if (t < 3) load_a(g, t + 1);
-        else if (g + WAVES < groups) load_a(g + WAVES, 0);
+      for (int i = 0; i < TMR; ++i) {
+        const uint16_t* ap = a_row[i] + kb0 * 32 + t * 64;   // a_row already points at this lane's row and block half
+        const bool ok = a_ok[i] && kb0 + bl < nbk;
 #pragma unroll
-        for (int i = 0; i < TMR; ++i)
-#pragma unroll
-          for (int s = 0; s < 4; ++s) a[i][s] = *reinterpret_cast<const u32x4*>(p_a + (32 * i + nl) * kW4RowStride + h * 64 + 16 * s);
-      } else {
-#pragma unroll
-        for (int i = 0; i < TMR; ++i) {
-          const uint16_t* ap = a_row[i] + kb0 * 32 + t * 64;   // a_row already points at this lane's row and block half
-          const bool ok = a_ok[i] && kb0 + bl < nbk;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            a[i][s] = (u32x4){0, 0, 0, 0};
-            if (ok) a[i][s] = *reinterpret_cast<const u32x4*>(ap + 8 * s);
-          }
+        for (int s = 0; s < 4; ++s) {
+          a[i][s] = (u32x4){0, 0, 0, 0};
+          if (ok) a[i][s] = *reinterpret_cast<const u32x4*>(ap + 8 * s);
         }
       }
       const u32x4 qq = *reinterpret_cast<const u32x4*>(patch + nl * kW4RowStride + bl * 16);
@@ -243,10 +206,12 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
   }
 }
 
-template <int MODE, int TMR, bool OUT_BF16, int WAVES>
+template <int MODE, int TMR, bool OUT_BF16>
 void launch_skinny(dim3 grid, hipStream_t s, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi,
                    int64_t nbk, int64_t M, int64_t N, void* D, int64_t ldd) {
-  constexpr int lds_part = WAVES * TMR * 16 * 64 * 4, lds_patch = WAVES * kW4WaveBytes<TMR>;
+  // two row tiles need more than the 128 registers a lane gets with 16 wavefronts (the compiler spilled ~90): 8 then
+  constexpr int WAVES = TMR == 1 ? 16 : 8;
+  constexpr int lds_part = WAVES * TMR * 16 * 64 * 4, lds_patch = WAVES * kW4PatchBytes;
   constexpr int lds = lds_part > lds_patch ? lds_part : lds_patch;
   static_assert(lds <= 160 * 1024, "LDS");
   allow_dynamic_lds<&w4a16_skinny_kernel<MODE, TMR, OUT_BF16, WAVES>>((int)lds);
@@ -263,16 +228,11 @@ int dispatch_skinny(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
   const int64_t nbk = K / kBlock;
   const bool bf = d_dtype == MXP_BF16;
   if (M <= 32) {
-    if (bf) launch_skinny<MODE, 1, true, 16>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-    else launch_skinny<MODE, 1, false, 16>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-  } else if (ct >= kNumCU * 3 / 2) {
-    // four wavefronts per workgroup where those fill the chip (448 column tiles: 29.6 us against 31.8; 896: 51.0 against 56.0),
-    // eight where the column tiles are few (128: 43.6 against 60.9)
-    if (bf) launch_skinny<MODE, 2, true, 4>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-    else launch_skinny<MODE, 2, false, 4>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+    if (bf) launch_skinny<MODE, 1, true>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+    else launch_skinny<MODE, 1, false>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
   } else {
-    if (bf) launch_skinny<MODE, 2, true, 8>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-    else launch_skinny<MODE, 2, false, 8>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+    if (bf) launch_skinny<MODE, 2, true>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+    else launch_skinny<MODE, 2, false>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
   }
   return launch_status();
 }
