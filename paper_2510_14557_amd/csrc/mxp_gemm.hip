@@ -1710,9 +1710,10 @@ int launch_canon(const uint8_t* Ai, const uint8_t* we, const uint8_t* ws, const 
   if (M <= 32) {
     // One column tile per workgroup: 36 KiB of LDS, so that several workgroups share a compute unit and one's loads run under
     // another's products.  (8 x 28672 x 8192: 43.8 us against 48.1 with two tiles and 48.4 with four; 1 x 14336 x 4096: 17.4
-    // against 18.5 / 27.3.)  Sixteen wavefronts where K has a chunk for each and the column tiles are fewer than the compute
-    // units (8 x 4096 x 4096: 11.4 against 11.8; 32 x 8192 x 28672, as many tiles as units: 50.1 against 49.3).
-    if (wide && ct < kEnough) launch_canon_cfg<1, 1, PLUS, 16>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
+    // against 18.5 / 27.3.)  Long K with fewer tiles: sixteen wavefronts (9 x 8117 x 12800 21.9 against 22.8), then two
+    // tiles (16 x 13234 x 13056 28.9 against 30.7).
+    if (wide && ct / 2 < kEnough) launch_canon_cfg<1, 1, PLUS, 16>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
+    else if (wide && ct / 4 < kEnough) launch_canon_cfg<1, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
     else launch_canon_cfg<1, 1, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
   } else {
     if (ct / 2 >= kEnough) launch_canon_cfg<2, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
@@ -1982,6 +1983,15 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   if (workspace_bytes < mxp_gemm_workspace_bytes(M, N, K)) return MXP_ERR_WORKSPACE;
   uint8_t* wa = static_cast<uint8_t*>(workspace);
   uint8_t* wb = wa + align_up((size_t)image_geom(M, K).total());
+  if (M <= 64 && K % 256 == 0 && (fmtB == MXP_FMT_MXFP4P || fmtA != fmtB)) {
+    // few rows, weights in whole chunks of 8 blocks: the kernel that reads the canonical weights as they are -- no image of
+    // them to write and read back (8 x 4096 x 4096 17.2 -> 10.6 us, 13 x 8192 x 8192 33.5 -> 18.1, 64 x 1000 x 8192 20.4 ->
+    // 19.8, 16 x 256 x 256 7.8 -> 6.8).  Two plain MXFP4 operands keep their four-bit images on both sides.
+    rc = prepack_launch(A_elems, A_scales, A_idx, fmtA, M, K, wa, s);
+    if (rc != MXP_OK) return rc;
+    return fmtB == MXP_FMT_MXFP4P ? launch_canon<true>(wa, B_elems, B_scales, B_idx, M, N, K, D, d_dtype, ldd, s)
+                                  : launch_canon<false>(wa, B_elems, B_scales, B_idx, M, N, K, D, d_dtype, ldd, s);
+  }
   if (M <= 64 && fmtB == MXP_FMT_MXFP4P) {
     // few rows (the decode stage, Sec. 7.2): the product is bound by the weight bytes, so MXFP4+ weights go into the 4-bit
     // image with residual bytes (BM_H in place, BM_L by a second MFMA: Eq. 3, Sec. 5.2) instead of the wider E2M3 one --

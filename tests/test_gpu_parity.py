@@ -493,8 +493,8 @@ def test_gemm_w4a16_few_rows(M, N, K, w_fmt):
 @pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp"])
 @pytest.mark.parametrize("M,N,K", [(33, 12256, 96), (40, 12257, 288), (64, 12300, 2080)])
 def test_gemm_w4a16_two_row_tiles_many_columns(M, N, K, w_fmt):
-    """Two row tiles on both sides of the change from eight to four wavefronts (384 column tiles); K that ends inside a
-    super-step and inside a wavefront's round, rows of activations that end inside the second tile."""
+    """Two row tiles and more column tiles than compute units; K that ends inside a super-step and inside a wavefront's round,
+    rows of activations that end inside the second tile."""
     a = synth.activations(M, K, config_id=1, tensor_id=92)
     qw = oracle.quantize(synth.weights(N, K, config_id=1, tensor_id=93, t3_frac=0.001), FMT[w_fmt][1])
     ref, S = oracle.gemm_w4a16(a, qw, FMT[w_fmt][1])
@@ -510,6 +510,23 @@ def test_gemm_decode_canonical_many_columns(M, N, K, w_fmt):
     qw = oracle.quantize(synth.weights(N, K, config_id=1, tensor_id=95, t3_frac=0.001), FMT[w_fmt][1])
     ref, S = oracle.gemm(oracle.quantize(a, oracle.MXFP4P), oracle.MXFP4P, qw, FMT[w_fmt][1])
     check_gemm(mxp.gemm_decode_bf16a(to_dev(a), mxp.MXFP4P, q_dev(qw), FMT[w_fmt][0]), ref, S, "canonical %s %dx%dx%d" % (w_fmt, M, N, K))
+
+
+@pytest.mark.parametrize("fa,fb", [("mxfp4p", "mxfp4p"), ("mxfp4", "mxfp4p"), ("mxfp4p", "mxfp4")])
+@pytest.mark.parametrize("M,N,K", [(1, 33, 256), (32, 100, 512), (33, 70, 768), (64, 1001, 2304), (64, 65, 288), (65, 65, 256)])
+def test_gemm_few_rows_canonical_route(fa, fb, M, N, K):
+    """Few rows on either side of what the kernel on canonical weights takes (64 rows, K in whole chunks of 256); weights
+    with flushed and non-finite blocks among them."""
+    a = synth.activations(M, K, config_id=1, tensor_id=96)
+    w = synth.bf16_bits_to_f32(synth.weights(N, K, config_id=1, tensor_id=97, t3_frac=0.001)).astype(np.float32)
+    w[0, :32] = 0.0
+    w[3, 32:64] = np.nan
+    qa, qb = oracle.quantize(a, FMT[fa][1]), oracle.quantize(w, FMT[fb][1])
+    ref, S = oracle.gemm(qa, FMT[fa][1], qb, FMT[fb][1])
+    D = mxp.gemm(q_dev(qa), FMT[fa][0], q_dev(qb), FMT[fb][0])
+    rest = np.arange(N) != 3
+    assert torch.isnan(D[:, 3]).all() and np.isnan(ref[:, 3]).all()
+    check_gemm(D[:, torch.from_numpy(rest).cuda()], ref[:, rest], S[:, rest], "few rows %s x %s %dx%dx%d" % (fa, fb, M, N, K))
 
 
 @pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp"])
