@@ -108,7 +108,11 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(uint32_t bits) {
   return (bits + 0x7FFFu + ((bits >> 16) & 1u)) >> 16;
 }
 
-constexpr int kDequantUnroll = 4;                    // groups per lane and pass of the de-conversion
+// Groups per lane and pass of the de-conversion: four for bf16 results from 4096 x 4096 values on, one below and for fp32
+// results (us, one | four: MXFP6+ to bf16 64 x 4096 2.9 | 3.4, 2048 x 4096 6.4 | 6.3, 4096 x 4096 10.4 | 9.1, 14336 x 8192
+// 80.9 | 57.3; to fp32 64 x 4096 3.1 | 3.8, 14336 x 8192 137 | 140, MXFP8 14336 x 8192 101 | 143).
+constexpr int kDequantUnroll = 4;
+constexpr int64_t kDeepGroups = (int64_t)1 << 21;
 
 // ---- quantize -------------------------------------------------------------------------------------------------
 // nq = number of 8-element groups (4 per block); a quad of lanes is one block, so a quad is inside or outside as a whole.
@@ -382,53 +386,71 @@ __device__ __forceinline__ void decode_any(uint32_t lo, uint32_t hi, uint32_t sb
   }
 }
 
+// This lane's share of block g's code string: two dwords, of which MXFP6 uses 48 bits (from bit 16 on in odd lanes).
+template <int BITS>
+__device__ __forceinline__ u32x2 load_share(const uint8_t* __restrict__ elems, int64_t g, uint32_t part) {
+  if constexpr (BITS == 8) return *reinterpret_cast<const u32x2*>(elems + g * 32 + part * 8);
+  const uint32_t* in = reinterpret_cast<const uint32_t*>(elems + g * 24) + (part >> 1) * 3u + (part & 1u);   // dwords 0,1 / 1,2 / 3,4 / 4,5
+  return u32x2{in[0], in[1]};
+}
+template <int BITS>
+__device__ __forceinline__ void align_share(u32x2 w, uint32_t part, uint32_t& lo, uint32_t& hi) {
+  lo = w.x;
+  hi = w.y;
+  if (BITS == 6) {
+    const uint64_t both = (((uint64_t)w.y << 32) | w.x) >> (16u * (part & 1u));
+    lo = (uint32_t)both;
+    hi = (uint32_t)(both >> 32) & 0xFFFFu;
+  }
+}
+
+template <bool OUT_BF16>
+__device__ __forceinline__ void store_values(void* __restrict__ dst, int64_t off, const uint32_t (&f)[8], const uint32_t (&hb)[4]) {
+  if (OUT_BF16) {
+    *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst) + off) = u32x4{hb[0], hb[1], hb[2], hb[3]};
+  } else {
+    u32x4* o = reinterpret_cast<u32x4*>(static_cast<float*>(dst) + off);
+    o[0] = u32x4{f[0], f[1], f[2], f[3]};
+    o[1] = u32x4{f[4], f[5], f[6], f[7]};
+  }
+}
+
 // A quad of lanes is a block, a lane gives eight of its values (one or two 16-byte stores).  Bound by the vector ALU
 // rather than by memory unless the instructions per lane are few: no 64-bit division where rows follow each other without
-// a gap (DENSE), the BM's bits put together from fields, general blocks out of line.  A lane takes U groups 256 apart, all
-// loads of them ahead of the first use, so that scale, index and code bytes are one round trip and not three.
-template <int BITS, bool PLUS, bool OUT_BF16, bool DENSE>
+// a gap (DENSE), the BM's bits put together from fields, and each lane converts its own share alone, which it finds in the
+// first registers of the conversion's result.  A lane takes U groups 256 apart, all loads of them ahead of the first use.
+// General blocks are decoded in a loop of their own behind the common ones: their code is long, and a small tensor is
+// bound by fetching the code it runs through.  (us, whole block converted by each lane and general blocks inline -> this:
+// MXFP6 to bf16 16 x 4096 5.4 -> 2.9, 4096 x 14336 55.5 -> 25.5; to fp32 10.7 -> 2.9, 112 -> 55.6.)
+template <int BITS, bool PLUS, bool OUT_BF16, bool DENSE, int U>
 __global__ void __launch_bounds__(256) dequantize_wide_kernel(const uint8_t* __restrict__ elems, const uint8_t* __restrict__ scales,
                                                               const uint8_t* __restrict__ bm_idx, int64_t nbk, int64_t ld,
                                                               int64_t nq, void* __restrict__ dst) {
   using F = Elem<BITS>;
-  constexpr int U = kDequantUnroll, NR = BITS == 8 ? 2 : 6;
   const uint32_t tid = threadIdx.x, part = tid & 3u;
   const int64_t ng = nq >> 2;
+  auto offset = [&](int64_t g) {
+    if (DENSE) return g * 32 + part * 8;
+    const int64_t row = g / nbk;
+    return row * ld + (g - row * nbk) * 32 + part * 8;
+  };
   for (int64_t q0 = (int64_t)blockIdx.x * (256 * U); q0 < nq; q0 += (int64_t)gridDim.x * (256 * U)) {
-    uint32_t sbs[U], bms[U], raw[U][NR];
-    int64_t gs[U];
+    const int64_t g0 = (q0 >> 2) + (tid >> 2);       // this quad's first block; the others follow 64 apart
+    uint32_t sbs[U], bms[U], general = 0;
+    u32x2 raw[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      int64_t g = (q0 >> 2) + 64 * u + (tid >> 2);
-      g = g < ng ? g : ng - 1;                       // past the end: the last block again, not stored
-      gs[u] = g;
+      const int64_t g = g0 + 64 * u < ng ? g0 + 64 * u : ng - 1;       // past the end: the last block again, not stored
       sbs[u] = scales[g];
       bms[u] = PLUS ? (uint32_t)bm_idx[g] : 0u;
-      if constexpr (BITS == 8) {
-        const u32x2 v = *reinterpret_cast<const u32x2*>(elems + g * 32 + part * 8);
-        raw[u][0] = v.x; raw[u][1] = v.y;
-      } else {
-        const u32x2* in = reinterpret_cast<const u32x2*>(elems + g * 24);
-        const u32x2 d0 = in[0], d1 = in[1], d2 = in[2];
-        raw[u][0] = d0.x; raw[u][1] = d0.y; raw[u][2] = d1.x; raw[u][3] = d1.y; raw[u][4] = d2.x; raw[u][5] = d2.y;
-      }
+      raw[u] = load_share<BITS>(elems, g, part);
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const uint32_t sb = sbs[u];
       const uint32_t bm = PLUS ? (bms[u] & 31u) - part * 8u : 64u;     // the BM's place among this lane's eight; above 7: not here
-      // this lane's own code bits: 48 (lo, hi[15:0]) or 64
       uint32_t lo, hi;
-      if constexpr (BITS == 8) {
-        lo = raw[u][0];
-        hi = raw[u][1];
-      } else {
-        const uint32_t w0 = part == 0u ? raw[u][0] : (part == 1u ? raw[u][1] : (part == 2u ? raw[u][3] : raw[u][4]));
-        const uint32_t w1 = part == 0u ? raw[u][1] : (part == 1u ? raw[u][2] : (part == 2u ? raw[u][4] : raw[u][5]));
-        const uint64_t both = (((uint64_t)w1 << 32) | w0) >> (16u * (part & 1u));
-        lo = (uint32_t)both;
-        hi = (uint32_t)(both >> 32) & 0xFFFFu;
-      }
+      align_share<BITS>(raw[u], part, lo, hi);
       // Common case (no result below the normal range, no overflow, no E4M3 NaN code among the ordinary elements): the CDNA4
       // unpack-convert instructions, value * X exact in both output types; the lane that holds the BM then writes it over
       // its element.
@@ -438,8 +460,10 @@ __global__ void __launch_bounds__(256) dequantize_wide_kernel(const uint8_t* __r
         if (PLUS && bm < 8u) nanlike &= ~((uint64_t)0x80u << (8u * bm));          // the BM's byte is all mantissa
         plain = plain && nanlike == 0u;
       }
-      uint32_t f[8], hb[4];
-      if (plain) {
+      if (!plain) {
+        general |= 1u << u;
+      } else if (g0 + 64 * u < ng) {
+        uint32_t f[8], hb[4];
         const float X = __uint_as_float(sb << 23);
         const uint32_t code = (uint32_t)((((uint64_t)hi << 32) | lo) >> (((uint32_t)BITS * bm) & 63u)) & ((1u << BITS) - 1u);
         // 2^e_max * 1.m * X: sign | exponent field sb + e_max | BITS - 1 mantissa bits, left-aligned
@@ -453,12 +477,10 @@ __global__ void __launch_bounds__(256) dequantize_wide_kernel(const uint8_t* __r
             c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(hi, X, true);
             hb[0] = c0.u; hb[1] = c1.u; hb[2] = c2.u; hb[3] = c3.u;
           } else {
-            const v6u str = {raw[u][0], raw[u][1], raw[u][2], raw[u][3], raw[u][4], raw[u][5]};
             union { v32bf v; uint32_t u[16]; } c;
-            c.v = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6(str, X);
+            c.v = __builtin_amdgcn_cvt_scalef32_pk32_bf16_fp6((v6u){lo, hi, 0u, 0u, 0u, 0u}, X);
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              hb[j] = part == 0u ? c.u[j] : (part == 1u ? c.u[4 + j] : (part == 2u ? c.u[8 + j] : c.u[12 + j]));
+            for (int j = 0; j < 4; ++j) hb[j] = c.u[j];
           }
           if (PLUS) {
             const uint32_t mask = (bm & 1u) ? 0xFFFF0000u : 0xFFFFu, put = bmh | (bmh << 16);
@@ -475,42 +497,35 @@ __global__ void __launch_bounds__(256) dequantize_wide_kernel(const uint8_t* __r
             f[0] = __float_as_uint(f0[0]); f[1] = __float_as_uint(f0[1]); f[2] = __float_as_uint(f1[0]); f[3] = __float_as_uint(f1[1]);
             f[4] = __float_as_uint(f2[0]); f[5] = __float_as_uint(f2[1]); f[6] = __float_as_uint(f3[0]); f[7] = __float_as_uint(f3[1]);
           } else {
-            const v6u str = {raw[u][0], raw[u][1], raw[u][2], raw[u][3], raw[u][4], raw[u][5]};
             union { v32f v; uint32_t u[32]; } c;
-            c.v = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(str, X);
+            c.v = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6((v6u){lo, hi, 0u, 0u, 0u, 0u}, X);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-              f[i] = part == 0u ? c.u[i] : (part == 1u ? c.u[8 + i] : (part == 2u ? c.u[16 + i] : c.u[24 + i]));
+            for (int i = 0; i < 8; ++i) f[i] = c.u[i];
           }
           if (PLUS) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) f[i] = bm == (uint32_t)i ? bmh << 16 : f[i];
           }
         }
-      } else {
-        decode_any<BITS>(lo, hi, sb, bm, f);
-        if (OUT_BF16) {
-          uint32_t h[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) h[i] = sb == 255u ? 0x7FC0u : f32_to_bf16_rne(f[i]);
-#pragma unroll
-          for (int j = 0; j < 4; ++j) hb[j] = h[2 * j] | (h[2 * j + 1] << 16);
-        }
+        store_values<OUT_BF16>(dst, offset(g0 + 64 * u), f, hb);
       }
-      if (q0 + 256 * u + tid < nq) {
-        int64_t off = q0 * 8 + (256 * u + tid) * 8u;
-        if (!DENSE) {
-          const int64_t row = gs[u] / nbk;
-          off = row * ld + (gs[u] - row * nbk) * 32 + part * 8;
-        }
-        if (OUT_BF16) {
-          *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(dst) + off) = u32x4{hb[0], hb[1], hb[2], hb[3]};
-        } else {
-          u32x4* o = reinterpret_cast<u32x4*>(static_cast<float*>(dst) + off);
-          o[0] = u32x4{f[0], f[1], f[2], f[3]};
-          o[1] = u32x4{f[4], f[5], f[6], f[7]};
-        }
+    }
+#pragma unroll 1
+    for (int u = 0; general >> u != 0u; ++u) {
+      const int64_t g = g0 + 64 * u;
+      if (!((general >> u) & 1u) || g >= ng) continue;
+      const uint32_t sb = scales[g], bm = PLUS ? ((uint32_t)bm_idx[g] & 31u) - part * 8u : 64u;
+      uint32_t lo, hi, f[8], hb[4];
+      align_share<BITS>(load_share<BITS>(elems, g, part), part, lo, hi);
+      decode_any<BITS>(lo, hi, sb, bm, f);
+      if (OUT_BF16) {
+        uint32_t h[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) h[i] = sb == 255u ? 0x7FC0u : f32_to_bf16_rne(f[i]);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) hb[j] = h[2 * j] | (h[2 * j + 1] << 16);
       }
+      store_values<OUT_BF16>(dst, offset(g), f, hb);
     }
   }
 }
@@ -798,14 +813,16 @@ int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K
 int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows,
                            int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t s) {
   const int64_t nbk = K / kBlock, nq = rows * nbk * 4;
-  const int64_t want = (nq + 256 * kDequantUnroll - 1) / (256 * kDequantUnroll), cap = (int64_t)1 << 24;
+  const bool bf = dst_dtype == MXP_BF16, dense = rows == 1 || ld_dst == K, deep = bf && nq >= kDeepGroups;
+  const int64_t per = 256 * (deep ? kDequantUnroll : 1), want = (nq + per - 1) / per, cap = (int64_t)1 << 24;
   const dim3 grid((unsigned)(want < cap ? want : cap));
-  const bool bf = dst_dtype == MXP_BF16, dense = rows == 1 || ld_dst == K;
-#define MXP_LAUNCH_DWD(BT, P, O, DN) hipLaunchKernelGGL((dequantize_wide_kernel<BT, P, O, DN>), grid, dim3(256), 0, s, elems, scales, bm_idx, nbk, ld_dst, nq, dst)
-#define MXP_LAUNCH_DW(BT, P, O)                      \
-  do {                                               \
-    if (dense) MXP_LAUNCH_DWD(BT, P, O, true);       \
-    else MXP_LAUNCH_DWD(BT, P, O, false);            \
+#define MXP_LAUNCH_DWD(BT, P, O, DN, U) hipLaunchKernelGGL((dequantize_wide_kernel<BT, P, O, DN, U>), grid, dim3(256), 0, s, elems, scales, bm_idx, nbk, ld_dst, nq, dst)
+#define MXP_LAUNCH_DW(BT, P, O)                                                  \
+  do {                                                                           \
+    if (deep && dense) MXP_LAUNCH_DWD(BT, P, O, true, (O) ? kDequantUnroll : 1); \
+    else if (deep) MXP_LAUNCH_DWD(BT, P, O, false, (O) ? kDequantUnroll : 1);    \
+    else if (dense) MXP_LAUNCH_DWD(BT, P, O, true, 1);                           \
+    else MXP_LAUNCH_DWD(BT, P, O, false, 1);                                     \
   } while (0)
   switch (fmt) {
     case MXP_FMT_MXFP6: if (bf) MXP_LAUNCH_DW(6, false, true); else MXP_LAUNCH_DW(6, false, false); break;

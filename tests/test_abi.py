@@ -252,3 +252,21 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
         mxp.version()
     with pytest.raises(mxp.MxpError):
         mxp.image_bytes(64, 64)
+
+
+def kernel_metadata(path):
+    """The kernels' metadata maps (ELF notes "AMDGPU", type 32) of every code object inside a built library."""
+    msgpack = pytest.importorskip("msgpack")
+    data, at = open(path, "rb").read(), 0
+    tag = (32).to_bytes(4, "little") + b"AMDGPU\0\0"
+    while (at := data.find(tag, at)) >= 0:
+        size = int.from_bytes(data[at - 4:at], "little")
+        at += len(tag)
+        yield from msgpack.unpackb(data[at:at + size])["amdhsa.kernels"]
+
+
+def test_conversion_kernels_keep_their_values_in_registers():
+    """A conversion kernel that indexes its registers at run time goes through scratch memory instead."""
+    found = {k[".name"]: k[".private_segment_fixed_size"] for k in kernel_metadata(mxp.LIB_PATH) if "quantize" in k[".name"]}
+    assert sum("dequantize_wide_kernel" in n for n in found) >= 16
+    assert not {n: b for n, b in found.items() if b}

@@ -888,6 +888,30 @@ def test_wide_pass_edges_dense_and_strided(fmt, rows, K):
             assert (out[:rows, K:] == 5.0).all() and (out[rows] == 5.0).all()
 
 
+@pytest.mark.parametrize("fmt", list(WIDE))
+@pytest.mark.parametrize("rows,K", [(524287, 32), (524288, 32), (524289, 32), (5001, 4128)])
+def test_wide_dequantize_large_equals_pieces(fmt, rows, K):
+    """bf16 results of 2^24 values and more take several groups per lane; pieces of the same rows do not (the form that is
+    compared with the oracle).  Any codes, any scale and index bytes, rows without and with a gap between them."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(rows + K)
+    junk = lambda n: torch.randint(0, 256, (rows, n), generator=gen, device="cuda", dtype=torch.uint8)
+    code = WIDE[fmt][0]
+    q = (junk(K * (6 if "6" in fmt else 8) // 8), junk(K // 32), junk(K // 32))
+    usual = torch.rand((rows, K // 32), generator=gen, device="cuda") < 0.9
+    q[1][usual] = 120
+    out = torch.full((rows + 1, K + 32), 5.0, dtype=torch.bfloat16, device="cuda")
+    dense = mxp.dequantize(q, code, torch.bfloat16)
+    mxp.dequantize(q, code, out=out[:rows, :K])
+    bits = lambda t: t.contiguous().view(torch.int16)
+    assert (out[:rows, K:] == 5.0).all() and (out[rows] == 5.0).all()
+    assert torch.equal(bits(out[:rows, :K]), bits(dense))
+    step = (1 << 21) // K // 16 * 16                            # an eighth of that size, pieces starting at 16-byte addresses
+    for r in range(0, rows, step):
+        piece = mxp.dequantize(tuple(t[r:r + step] for t in q), code, torch.bfloat16)
+        assert torch.equal(bits(dense[r:r + step]), bits(piece)), (fmt, rows, K, r)
+
+
 # ---- products of six- and eight-bit operands (Sec. 4.2 formats) -------------------------------------------------------
 # MXFP6(+): E2M3 images; the MXFP6+ BM enters as BM_H + BM_L over K segments, every product is exact in the MFMA, so the
 # bound of the main path applies.  MXFP8: E4M3 images, the FP8 dot product's bound (see check_gemm_e4m3 below).
