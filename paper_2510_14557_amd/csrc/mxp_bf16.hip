@@ -269,7 +269,14 @@ __device__ __forceinline__ void run_bf16_tile(uint8_t* lds, const uint16_t* __re
 #undef MXP_READ_B
 #undef MXP_COPY
   wait_copies_and_barrier<0>();                              // the slots are idle: their place holds the epilogue's patches
-  store_tile_lds<WM, WN, OUT_BF16>(acc, m0 / 32 + wm * WM, n0 / 32 + wn * WN, lane, M, N, Dv, ldd, lds + wave * (2 * kPatchBytes));
+  uint8_t* patch = lds + wave * (2 * kPatchBytes);
+  const int64_t tm = m0 / 32 + wm * WM, tn = n0 / 32 + wn * WN;
+  // Streaming stores where a store instruction's runs of 128 bytes start on whole lines (fp32) or halves of them (bf16); elsewhere
+  // the cache has to put the lines together (streaming | ordinary, us: 4096 x 14336 x 256 to bf16 61 | 69, 4096 x 14352 x 256 91 | 74,
+  // 2772 x 15036 x 256 to fp32 126 | 59; 4096 x 14352 x 256 to fp32, half lines, 82 | 74).
+  if ((((uint64_t)(uintptr_t)Dv | (uint64_t)ldd * (OUT_BF16 ? 2 : 4)) & (OUT_BF16 ? 63u : 127u)) == 0)
+    store_tile_lds<WM, WN, OUT_BF16, true>(acc, tm, tn, lane, M, N, Dv, ldd, patch);
+  else store_tile_lds<WM, WN, OUT_BF16, false>(acc, tm, tn, lane, M, N, Dv, ldd, patch);
 }
 
 // Tile lists.  Full tiles (256 x 256) are in band order; the last `2 * halved` workgroups compute the halves (256 x 128) of

@@ -23,15 +23,19 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float v) { return pack_bf16x
 // Each 32 x 32 tile is therefore passed through a private 32 x 36-float LDS patch (rows padded by 16 bytes against bank
 // conflicts; LDS operations of one wavefront execute in order, so no wait is needed between the write and the read)
 // and comes back with 8 consecutive lanes holding the 128 contiguous bytes of one row: every store instruction
-// writes 8 full lines.  `patch` is this wavefront's scratch, two patches of kPatchBytes.
+// writes 8 full lines.  `patch` is this wavefront's scratch, two patches of kPatchBytes.  STREAM: streaming stores.
 constexpr int kPatchStride = 144;                 // bytes per patch row: 32 floats + 16
 constexpr int kPatchBytes = 32 * kPatchStride;
 
-template <int TWM, int TWN, bool OUT_BF16>
+template <int TWM, int TWN, bool OUT_BF16, bool STREAM = true>
 __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int64_t tile_m, int64_t tile_n, int lane, int64_t M,
                                                int64_t N, void* __restrict__ Dv, int64_t ldd, uint8_t* patch) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   const bool vec_ok = (ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(Dv) & 15u) == 0);
+  auto put = [](auto* at, auto v) {
+    if constexpr (STREAM) __builtin_nontemporal_store(v, at);
+    else *at = v;
+  };
   const int wr = (lane & 31) * kPatchStride + 16 * (lane >> 5);   // + 32 g
   const int rd = (lane >> 3) * kPatchStride + (lane & 7) * 16;    // + 8 k rows
   if (OUT_BF16 && vec_ok && TWN % 2 == 0) {
@@ -58,7 +62,7 @@ __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int6
           if (row >= M || col >= N) continue;
           if (col + 3 < N) {
             u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
+            put(reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col), o);
           } else {
 #pragma unroll
             for (int q = 0; q < 4; ++q)
@@ -88,9 +92,9 @@ __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int6
         if (vec_ok && col + 3 < N) {
           if (OUT_BF16) {
             u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
+            put(reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col), o);
           } else {
-            __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(static_cast<float*>(Dv) + row * ldd + col));
+            put(reinterpret_cast<f32x4*>(static_cast<float*>(Dv) + row * ldd + col), v);
           }
         } else {
 #pragma unroll

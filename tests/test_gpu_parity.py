@@ -2178,3 +2178,31 @@ def test_gemm_w4a16_weights_deconverted_once(fmt, M, N, K):
             outs.append(d[:, :N])
         assert bool(outs[0].isfinite().all())
         assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2]), (fmt, M, N, K, dt)
+
+
+@pytest.mark.parametrize("M,N", [(130, 300), (257, 129), (1100, 4500)])
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_bf16_product_output_rows_at_any_alignment(M, N, dt):
+    """Rows of D on whole lines, on halves and quarters of them, at any element, and D itself behind a line's start: the same
+    values, nothing written beside them (128 x 128 blocks, half and full tiles)."""
+    K = 1280
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(N)
+    a = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    qw = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16), mxp.MXFP8P)
+    L, ref = mxp.lib(), None
+    need = L.mxp_gemm_w4a16_workspace_bytes(M, N, K, mxp.MXFP8P)
+    assert need >= 2 * N * K
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    wide = (N + 63) // 64 * 64
+    for ldd, start in ((wide, 0), (wide + 32, 0), (wide + 16, 0), (wide + 8, 0), (wide + 4, 0), (wide + 1, 0), (wide, 16), (wide, 4), (wide, 1)):
+        d = torch.full((M * ldd + 64,), float("nan"), dtype=dt, device="cuda")
+        rc = L.mxp_gemm_w4a16_ws(M, N, K, a.data_ptr(), mxp.BF16, K, qw[0].data_ptr(), qw[1].data_ptr(), qw[2].data_ptr(), mxp.MXFP8P,
+                                 d[start:].data_ptr(), mxp._dt(d), ldd, ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        rows = d[start:start + M * ldd].view(M, ldd)
+        out = rows[:, :N].clone()
+        ref = out if ref is None else ref
+        assert torch.equal(out, ref), (ldd, start)
+        rows[:, :N] = float("nan")
+        assert bool(d.isnan().all()), (ldd, start)
