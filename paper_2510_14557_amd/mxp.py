@@ -464,9 +464,16 @@ def _optional_workspace(nbytes: int, device):
         return None
 
 
-def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None):
-    """Un-quantized bf16 activations x canonical weights of any block format, de-converted inside the kernel (4-bit weights:
-    few-row kernel for M <= 64; otherwise 256 x 256 tiles on the bf16 MFMA)."""
+def gemm_w4a16_workspace_bytes(M: int, N: int, K: int, fmt_w: int) -> int:
+    return int(lib().mxp_gemm_w4a16_workspace_bytes(M, N, K, fmt_w))
+
+
+def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None,
+               workspace: torch.Tensor | None = None):
+    """Un-quantized bf16 activations x canonical weights of any block format (4-bit weights: few-row kernel for M <= 128;
+    otherwise tiles on the bf16 MFMA, the weights de-converted inside the kernel or, with room for them as bf16, once ahead of
+    it).  workspace: that room (gemm_w4a16_workspace_bytes, at most 256 MiB), kept by the caller; an empty tensor for none.
+    Left out, it is allocated per call where it pays and memory is there."""
     _dev2d(a)
     we, ws, wi = qw
     M, K = a.shape
@@ -477,10 +484,10 @@ def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype 
         out = torch.empty((M, N), dtype=out_dtype, device=a.device)
     lda = a.stride(0) if M > 1 else max(K, 1)
     ldd = out.stride(0) if M > 1 else max(N, 1)
-    nbytes = int(lib().mxp_gemm_w4a16_workspace_bytes(M, N, K, fmt_w))
-    workspace = _optional_workspace(nbytes, a.device)
+    if workspace is None:
+        workspace = _optional_workspace(gemm_w4a16_workspace_bytes(M, N, K, fmt_w), a.device)
     _check(lib().mxp_gemm_w4a16_ws(M, N, K, _p(a), _dt(a), lda, _p(we), _p(ws), _p(wi), fmt_w, _p(out), _dt(out), ldd, _p(workspace),
-                                   nbytes if workspace is not None else 0, _stream()), "mxp_gemm_w4a16")
+                                   workspace.numel() if workspace is not None else 0, _stream()), "mxp_gemm_w4a16")
     return out
 
 

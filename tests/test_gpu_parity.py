@@ -2206,3 +2206,21 @@ def test_bf16_product_output_rows_at_any_alignment(M, N, dt):
         assert torch.equal(out, ref), (ldd, start)
         rows[:, :N] = float("nan")
         assert bool(d.isnan().all()), (ldd, start)
+
+
+def test_gemm_w4a16_workspace_is_the_callers_choice():
+    """An empty workspace, or one that the caller keeps: no device memory is taken by the call; left out, at most 256 MiB are."""
+    M, N, K = 200, 4096, 4096
+    a = torch.randn((M, K), device="cuda").to(torch.bfloat16)
+    qw = mxp.quantize(torch.randn((N, K), device="cuda").to(torch.bfloat16), mxp.MXFP4P)
+    need = mxp.gemm_w4a16_workspace_bytes(M, N, K, mxp.MXFP4P)
+    assert 0 < need <= 256 << 20
+    outs = []
+    for ws, most in ((torch.empty(0, dtype=torch.uint8, device="cuda"), 0), (torch.empty(need, dtype=torch.uint8, device="cuda"), 0), (None, need)):
+        out = torch.empty((M, N), device="cuda")
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        mxp.gemm_w4a16(a, qw, out=out, workspace=ws)
+        assert torch.cuda.max_memory_allocated() - before <= most
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
