@@ -322,14 +322,16 @@ int mxp_gemm_decode_bf16a(int64_t M, int64_t N, int64_t K, const void* A, int a_
  * M <= 64 (up to 128 in two passes): a kernel bound by reading the 4-bit weights once.  Larger M (prefill with
  * weight-only quantization): 256 x 256 output tiles, the weights de-converted once per tile and 64-element step of K
  * on their way into LDS.  The tiled kernel also takes MXFP6(+) and MXFP8(+) weights (any M).  D is MXP_F32 or MXP_BF16
- * with row stride ldd.  No workspace. */
+ * with row stride ldd.  No workspace; mxp_gemm_w4a16_ws is faster where it has a use for one. */
 int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
                    const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW,
                    void* D, int d_dtype, int64_t ldd, void* stream);
-/* The same with room for W as bf16: many activation rows then de-convert W once, ahead of the product (in slabs of as
- * many rows of W as fit; the same products in the same order), instead of once per row of output tiles inside it.
- * mxp_gemm_w4a16_workspace_bytes: the room worth giving, at most 256 MiB (or 256 rows of W); 0 where it would not be used.
- * workspace may be NULL or smaller: the call then runs as mxp_gemm_w4a16 does. */
+/* The same with room for W as bf16: W is then de-converted once, ahead of a plain bf16 product (in even slabs of as many
+ * rows of W as fit; the same products in the same order), where that is estimated to be faster than de-conversion inside
+ * the product: 4-bit W above 128 rows of A, wider W at any number of rows, K >= 256, lda < 2^23.
+ * mxp_gemm_w4a16_workspace_bytes: the room worth giving, at most 256 MiB; 0 where it would not be used (for rows of A and D
+ * without gaps).  workspace may be NULL or smaller: the call then uses smaller slabs or runs as mxp_gemm_w4a16 does; larger
+ * room is used too. */
 size_t mxp_gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K, int fmtW);
 int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
                       const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW,

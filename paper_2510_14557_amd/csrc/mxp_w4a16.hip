@@ -9,6 +9,7 @@
 // weight element.
 #include "mxp_common.h"
 #include "mxp_decode.h"
+#include <cmath>
 
 namespace {
 
@@ -545,13 +546,14 @@ inline int kind_of(int fmt) {
 inline int64_t block_bytes(int fmt) { return fmt < MXP_FMT_MXFP6 ? 16 : fmt < MXP_FMT_MXFP8 ? 24 : 32; }   // codes of one block
 inline int plus_of(int fmt) { return fmt == MXP_FMT_MXFP6P || fmt == MXP_FMT_MXFP8P; }
 
+// fewer than ~200 tiles of 256 rows: tiles of 128 rows, twice as many workgroups (four-bit weights only)
+inline bool tiles_of_128_rows(int64_t M, int64_t N) { return ((M + 255) / 256) * ((N + 255) / 256) < 200 && M > 128; }
+
 // un-quantized bf16 activations x weights of any block format
 int dispatch_tiled(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws,
                    const uint8_t* wi, int fmtW, void* D, int d_dtype, int64_t ldd, hipStream_t s) {
   const QOperand none = {nullptr, nullptr, nullptr, 0}, qw = {we, ws, wi, plus_of(fmtW)};
-  // fewer than ~200 tiles of 256 rows: tiles of 128 rows, twice as many workgroups (four-bit weights only)
-  const bool small = ((M + 255) / 256) * ((N + 255) / 256) < 200 && M > 128;
-  if (small && kind_of(fmtW) <= 3) {
+  if (tiles_of_128_rows(M, N) && kind_of(fmtW) <= 3) {
     switch (kind_of(fmtW)) {
       case 1: return launch_deconv<kRawBf16, 1, 2>(M, N, K, A, lda, none, qw, D, d_dtype, ldd, s);
       case 2: return launch_deconv<kRawBf16, 2, 2>(M, N, K, A, lda, none, qw, D, d_dtype, ldd, s);
@@ -601,28 +603,57 @@ int deconv_gemm_launch(int64_t M, int64_t N, int64_t K, const uint8_t* ae, const
 }  // namespace mxp
 
 namespace {
-// Rows of W that are de-converted at a time: at most this many bytes of bf16 (the size of the last-level cache, which the
-// product then reads them from), in whole tiles.
-constexpr int64_t kSlabBytes = (int64_t)256 << 20;
-int64_t slab_rows(int64_t N, int64_t K, int64_t bytes) {
-  const int64_t r = bytes / (2 * K);
-  return r >= N ? N : r / 256 * 256;
-}
-// Where W is de-converted once, as bf16, ahead of a plain bf16 product (de-converted per row of tiles -> once, us, bf16 out):
+// W de-converted once, as bf16, ahead of a plain bf16 product -- or in the product kernel, again for each row of its tiles.
+// Which is faster follows from what either makes of a shape: rounds of tiles over the chip that each walk along K, against
+// a pass over W and fewer, faster rounds.  Both are estimated (us) with the rates that the two routes measured over 3700
+// shapes (1 - 4096 rows, N 200 - 60000, K 256 - 30000, all formats; the estimates are off by 9 and 11 %), and W is de-converted
+// once where that is ahead by a margin.  In the kernel -> once, us, bf16 out:
 //   MXFP4+, 14336 x 4096: 160 rows 88.6 -> 60.5, 1024 131 -> 115, 4096 501 -> 363; 4096 x 14336: 160 rows 296 -> 110, 2048 331 -> 205
 //   MXFP8+, 14336 x 4096:  16 rows 162 -> 58.6, 1024 170 -> 119, 4096 668 -> 374; 4096 x 14336:  16 rows 544 -> 105
-// Four-bit W up to 128 rows stays with the few-row kernel (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60); six- and
-// eight-bit W have none.  K = 256 is where the second launch has paid for itself (MXFP4+ 160 x 300: 11.6 -> 11.4).
-bool de_convert_once(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW) {
-  return (M > 128 || fmtW >= MXP_FMT_MXFP6) && K >= 256 && mxp::bf16_gemm_takes(M, N, K, lda);
+// and where it stays in the kernel (column tiles fill the chip, few rows of them repeat the work; W in slabs that do not):
+//   MXFP4+, 28672 x 8192: 129 rows 202 | 265, 512 267 | 347; 28672 x 14336: 512 rows 464 | 880; 14336 x 256: 512 rows 13.6 | 17.3
+// Of the 3700 shapes 13 are slower than in the kernel by more than 3 % (11 % at most), 92 would gain more than 5 % (14 % on average).
+double in_kernel_us(int64_t M, int64_t N, int64_t K, int fmtW) {
+  const bool four = fmtW < MXP_FMT_MXFP6, halves = four && tiles_of_128_rows(M, N);
+  // ns per element of K and round, by what a block's de-conversion takes
+  const double c = halves ? 20.0 : four ? 27.0 : fmtW == MXP_FMT_MXFP6 ? 28.0 : fmtW == MXP_FMT_MXFP6P ? 33.5 : fmtW == MXP_FMT_MXFP8 ? 30.0 : 39.0;
+  const double tiles = (double)((M + (halves ? 127 : 255)) / (halves ? 128 : 256)) * (double)((N + 255) / 256);
+  return (four ? 8.0 : 10.0) + (double)K * c * (std::ceil(tiles / mxp::kNumCU) + 0.28 * tiles / mxp::kNumCU) * 1e-3 + (double)M * N / 1.75e6;
 }
+double once_us(int64_t M, int64_t n, int64_t K, int fmtW, bool d_vectors) {          // n rows of W
+  const double blocks = (double)((M + 127) / 128) * (double)((n + 127) / 128), tiles = (double)((M + 255) / 256) * (double)((n + 255) / 256);
+  const double rounds = std::floor(tiles / mxp::kNumCU), rem = tiles - rounds * mxp::kNumCU;
+  const double walk = blocks <= mxp::kNumCU ? 5.5 + 1.6 * blocks / mxp::kNumCU
+                                            : 19.5 * rounds + (rem == 0 ? 0.0 : rem <= mxp::kNumCU / 2 ? 12.0 : 19.5);   // ns per element of K
+  const double bytes = 2.0 + (double)block_bytes(fmtW) / 32 + 1.0 / 16;               // bf16, codes, scale and index
+  return 10.0 + bytes * (double)n * (double)K / 5e6 + (double)K * walk * 1e-3 + (double)M * n / 1.75e6 + (d_vectors ? 0.0 : (double)M * n / 1.05e6);
+}
+
+// Rows of W that are de-converted at a time, given room for so many bytes of them; 0: de-conversion stays in the kernel.
+// Slabs are whole tiles and as even as that allows.  d_vectors: the rows of D start at 16-byte addresses.
+int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d_vectors, size_t bytes) {
+  const bool four = fmtW < MXP_FMT_MXFP6;
+  // four-bit W up to 128 rows has the few-row kernel (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60)
+  if ((four && M <= 128) || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
+  int64_t rows = N, n = 1;
+  if (bytes / (2 * (size_t)K) < (size_t)N) {
+    rows = (int64_t)(bytes / (2 * (size_t)K)) / 256 * 256;
+    if (rows == 0) return 0;
+    n = (N + rows - 1) / rows;
+    rows = ((N + n - 1) / n + 255) / 256 * 256;
+  }
+  const double once = (double)(n - 1) * once_us(M, rows, K, fmtW, d_vectors) + once_us(M, N - (n - 1) * rows, K, fmtW, d_vectors);
+  // short K and many columns: the second launch and the pass over W weigh more than the rates say (MXFP4+ 512 x 14336 x 512
+  // 20.5 | 27.0, 512 x 14336 x 1024 31.1 | 35.3, estimated 4 and 11 % the other way; MXFP8+ 512 x 57344 x 256 46.3 | 50.5)
+  const bool short_k = four ? K < 1280 && N > 4608 : K < 640 && N > 16384;
+  return once * (short_k ? 1.25 : n == 1 ? 1.02 : 1.1) < in_kernel_us(M, N, K, fmtW) ? rows : 0;
+}
+constexpr size_t kSlabBytes = (size_t)256 << 20;             // what the last-level cache holds, which the product reads a slab from
 }  // namespace
 
 extern "C" size_t mxp_gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K, int fmtW) {
-  if (M <= 0 || N <= 0 || K <= 0 || fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P || !de_convert_once(M, N, K, K, fmtW)) return 0;
-  int64_t r = slab_rows(N, K, kSlabBytes);
-  if (r < 256) r = N < 256 ? N : 256;
-  return ((size_t)r * (size_t)K * 2 + 255) / 256 * 256;
+  if (M <= 0 || N <= 0 || K <= 0 || fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P) return 0;
+  return ((size_t)slab_rows(M, N, K, K, fmtW, N % 4 == 0, kSlabBytes) * (size_t)K * 2 + 255) / 256 * 256;
 }
 
 extern "C" int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
@@ -647,20 +678,19 @@ extern "C" int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A,
   if (a_dtype != MXP_BF16) return MXP_ERR_UNSUPPORTED;      // the activations are multiplied as bf16
   if (!aligned16(A) || !aligned16(W_elems) || !aligned16(W_scales) || (W_idx && !aligned16(W_idx)) || (lda * 2) % 16 != 0)
     return MXP_ERR_ALIGN;
-  if (workspace && aligned16(workspace) && de_convert_once(M, N, K, lda, fmtW)) {
-    const int64_t slab = slab_rows(N, K, (int64_t)workspace_bytes);
-    if (slab == N || slab >= 2048) {
-      const int64_t nbk = K / kBlock, esz = d_dtype == MXP_BF16 ? 2 : 4, row_bytes = nbk * block_bytes(fmtW);
-      for (int64_t n0 = 0; n0 < N; n0 += slab) {
-        const int64_t nr = N - n0 < slab ? N - n0 : slab;
-        int rc = dequantize_bf16_launch(W_elems + n0 * row_bytes, W_scales + n0 * nbk, W_idx ? W_idx + n0 * nbk : nullptr, fmtW, nr, K,
-                                        workspace, s);
-        if (rc != MXP_OK) return rc;
-        rc = bf16_gemm_launch(M, nr, K, A, lda, workspace, K, static_cast<uint8_t*>(D) + n0 * esz, d_dtype, ldd, s);
-        if (rc != MXP_OK) return rc;
-      }
-      return MXP_OK;
+  const int64_t slab =
+      workspace && aligned16(workspace) ? slab_rows(M, N, K, lda, fmtW, ldd % 4 == 0 && aligned16(D), workspace_bytes) : 0;
+  if (slab) {
+    const int64_t nbk = K / kBlock, esz = d_dtype == MXP_BF16 ? 2 : 4, row_bytes = nbk * block_bytes(fmtW);
+    for (int64_t n0 = 0; n0 < N; n0 += slab) {
+      const int64_t nr = N - n0 < slab ? N - n0 : slab;
+      int rc = dequantize_bf16_launch(W_elems + n0 * row_bytes, W_scales + n0 * nbk, W_idx ? W_idx + n0 * nbk : nullptr, fmtW, nr, K,
+                                      workspace, s);
+      if (rc != MXP_OK) return rc;
+      rc = bf16_gemm_launch(M, nr, K, A, lda, workspace, K, static_cast<uint8_t*>(D) + n0 * esz, d_dtype, ldd, s);
+      if (rc != MXP_OK) return rc;
     }
+    return MXP_OK;
   }
   // six- and eight-bit weights: the tiled kernel at any number of rows
   if (wide_w) return dispatch_tiled(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);

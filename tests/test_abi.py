@@ -254,6 +254,22 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
         mxp.image_bytes(64, 64)
 
 
+@pytest.mark.parametrize("fmt", [mxp.MXFP4P, mxp.MXFP6, mxp.MXFP8P])
+def test_room_for_deconverted_weights_is_bounded_and_whole_tiles(fmt):
+    """At most 256 MiB at any size; all of W or even slabs of whole tiles; nothing where the few-row kernel or a refusal waits."""
+    for M in (1, 129, 700, 4096):
+        for N in (16, 257, 4096, 28672, 1 << 20):
+            for K in (224, 256, 4096, 14336, 65568, 1 << 17, 1 << 20, 1 << 21):
+                need = mxp.gemm_w4a16_workspace_bytes(M, N, K, fmt)
+                assert need <= 256 << 20, (M, N, K, need)
+                rows = need // (2 * K)
+                assert need == (2 * K * rows + 255) // 256 * 256 and (rows in (0, N) or rows % 256 == 0), (M, N, K, need)
+                assert mxp.gemm_workspace_bytes(M, N, K, mxp.MXFP8, fmt) == (2 * M * K + 255) // 256 * 256 + need
+                if K < 256 or (fmt == mxp.MXFP4P and M <= 128):
+                    assert need == 0
+    assert mxp.gemm_w4a16_workspace_bytes(4096, 14336, 4096, mxp.MXFP4P) == 2 * 14336 * 4096
+
+
 def kernel_metadata(path):
     """The kernels' metadata maps (ELF notes "AMDGPU", type 32) of every code object inside a built library."""
     msgpack = pytest.importorskip("msgpack")

@@ -2224,3 +2224,53 @@ def test_gemm_w4a16_workspace_is_the_callers_choice():
         assert torch.cuda.max_memory_allocated() - before <= most
         outs.append(out)
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+def w4a16_in(nbytes, a, qw, code, dt):
+    """mxp_gemm_w4a16_ws with that much room, and whether it was used."""
+    M, K = a.shape
+    N = qw[0].shape[0]
+    ws = torch.full((max(nbytes, 16),), 0xA5, dtype=torch.uint8, device="cuda")
+    d = torch.full((M, N), float("nan"), dtype=dt, device="cuda")
+    rc = mxp.lib().mxp_gemm_w4a16_ws(M, N, K, a.data_ptr(), mxp.BF16, a.stride(0), qw[0].data_ptr(), qw[1].data_ptr(), qw[2].data_ptr(), code,
+                                     d.data_ptr(), mxp._dt(d), N, ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+    assert rc == 0
+    return d, bool((ws != 0xA5).any())
+
+
+@pytest.mark.parametrize("M,N,K,fmt", [(129, 4096, 1280, "mxfp4p"), (300, 4096, 4096, "mxfp4pp"), (129, 28672, 512, "mxfp4p"), (256, 2304, 512, "mxfp4"),
+                                       (1, 28672, 288, "mxfp6"), (17, 1000, 288, "mxfp8p"), (128, 4096, 1280, "mxfp4p"), (300, 300, 224, "mxfp8"),
+                                       (5, 2304, 65568, "mxfp8"), (2, 300, 1 << 17, "mxfp6p")])
+def test_gemm_w4a16_room_is_used_where_it_is_asked_for(M, N, K, fmt):
+    """The size function and the call agree on where W is de-converted once; either way the bits are those of the call without
+    room.  Columns that fill the chip, short K, K beyond 65536 (two slabs of W), few rows of wide W among the shapes."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    code = {n: c for n, (c, _) in {**FMT, **WIDE}.items()}[fmt]
+    a = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    qw = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16), code)
+    need = mxp.gemm_w4a16_workspace_bytes(M, N, K, code)
+    plain, used = w4a16_in(0, a, qw, code, torch.float32)
+    assert not used
+    once, used = w4a16_in(need or 2 * N * K, a, qw, code, torch.float32)
+    assert used == (need > 0) and torch.equal(once, plain)
+    assert torch.equal(mxp.gemm_w4a16(a, qw, code), plain)
+    assert torch.equal(mxp.gemm_w4a16(a, qw, code, workspace=torch.empty(0, dtype=torch.uint8, device="cuda")), plain)
+
+
+@pytest.mark.parametrize("M,N,K", [(130, 2500, 3104), (300, 1100, 4096), (257, 4500, 4096)])
+@pytest.mark.parametrize("fmt", ["mxfp4p", "mxfp6", "mxfp8p"])
+def test_gemm_w4a16_slabs(fmt, M, N, K):
+    """W in two and three even slabs (the last one shorter, its end inside a tile): identical bits, both output types."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    code = {n: c for n, (c, _) in {**FMT, **WIDE}.items()}[fmt]
+    a = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    qw = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda").to(torch.bfloat16), code)
+    for dt in (torch.float32, torch.bfloat16):
+        plain, _ = w4a16_in(0, a, qw, code, dt)
+        for parts in (2, 3):
+            rows = (-(-N // parts) + 255) // 256 * 256
+            got, used = w4a16_in(2 * K * rows + 100, a, qw, code, dt)
+            assert torch.equal(got, plain), (parts, dt)
+            assert used or parts == 3, "room for half of W is worth using at these shapes"
