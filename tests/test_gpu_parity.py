@@ -2274,3 +2274,68 @@ def test_gemm_w4a16_slabs(fmt, M, N, K):
             got, used = w4a16_in(2 * K * rows + 100, a, qw, code, dt)
             assert torch.equal(got, plain), (parts, dt)
             assert used or parts == 3, "room for half of W is worth using at these shapes"
+
+
+@pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp", "mxfp6", "mxfp6p", "mxfp8", "mxfp8p"])
+def test_gemm_w4a16_special_blocks_above_128_rows(w_fmt):
+    """Flushed, NaN, extreme-scale blocks and every delta through the tiled kernel and through the product of W as bf16."""
+    w, fmt = mxpp_tensor(rows=96, K=512, bf16=False), {**FMT, **WIDE}[w_fmt]
+    w[40:77, :160] = special_tensor(bf16=False)
+    if w_fmt in WIDE:
+        w[49, 5] = 1.0                                           # (no 3e38 and no infinity: the sums are compared in fp32)
+        qw = oracle.wide.quantize(w, fmt[1])
+        w64 = oracle.wide.dequantize(qw, fmt[1])                 # values below the normal range are rounded to bf16 first
+        w64 = torch.from_numpy(w64.astype(np.float32)).to(torch.bfloat16).double().numpy()
+    else:
+        qw = oracle.quantize(w, fmt[1])
+        w64 = oracle.dequantize(qw, fmt[1]).astype(np.float64)
+    a = synth.activations(130, 512, config_id=1, tensor_id=64)
+    a64 = synth.bf16_bits_to_f32(a).astype(np.float64)
+    with np.errstate(all="ignore"):
+        ref, S = a64 @ w64.T, np.abs(a64) @ np.abs(w64).T
+    nan = np.isnan(ref)
+    ok = ~nan & np.isfinite(ref) & (np.abs(ref) < 1e37) & (S < 1e37)
+    assert nan.any() and ok.sum() > 2000
+    dev = q_dev(qw)
+    for nbytes in (0, 2 * 96 * 512):
+        D, used = w4a16_in(nbytes, to_dev(a), dev, fmt[0], torch.float32)
+        assert used == (nbytes > 0)
+        D = D.double().cpu().numpy()
+        assert (np.isnan(D) == nan).all()
+        assert (np.abs(D - ref)[ok] <= 2.0 ** -16 * S[ok] + 1.2e-38).all()
+
+
+@pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp"])
+@pytest.mark.parametrize("M,N,K", [(257, 300, 1024), (300, 520, 2048), (512, 1100, 640), (129, 70, 4160)])
+def test_gemm_w4a16_many_rows_without_room(M, N, K, w_fmt):
+    """The tiled kernel that de-converts on its way into LDS (tiles of 128 rows), against the oracle."""
+    a = synth.activations(M, K, config_id=1, tensor_id=62)
+    qw = oracle.quantize(synth.weights(N, K, config_id=1, tensor_id=63, t3_frac=0.001), FMT[w_fmt][1])
+    ref, S = oracle.gemm_w4a16(a, qw, FMT[w_fmt][1])
+    D, _ = w4a16_in(0, to_dev(a), q_dev(qw), FMT[w_fmt][0], torch.float32)
+    check_gemm(D, ref, S, "w4a16 without room %s %dx%dx%d" % (w_fmt, M, N, K))
+
+
+@pytest.mark.parametrize("fa,fb", [("mxfp8p", "mxfp8p"), ("mxfp8", "mxfp4p"), ("mxfp6p", "mxfp4pp"), ("mxfp4pp", "mxfp6"), ("mxfp4p", "mxfp8")])
+@pytest.mark.parametrize("M,N,K", [(257, 2500, 1280), (40, 700, 288)])
+def test_gemm_room_for_one_operand_and_for_slabs_of_the_other(M, N, K, fa, fb):
+    """mxp_gemm on de-converted operands with no room, room for A, for A and half of B, for both: identical bits above 128 rows,
+    the same products in another order below (4-bit B: the few-row kernel)."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(K)
+    code = {n: c for n, (c, _) in {**FMT, **WIDE}.items()}
+    qa = mxp.quantize(torch.randn((M, K), generator=gen, device="cuda"), code[fa])
+    qb = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda"), code[fb])
+    a64, b64 = (mxp.dequantize(q, code[f]).double() for q, f in ((qa, fa), (qb, fb)))
+    ref, S = (a64 @ b64.t()).cpu().numpy(), (a64.abs() @ b64.abs().t()).cpu().numpy()
+    room_a, half = (2 * M * K + 255) // 256 * 256, 2 * K * ((N // 2 + 255) // 256 * 256)
+    first = None
+    for nbytes in (16, room_a - 16, room_a, room_a + half, room_a + 2 * N * K):
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+        D = mxp.gemm(qa, code[fa], qb, code[fb], workspace=ws)
+        assert bool((ws[:room_a] != 0xA5).any()) == (nbytes >= room_a)
+        if nbytes == room_a + 2 * N * K and M > 128:
+            assert bool((ws[room_a:] != 0xA5).any())
+        check_gemm(D, ref, S, "%s x %s %dx%dx%d, room %d" % (fa, fb, M, N, K, nbytes))
+        first = D if first is None else first
+        assert M <= 128 or torch.equal(D, first), (fa, fb, nbytes)
