@@ -1527,7 +1527,7 @@ int launch_block(const uint8_t* Ai, const uint8_t* Bi, int64_t M, int64_t N, int
 constexpr int kCanonPatchStride = 144;                        // bytes per patch row: 128 + 16 against bank conflicts
 constexpr int kCanonPatchBytes = 32 * kCanonPatchStride;
 
-template <int TMR, int CT, bool OUT_BF16, bool PLUS, int AT, int WAVES>
+template <int TMR, int CT, bool OUT_BF16, bool PLUS, int AT, int WAVES, bool AHEAD>
 __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uint8_t* __restrict__ a_el, const uint8_t* __restrict__ a_sc,
                                                                        const u32x4* __restrict__ w_el, const uint8_t* __restrict__ w_sc,
                                                                        const uint8_t* __restrict__ w_ix, int64_t nbk, int k_tiles,
@@ -1552,7 +1552,7 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
 
   const int n_chunks = (k_tiles + CHUNK - 1) / CHUNK;
   const int first = (int)((blockIdx.x * 5u) % (uint32_t)n_chunks);
-  // one chunk of weights as it lies in memory; the next one's loads fly while this one is multiplied
+  // one chunk of weights as it lies in memory; AHEAD: the next one's loads fly while this one is multiplied
   u32x4 raw[CT][4];
   u32x2 s8n[CT], i8n[CT];
   auto load_weights = [&](int ci) {
@@ -1576,9 +1576,10 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
       }
     }
   };
-  if (wave < n_chunks) load_weights(wave);
+  if (AHEAD && wave < n_chunks) load_weights(wave);
   for (int ci = wave; ci < n_chunks; ci += WAVES) {
     const int q = ci + first < n_chunks ? ci + first : ci + first - n_chunks;
+    if (!AHEAD) load_weights(ci);
     u32x2 s8[CT], i8[CT];
 #pragma unroll
     for (int j = 0; j < CT; ++j) { s8[j] = s8n[j]; i8[j] = i8n[j]; }
@@ -1606,7 +1607,7 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
 #pragma unroll
       for (int r = 0; r < 4; ++r)
         *reinterpret_cast<u32x4*>(patch + (8 * r + ld_row) * kCanonPatchStride + ld_piece * 16) = raw[j][r];
-      if (j == CT - 1 && ci + WAVES < n_chunks) load_weights(ci + WAVES);
+      if (AHEAD && j == CT - 1 && ci + WAVES < n_chunks) load_weights(ci + WAVES);
 #pragma unroll
       for (int c = 0; c < CHUNK; ++c) {
         const u32x4 nib = *reinterpret_cast<const u32x4*>(patch + n_in * kCanonPatchStride + (2 * c + h) * 16);
@@ -1677,7 +1678,7 @@ __global__ void __launch_bounds__(64 * WAVES) gemm_skinny_canon_kernel(const uin
   }
 }
 
-template <int TMR, int CT, bool PLUS, int WAVES>
+template <int TMR, int CT, bool PLUS, int WAVES, bool AHEAD>
 void launch_canon_cfg(bool bf, int64_t n_ct, hipStream_t s, const uint8_t* ae, const uint8_t* as, const uint8_t* we, const uint8_t* ws,
                       const uint8_t* wi, int64_t nbk, int kt, int64_t M, int64_t N, void* D, int64_t ldd) {
   constexpr int part_bytes = WAVES * TMR * CT * 16 * 64 * 4, patch_bytes = WAVES * kCanonPatchBytes;
@@ -1686,12 +1687,12 @@ void launch_canon_cfg(bool bf, int64_t n_ct, hipStream_t s, const uint8_t* ae, c
   const dim3 grid((unsigned)((n_ct + CT - 1) / CT));
   const u32x4* we4 = reinterpret_cast<const u32x4*>(we);
   if (bf) {
-    allow_dynamic_lds<&gemm_skinny_canon_kernel<TMR, CT, true, PLUS, kTileBytes, WAVES>>((int)lds);
-    hipLaunchKernelGGL((gemm_skinny_canon_kernel<TMR, CT, true, PLUS, kTileBytes, WAVES>), grid, dim3(64 * WAVES), lds, s, ae, as, we4, ws, wi,
+    allow_dynamic_lds<&gemm_skinny_canon_kernel<TMR, CT, true, PLUS, kTileBytes, WAVES, AHEAD>>((int)lds);
+    hipLaunchKernelGGL((gemm_skinny_canon_kernel<TMR, CT, true, PLUS, kTileBytes, WAVES, AHEAD>), grid, dim3(64 * WAVES), lds, s, ae, as, we4, ws, wi,
                        nbk, kt, M, N, D, ldd);
   } else {
-    allow_dynamic_lds<&gemm_skinny_canon_kernel<TMR, CT, false, PLUS, kTileBytes, WAVES>>((int)lds);
-    hipLaunchKernelGGL((gemm_skinny_canon_kernel<TMR, CT, false, PLUS, kTileBytes, WAVES>), grid, dim3(64 * WAVES), lds, s, ae, as, we4, ws, wi,
+    allow_dynamic_lds<&gemm_skinny_canon_kernel<TMR, CT, false, PLUS, kTileBytes, WAVES, AHEAD>>((int)lds);
+    hipLaunchKernelGGL((gemm_skinny_canon_kernel<TMR, CT, false, PLUS, kTileBytes, WAVES, AHEAD>), grid, dim3(64 * WAVES), lds, s, ae, as, we4, ws, wi,
                        nbk, kt, M, N, D, ldd);
   }
 }
@@ -1707,18 +1708,28 @@ int launch_canon(const uint8_t* Ai, const uint8_t* we, const uint8_t* ws, const 
   const uint8_t *ae = Ai, *as = Ai + ga.elem_bytes;
   const bool bf = d_dtype == MXP_BF16, wide = kt >= 64;
   constexpr int64_t kEnough = 200;
+#define MXP_CANON(TMR, CT, WAVES, AHEAD) launch_canon_cfg<TMR, CT, PLUS, WAVES, AHEAD>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd)
   if (M <= 32) {
-    // One column tile per workgroup: 36 KiB of LDS, so that several workgroups share a compute unit and one's loads run under
-    // another's products.  (8 x 28672 x 8192: 43.8 us against 48.1 with two tiles and 48.4 with four; 1 x 14336 x 4096: 17.4
-    // against 18.5 / 27.3.)  Long K with fewer tiles: sixteen wavefronts (9 x 8117 x 12800 21.9 against 22.8), then two
-    // tiles (16 x 13234 x 13056 28.9 against 30.7).
-    if (wide && ct / 2 < kEnough) launch_canon_cfg<1, 1, PLUS, 16>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
-    else if (wide && ct / 4 < kEnough) launch_canon_cfg<1, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
-    else launch_canon_cfg<1, 1, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
+    // One column tile per workgroup of eight wavefronts (36 KiB of LDS, 111 registers for MXFP4+): two workgroups share a
+    // compute unit, one's loads run under the other's products, and no round over the chip is nearly empty (8 x 28672 x 8192
+    // with its conversion 43.6 us as four tiles, 41.5 as one; 16 x 40000 x 8192 75.6 -> 53.4).  From K = 4096 on
+    //  - up to 400 tiles: sixteen wavefronts, without loads ahead (1 x 3000 x 14336 20.6 against 21.6 with them, 22.4 with eight
+    //    wavefronts and them);
+    //  - 400 - 800: two tiles (16 x 13500 x 8192 26.1 against 27.0 with one, 16 x 13500 x 14336 39.7 against 42.4);
+    //  - 800 - 1024, one round of workgroups of four tiles: four, without loads ahead, where a tile's products outweigh its bytes,
+    //    that is plain codes or more than 16 rows (MXFP4 32 x 28672 x 8192 35.4 against 42.4 with one, 1 x 25700 x 14336 53.0
+    //    against 55.3; MXFP4+ 32 x 28672 x 14336 73.8 against 79.7, but 1 x 28672 x 14336 73.5 against 68.9).
+    if (wide && ct / 2 < kEnough) MXP_CANON(1, 1, 16, false);
+    else if (wide && ct / 4 < kEnough) MXP_CANON(1, 2, 8, true);
+    else if (wide && ct <= 4 * kNumCU && (!PLUS || M > 16)) MXP_CANON(1, 4, 8, false);
+    else MXP_CANON(1, 1, 8, true);
   } else {
-    if (ct / 2 >= kEnough) launch_canon_cfg<2, 2, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);
-    else launch_canon_cfg<2, 1, PLUS, 8>(bf, ct, s, ae, as, we, ws, wi, nbk, kt, M, N, D, ldd);   // 16 wavefronts would spill
+    // (sixteen wavefronts would spill; K below 1024: no wavefront has a chunk ahead, 40 x 28672 x 256 16.9 against 17.8)
+    if (ct / 2 >= kEnough && kt < 16) MXP_CANON(2, 2, 8, false);
+    else if (ct / 2 >= kEnough) MXP_CANON(2, 2, 8, true);
+    else MXP_CANON(2, 1, 8, true);
   }
+#undef MXP_CANON
   return launch_status();
 }
 

@@ -2339,3 +2339,21 @@ def test_gemm_room_for_one_operand_and_for_slabs_of_the_other(M, N, K, fa, fb):
         check_gemm(D, ref, S, "%s x %s %dx%dx%d, room %d" % (fa, fb, M, N, K, nbytes))
         first = D if first is None else first
         assert M <= 128 or torch.equal(D, first), (fa, fb, nbytes)
+
+
+@pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p"])
+@pytest.mark.parametrize("M,N,K", [(5, 3001, 4352), (3, 12830, 4096), (32, 25570, 4352), (16, 25601, 4096), (17, 25601, 4352), (32, 32770, 4096),
+                                   (40, 12830, 512), (64, 12801, 768), (33, 12830, 1024)])
+def test_gemm_decode_canonical_every_launch_class(M, N, K, w_fmt):
+    """Canonical weights at the edges of the launch rule: sixteen wavefronts, two and four column tiles at long K (chunks that
+    do not divide by the wavefronts, a ragged last group of tiles), and two row tiles with and without loads ahead."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(M + N + K)
+    a = torch.randn((M, K), generator=gen, device="cuda").to(torch.bfloat16)
+    code = FMT[w_fmt][0]
+    qw = mxp.quantize((torch.randn((N, K), generator=gen, device="cuda") * 0.02).to(torch.bfloat16), code)
+    a64 = mxp.dequantize(mxp.quantize(a, mxp.MXFP4P), mxp.MXFP4P).double()
+    w64 = mxp.dequantize(qw, code).double()
+    D = mxp.gemm_decode_bf16a(a, mxp.MXFP4P, qw, code)
+    check_gemm(D, (a64 @ w64.t()).cpu().numpy(), (a64.abs() @ w64.abs().t()).cpu().numpy(), "canonical %s %dx%dx%d" % (w_fmt, M, N, K))
+    assert torch.equal(mxp.gemm_decode_bf16a(a, mxp.MXFP4P, qw, code, out_dtype=torch.bfloat16), D.to(torch.bfloat16))
