@@ -122,9 +122,15 @@ def _check(rc: int, what: str):
         raise MxpError("%s failed: %s (%d)" % (what, status_string(rc), rc))
 
 
+# The current stream's handle without a Stream object per call (16 x 256 x 256 through two quantize calls, gemm and dequantize,
+# host-bound: 54.8 -> 43.9 us).  The name is not part of torch's public interface: without it the public way is taken.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream() -> int:
-    # the handle itself, no Stream object per call: 16 x 256 x 256, six calls of the binding, 54.8 -> 43.9 us (host-bound)
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _dt(t: torch.Tensor) -> int:

@@ -254,6 +254,15 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
         mxp.image_bytes(64, 64)
 
 
+def test_stream_handle_without_torchs_private_name(monkeypatch):
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(mxp, "_raw_stream", None)
+    monkeypatch.setattr(mxp.torch.cuda, "current_stream", lambda: Stream)
+    assert mxp._stream() == 1234
+
+
 @pytest.mark.parametrize("fmt", [mxp.MXFP4P, mxp.MXFP6, mxp.MXFP8P])
 def test_room_for_deconverted_weights_is_bounded_and_whole_tiles(fmt):
     """At most 256 MiB at any size; all of W or even slabs of whole tiles; nothing where the few-row kernel or a refusal waits."""

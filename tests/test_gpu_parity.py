@@ -2357,3 +2357,12 @@ def test_gemm_decode_canonical_every_launch_class(M, N, K, w_fmt):
     D = mxp.gemm_decode_bf16a(a, mxp.MXFP4P, qw, code)
     check_gemm(D, (a64 @ w64.t()).cpu().numpy(), (a64.abs() @ w64.abs().t()).cpu().numpy(), "canonical %s %dx%dx%d" % (w_fmt, M, N, K))
     assert torch.equal(mxp.gemm_decode_bf16a(a, mxp.MXFP4P, qw, code, out_dtype=torch.bfloat16), D.to(torch.bfloat16))
+
+
+def test_calls_run_on_the_current_stream():
+    """The handle that the binding passes, on the default stream, inside and after a side stream's scope."""
+    side = torch.cuda.Stream()
+    assert mxp._stream() == torch.cuda.current_stream().cuda_stream
+    with torch.cuda.stream(side):
+        assert mxp._stream() == side.cuda_stream
+    assert mxp._stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
