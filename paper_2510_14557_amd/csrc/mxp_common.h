@@ -30,7 +30,7 @@ inline bool plain_wide_format(int fmt) { return fmt == MXP_FMT_MXFP6 || fmt == M
 int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K, int64_t ld_src, int fmt, uint8_t* elems,
                          uint8_t* scales, uint8_t* bm_idx, hipStream_t stream);
 int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows,
-                           int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t stream);
+                           int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t stream, bool read_next = false);
 
 // canonical operand -> dense bf16 rows that a product reads next (arguments already checked)
 int dequantize_bf16_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows, int64_t K, void* dst,

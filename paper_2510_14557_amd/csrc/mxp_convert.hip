@@ -455,7 +455,7 @@ int dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t
 namespace mxp {
 int dequantize_bf16_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows, int64_t K, void* dst,
                            hipStream_t s) {
-  if (is_wide_format(fmt)) return wide_dequantize_launch(elems, scales, bm_idx, fmt, rows, K, dst, MXP_BF16, K, s);
+  if (is_wide_format(fmt)) return wide_dequantize_launch(elems, scales, bm_idx, fmt, rows, K, dst, MXP_BF16, K, s, /*read_next=*/true);
   const int64_t nbk = K / kBlock, nq = rows * nbk * 4;
   if (fmt == MXP_FMT_MXFP4PP) return dequantize_launch<2>(elems, scales, bm_idx, rows, K, nbk, nq, dst, true, K, s, false);
   if (fmt == MXP_FMT_MXFP4P) return dequantize_launch<1>(elems, scales, bm_idx, rows, K, nbk, nq, dst, true, K, s, false);

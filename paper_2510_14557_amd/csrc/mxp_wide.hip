@@ -110,9 +110,11 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(uint32_t bits) {
 
 // Groups per lane and pass of the de-conversion: four for bf16 results from 4096 x 4096 values on, one below and for fp32
 // results (us, one | four: MXFP6+ to bf16 64 x 4096 2.9 | 3.4, 2048 x 4096 6.4 | 6.3, 4096 x 4096 10.4 | 9.1, 14336 x 8192
-// 80.9 | 57.3; to fp32 64 x 4096 3.1 | 3.8, 14336 x 8192 137 | 140, MXFP8 14336 x 8192 101 | 143).
+// 80.9 | 57.3; to fp32 64 x 4096 3.1 | 3.8, 14336 x 8192 137 | 140, MXFP8 14336 x 8192 101 | 143).  A product that reads the
+// values next gains from a quarter of that size on, by where they then lie (MXFP8 weights, 64 x 2048 x 2048 22.2 | 21.4,
+// 64 x 1000 x 1024 13.0 | 13.1).
 constexpr int kDequantUnroll = 4;
-constexpr int64_t kDeepGroups = (int64_t)1 << 21;
+constexpr int64_t kDeepGroups = (int64_t)1 << 21, kDeepGroupsReadNext = (int64_t)1 << 19;
 
 // ---- quantize -------------------------------------------------------------------------------------------------
 // nq = number of 8-element groups (4 per block); a quad of lanes is one block, so a quad is inside or outside as a whole.
@@ -811,9 +813,9 @@ int wide_quantize_launch(const void* src, int src_dtype, int64_t rows, int64_t K
 }
 
 int wide_dequantize_launch(const uint8_t* elems, const uint8_t* scales, const uint8_t* bm_idx, int fmt, int64_t rows,
-                           int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t s) {
+                           int64_t K, void* dst, int dst_dtype, int64_t ld_dst, hipStream_t s, bool read_next) {
   const int64_t nbk = K / kBlock, nq = rows * nbk * 4;
-  const bool bf = dst_dtype == MXP_BF16, dense = rows == 1 || ld_dst == K, deep = bf && nq >= kDeepGroups;
+  const bool bf = dst_dtype == MXP_BF16, dense = rows == 1 || ld_dst == K, deep = bf && nq >= (read_next ? kDeepGroupsReadNext : kDeepGroups);
   const int64_t per = 256 * (deep ? kDequantUnroll : 1), want = (nq + per - 1) / per, cap = (int64_t)1 << 24;
   const dim3 grid((unsigned)(want < cap ? want : cap));
 #define MXP_LAUNCH_DWD(BT, P, O, DN, U) hipLaunchKernelGGL((dequantize_wide_kernel<BT, P, O, DN, U>), grid, dim3(256), 0, s, elems, scales, bm_idx, nbk, ld_dst, nq, dst)
