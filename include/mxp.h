@@ -273,6 +273,8 @@ int mxp_gemm(int64_t M, int64_t N, int64_t K,
  * or frees memory.  The array holds mxp_gemm_static_capacity() bytes (64 MiB, resident on every GPU the library is used
  * on until the process ends); a product whose images need more -- mxp_gemm_workspace_size(M, N, K, fmtA, fmtB) bytes --
  * returns MXP_ERR_SCRATCH and enqueues nothing (the Llama-8B prefill-MLP product, 4096 x 14336 x 4096, needs 56.3 MiB).
+ * Pairs that are multiplied from de-converted operands, whose workspace is optional, are not refused: they use the array
+ * for A and slabs of B where A fits, and otherwise leave it alone.
  * All calls on one GPU share that array, which keeps the previous call's images: every byte a product reads is
  * rewritten by the image kernels of the same call first, and calls whose work overlaps on one GPU (different streams,
  * or different threads) race -- serialise them.  The first call on a device asks the runtime for the array's address on

@@ -1,6 +1,7 @@
 // mxp_gemm_w4a16 : D[M][N] = A[M][K] (bf16, not quantized) x deq(W)[N][K]^T, W in canonical MXFP4 / MXFP4+ / MXFP4++
 // (few rows: a weight-read-bound kernel; many rows: a tiled kernel, which also takes MXFP6(+) / MXFP8(+) weights and, for
-// the MXFP8+ products of mxp_gemm, quantized eight-bit activations).
+// the MXFP8+ products of mxp_gemm, quantized eight-bit activations), and mxp_gemm_w4a16_ws, which may de-convert W once
+// into a workspace ahead of the bf16 product of mxp_bf16.hip.
 //
 // The conversion-based use of the formats (Sec. 5: on hardware that lacks low-precision units, or for weight-only
 // quantization, the blocks are de-converted to a wider type the hardware multiplies, Eq. 2 inside the kernel; the BM
@@ -606,7 +607,7 @@ namespace {
 // W de-converted once, as bf16, ahead of a plain bf16 product -- or in the product kernel, again for each row of its tiles.
 // Which is faster follows from what either makes of a shape: rounds of tiles over the chip that each walk along K, against
 // a pass over W and fewer, faster rounds.  Both are estimated (us) with the rates that the two routes measured over 3700
-// shapes (1 - 4096 rows, N 200 - 60000, K 256 - 30000, all formats; the estimates are off by 9 and 11 %), and W is de-converted
+// shapes (1 - 4096 rows, N 200 - 60000, K 256 - 30000, six formats; the estimates are off by 9 and 11 %), and W is de-converted
 // once where that is ahead by a margin.  In the kernel -> once, us, bf16 out:
 //   MXFP4+, 14336 x 4096: 160 rows 88.6 -> 60.5, 1024 131 -> 115, 4096 501 -> 363; 4096 x 14336: 160 rows 296 -> 110, 2048 331 -> 205
 //   MXFP8+, 14336 x 4096:  16 rows 162 -> 58.6, 1024 170 -> 119, 4096 668 -> 374; 4096 x 14336:  16 rows 544 -> 105

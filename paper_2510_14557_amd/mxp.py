@@ -13,7 +13,7 @@ import torch
 
 F32, BF16 = 0, 1
 MXFP4, MXFP4P, MXFP4PP = 0, 1, 2
-MXFP6, MXFP6P, MXFP8, MXFP8P = 3, 4, 5, 6          # conversion and de-conversion only
+MXFP6, MXFP6P, MXFP8, MXFP8P = 3, 4, 5, 6          # quantize, dequantize, gemm, gemm_w4a16
 _CODE_BITS = {MXFP4: 4, MXFP4P: 4, MXFP4PP: 4, MXFP6: 6, MXFP6P: 6, MXFP8: 8, MXFP8P: 8}
 IMAGE_E2M3, IMAGE_E2M1, IMAGE_E4M3, IMAGE_E2M1R, IMAGE_E2M1X = 0, 1, 2, 3, 4
 

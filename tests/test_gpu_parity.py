@@ -533,8 +533,9 @@ def test_gemm_few_rows_canonical_route(fa, fb, M, N, K):
 @pytest.mark.parametrize("M,N,K", [(65, 40, 64), (100, 200, 416), (257, 300, 1024), (300, 520, 2048), (512, 1100, 640),
                                    (129, 70, 4160)])
 def test_gemm_w4a16_many_rows(M, N, K, w_fmt):
-    """The tiled form of the conversion-based product (more than 64 activation rows): ragged tiles in M and N, K that
-    ends inside a step (odd number of blocks) and inside a group of 8 blocks."""
+    """The conversion-based product above 64 activation rows as the binding calls it (two passes of the few-row kernel up to
+    128; then W de-converted once, or in the tiled kernel for short K): ragged tiles in M and N, K that ends inside a step
+    (odd number of blocks) and inside a group of 8 blocks."""
     a = synth.activations(M, K, config_id=1, tensor_id=62)
     w = synth.weights(N, K, config_id=1, tensor_id=63, t3_frac=0.001)
     qw = oracle.quantize(w, FMT[w_fmt][1])
@@ -554,7 +555,7 @@ def test_gemm_w4a16_many_rows(M, N, K, w_fmt):
 
 
 def test_gemm_w4a16_special_blocks():
-    """Flushed, NaN, extreme-scale weight blocks and every delta through the tiled kernel."""
+    """Flushed, NaN, extreme-scale weight blocks and every delta through the few-row kernel (70 rows: two passes)."""
     w = mxpp_tensor(rows=96, K=512, bf16=False)
     a = synth.activations(70, 512, config_id=1, tensor_id=64)
     for w_fmt in ("mxfp4p", "mxfp4pp"):
@@ -568,7 +569,7 @@ def test_gemm_w4a16_special_blocks():
 
 
 def test_gemm_w4a16_full_size_sampled():
-    """Prefill MLP shape, bf16 activations x MXFP4+ weights de-converted in the kernel; one output per 32 x 32 sub-tile."""
+    """Prefill MLP shape, bf16 activations x MXFP4+ weights de-converted once; one output per 32 x 32 sub-tile."""
     M, N, K = 4096, 14336, 4096
     a = synth.activations(M, K, config_id=4, tensor_id=0, dtype="bf16")
     w = synth.weights(N, K, config_id=4, tensor_id=1, dtype="bf16")
@@ -1968,7 +1969,7 @@ def test_gemm_operands_deconverted_in_the_kernel_every_pairing():
         check_gemm(D, da @ db.T, np.abs(da) @ np.abs(db).T, "%s x %s, operands de-converted in the kernel" % (fa, fb))
         Db = mxp.gemm(q_dev(qa), ca, q_dev(qb), cb, workspace=small, out_dtype=torch.bfloat16)
         assert torch.equal(Db, D.to(torch.bfloat16)), (fa, fb)
-        assert torch.equal(mxp.gemm(q_dev(qa), ca, q_dev(qb), cb), D), (fa, fb)      # A de-converted once: identical bits
+        assert torch.equal(mxp.gemm(q_dev(qa), ca, q_dev(qb), cb), D), (fa, fb)      # both operands de-converted once: identical bits
 
 
 @pytest.mark.parametrize("w_fmt", ["mxfp4", "mxfp4p", "mxfp4pp", "mxfp6p"])
