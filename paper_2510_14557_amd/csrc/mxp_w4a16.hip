@@ -649,11 +649,14 @@ int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d
   const bool short_k = four ? K < 1280 && N > 4608 : K < 640 && N > 16384;
   return once * (short_k ? 1.25 : n == 1 ? 1.02 : 1.1) < in_kernel_us(M, N, K, fmtW) ? rows : 0;
 }
-constexpr size_t kSlabBytes = (size_t)256 << 20;             // what the last-level cache holds, which the product reads a slab from
+// Room asked for at most: what the last-level cache holds, which the product then reads a slab from (us in slabs of 128 MiB | of
+// 256 | W whole: MXFP4+ 1024 x 28672 x 8192 499 | 440 | 467, 2048 x 57344 x 4096 836 | 782 | 787, 2048 x 28672 x 14336 1444 | 1325 |
+// 1326; few rows and long K would gain from more, 768 x 14336 x 28672 1291 | 903 | 761, which a caller may give).
+constexpr size_t kSlabBytes = (size_t)256 << 20;
 }  // namespace
 
 extern "C" size_t mxp_gemm_w4a16_workspace_bytes(int64_t M, int64_t N, int64_t K, int fmtW) {
-  if (M <= 0 || N <= 0 || K <= 0 || fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P) return 0;
+  if (M <= 0 || N <= 0 || K <= 0 || K > mxp::kMaxGemmK || fmtW < MXP_FMT_MXFP4 || fmtW > MXP_FMT_MXFP8P) return 0;
   return ((size_t)slab_rows(M, N, K, K, fmtW, N % 4 == 0, kSlabBytes) * (size_t)K * 2 + 255) / 256 * 256;
 }
 

@@ -277,6 +277,7 @@ def test_room_for_deconverted_weights_is_bounded_and_whole_tiles(fmt):
                 if K < 256 or (fmt == mxp.MXFP4P and M <= 128):
                     assert need == 0
     assert mxp.gemm_w4a16_workspace_bytes(4096, 14336, 4096, mxp.MXFP4P) == 2 * 14336 * 4096
+    assert mxp.gemm_w4a16_workspace_bytes(4096, 256, (1 << 21) + 32, fmt) == 0          # longer than a product takes
 
 
 def kernel_metadata(path):
