@@ -645,8 +645,9 @@ int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d
   }
   const double once = (double)(n - 1) * once_us(M, rows, K, fmtW, d_vectors) + once_us(M, N - (n - 1) * rows, K, fmtW, d_vectors);
   // short K and many columns: the second launch and the pass over W weigh more than the rates say (MXFP4+ 512 x 14336 x 512
-  // 20.5 | 27.0, 512 x 14336 x 1024 31.1 | 35.3, estimated 4 and 11 % the other way; MXFP8+ 512 x 57344 x 256 46.3 | 50.5)
-  const bool short_k = four ? K < 1280 && N > 4608 : K < 640 && N > 16384;
+  // 20.5 | 27.0, 512 x 14336 x 1024 31.1 | 35.3, estimated 4 and 11 % the other way; MXFP6 1024 x 14336 x 256
+  // 20.4 | 22.5, MXFP8+ 512 x 57344 x 256 46.3 | 50.5)
+  const bool short_k = four ? K < 1280 && N > 4608 : K < 640 && N > 12288;
   return once * (short_k ? 1.25 : n == 1 ? 1.02 : 1.1) < in_kernel_us(M, N, K, fmtW) ? rows : 0;
 }
 // Room asked for at most: what the last-level cache holds, which the product then reads a slab from (us in slabs of 128 MiB | of
