@@ -1334,12 +1334,9 @@ __global__ void __launch_bounds__(256) gemm_block_kernel(const uint8_t* __restri
                                                          int n_rg, int n_cg) {
   static_assert((TMR == 2 || TMR == 4) && (CT == 2 || (CT == 4 && TMR == 4)), "blocks of 64 x 64, 128 x 64 or 128 x 128");
   using C = BlockCfg<TMR, CT, BT, AT>;
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
   constexpr bool BIG = TMR * CT == 16;                                      // 128 x 128: the accumulators fill the AGPRs
   constexpr int WAVES = 4, CHUNK = BIG ? 1 : 2, NBUF = 2;                   // (a third k-tile in flight: 3 - 5 % slower)
-  constexpr int ROWS = 32 * TMR, COLS = 32 * CT, STRIDE = COLS + 4;        // floats per row of a partial block
   extern __shared__ __attribute__((aligned(16))) uint8_t block_lds[];
-  float* part = reinterpret_cast<float*>(block_lds);                        // [WAVES][ROWS][STRIDE]
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
@@ -1399,74 +1396,7 @@ __global__ void __launch_bounds__(256) gemm_block_kernel(const uint8_t* __restri
       }
     }
   }
-  // A 128 x 128 block has four partial blocks of 64 KiB, more than LDS holds: wavefronts 2 and 3 first hand theirs to
-  // wavefronts 0 and 1 in the accumulators' own layout (lane-contiguous 16-byte pieces, no transposition), which add them
-  // to their own; the two sums then go through the row layout like the four partials of the smaller blocks.
-  constexpr int PARTS = BIG ? 2 : WAVES;                                    // partial blocks in the row layout
-  if constexpr (BIG) {
-    f32x4* stage = reinterpret_cast<f32x4*>(block_lds) + (size_t)(wave & 1) * (TMR * CT * 4 * 64) + lane;
-    if (wave >= 2) {
-#pragma unroll
-      for (int i = 0; i < TMR; ++i)
-#pragma unroll
-        for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            stage[((i * CT + jj) * 4 + g) * 64] = (f32x4){acc[i][jj][4 * g], acc[i][jj][4 * g + 1], acc[i][jj][4 * g + 2], acc[i][jj][4 * g + 3]};
-    }
-    __syncthreads();
-    if (wave < 2) {
-#pragma unroll
-      for (int i = 0; i < TMR; ++i)
-#pragma unroll
-        for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 o = stage[((i * CT + jj) * 4 + g) * 64];
-            acc[i][jj][4 * g] += o[0]; acc[i][jj][4 * g + 1] += o[1]; acc[i][jj][4 * g + 2] += o[2]; acc[i][jj][4 * g + 3] += o[3];
-          }
-    }
-    __syncthreads();                                                        // the staging area is read: it becomes the row layout
-  }
-  // partial blocks to LDS as output rows: accumulator quad g of lane l is row l % 32, columns 8 g + 4 (l / 32) .. + 3 of its tile
-  if (wave < PARTS) {
-    float* mine = part + (size_t)wave * ROWS * STRIDE;
-#pragma unroll
-    for (int i = 0; i < TMR; ++i)
-#pragma unroll
-      for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 q4 = {acc[i][jj][4 * g], acc[i][jj][4 * g + 1], acc[i][jj][4 * g + 2], acc[i][jj][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(mine + (32 * i + (lane & 31)) * STRIDE + 32 * jj + 8 * g + 4 * (lane >> 5)) = q4;
-        }
-  }
-  __syncthreads();
-  const bool vec_ok = (ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(Dv) & 15u) == 0);
-  constexpr int QUADS = COLS / 4;                                           // 16-byte pieces per row
-  for (int e = tid; e < ROWS * QUADS; e += 256) {
-    const int r = e / QUADS, q = e % QUADS;
-    f32x4 v = *reinterpret_cast<const f32x4*>(part + r * STRIDE + 4 * q);
-#pragma unroll
-    for (int w = 1; w < PARTS; ++w) v += *reinterpret_cast<const f32x4*>(part + ((size_t)w * ROWS + r) * STRIDE + 4 * q);
-    const int64_t row = rt0 * 32 + r, col = ct0 * 32 + 4 * q;
-    if (row >= M || col >= N) continue;
-    if (vec_ok && col + 3 < N) {
-      if (OUT_BF16) {
-        const u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
-      } else {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(static_cast<float*>(Dv) + row * ldd + col));
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (col + t < N) {
-          if (OUT_BF16) static_cast<uint16_t*>(Dv)[row * ldd + col + t] = (uint16_t)f32_to_bf16_rne(v[t]);
-          else static_cast<float*>(Dv)[row * ldd + col + t] = v[t];
-        }
-    }
-  }
+  store_k_split<TMR, CT>(acc, block_lds, tid, wave, rt0, ct0, M, N, Dv, ldd, OUT_BF16);
 }
 
 // Which shapes take the block kernel: more rows than the few-row kernels take, and one round of workgroups on the chip's
@@ -1495,8 +1425,7 @@ int launch_block(const uint8_t* Ai, const uint8_t* Bi, int64_t M, int64_t N, int
   const int64_t n_rg = (big || tall) ? rg128 : (M + 63) / 64;
 #define MXP_BLOCK(TMRV, CTV, BFV)                                                                                                 \
   do {                                                                                                                            \
-    constexpr int rows_l = (CTV == 4 ? 2 : 4) * 32 * TMRV * (32 * CTV + 4) * 4, stage_l = CTV == 4 ? 2 * 16 * 4 * 64 * 16 : 0;    \
-    constexpr int lds = rows_l > stage_l ? rows_l : stage_l;                                                                      \
+    constexpr int lds = k_split_lds<TMRV, CTV>();                                                                                 \
     static_assert(lds <= 160 * 1024, "partial blocks must fit in LDS");                                                           \
     allow_dynamic_lds<&gemm_block_kernel<TMRV, CTV, BFV, BT, AT>>((int)lds);                                                    \
     hipLaunchKernelGGL((gemm_block_kernel<TMRV, CTV, BFV, BT, AT>), dim3((unsigned)(n_rg * n_cg)), dim3(256), lds, s, ae, as, be, \
@@ -1927,9 +1856,11 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   if (!aligned16(A_elems) || !aligned16(A_scales) || !aligned16(B_elems) || !aligned16(B_scales) || !aligned16(workspace) ||
       (A_idx && !aligned16(A_idx)) || (B_idx && !aligned16(B_idx)))
     return MXP_ERR_ALIGN;
+  if (workspace_bytes < mxp_gemm_workspace_bytes_fmt(M, N, K, fmtA, fmtB)) return MXP_ERR_WORKSPACE;
+  if (canon_gemm_takes(M, N, K, fmtA, fmtB))                 // (the workspace is not touched then)
+    return canon_gemm_launch(M, N, K, A_elems, A_scales, A_idx, fmtA, B_elems, B_scales, B_idx, fmtB, D, d_dtype, ldd, s);
   if (six && !(is_fp6(fmtA) && is_fp6(fmtB)) && (fmtA == MXP_FMT_MXFP6P || fmtB == MXP_FMT_MXFP6P)) {
     // MXFP6+ with a four-bit operand (Sec. 5: the approach carries over to MXFP6+): two K segments
-    if (workspace_bytes < mxp_gemm_workspace_bytes_fmt(M, N, K, fmtA, fmtB)) return MXP_ERR_WORKSPACE;
     uint8_t* wa2 = static_cast<uint8_t*>(workspace);
     uint8_t* wb2 = wa2 + align_up(mxp_image_bytes_fp6(M, K, 2));
     rc = is_fp6(fmtA) ? prepack_fp6_launch(A_elems, A_scales, A_idx, fmtA, M, K, 2, 0x2u, wa2, s)
@@ -1942,7 +1873,6 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   }
   if (six && !(is_fp6(fmtA) && is_fp6(fmtB))) {
     // plain MXFP6 with a four-bit operand: one E2M3 image each (a plain MXFP4 B stays in four-bit codes)
-    if (workspace_bytes < mxp_gemm_workspace_bytes(M, N, K)) return MXP_ERR_WORKSPACE;
     uint8_t* wa = static_cast<uint8_t*>(workspace);
     uint8_t* wb = wa + align_up((size_t)image_geom(M, K).total());
     rc = is_fp6(fmtA) ? prepack_fp6_launch(A_elems, A_scales, nullptr, fmtA, M, K, 1, 0u, wa, s)
@@ -1957,7 +1887,6 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   }
   if (six) {
     const Fp6Plan plan = fp6_plan(fmtA, fmtB);
-    if (workspace_bytes < mxp_gemm_workspace_bytes_fmt(M, N, K, fmtA, fmtB)) return MXP_ERR_WORKSPACE;
     uint8_t* wa6 = static_cast<uint8_t*>(workspace);
     uint8_t* wb6 = wa6 + align_up(mxp_image_bytes_fp6(M, K, plan.n_seg));
     rc = prepack_fp6_launch(A_elems, A_scales, A_idx, fmtA, M, K, plan.n_seg, plan.mask_a, wa6, s);
@@ -1970,7 +1899,6 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
     // one MXFP4++ operand (Sec. 4.3; Sec. 7.1: MX++ activations on MXFP4 / MXFP4+ weights): the exact product over two K
     // segments -- the MXFP4++ operand as [elements without the BM, scale lowered by delta | the BM alone, own scale], the
     // other operand as its E2M3 image twice
-    if (workspace_bytes < mxp_gemm_workspace_bytes_fmt(M, N, K, fmtA, fmtB)) return MXP_ERR_WORKSPACE;
     constexpr uint32_t kSplit = 1u | (2u << 2), kTwice = 0u;
     uint8_t* wa2 = static_cast<uint8_t*>(workspace);
     uint8_t* wb2 = wa2 + align_up(mxp_image_bytes_fp6(M, K, 2));
@@ -1982,7 +1910,6 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   }
   if (pp) {
     // both operands MXFP4++: E4M3 images (Sec. 4.3), FP8 MFMAs
-    if (workspace_bytes < mxp_gemm_workspace_bytes_e4m3(M, N, K)) return MXP_ERR_WORKSPACE;
     uint8_t* wa8 = static_cast<uint8_t*>(workspace);
     uint8_t* wb8 = wa8 + align_up((size_t)image_geom(M, K, kTileBytesE4M3).total());
     rc = prepack_e4m3_launch(A_elems, A_scales, A_idx, fmtA, M, K, wa8, s);
@@ -1991,7 +1918,6 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
     if (rc != MXP_OK) return rc;
     return gemm_images(wa8, MXP_IMAGE_E4M3, wb8, MXP_IMAGE_E4M3, M, N, K, D, d_dtype, ldd, s);
   }
-  if (workspace_bytes < mxp_gemm_workspace_bytes(M, N, K)) return MXP_ERR_WORKSPACE;
   uint8_t* wa = static_cast<uint8_t*>(workspace);
   uint8_t* wb = wa + align_up((size_t)image_geom(M, K).total());
   if (M <= 64 && K % 256 == 0 && (fmtB == MXP_FMT_MXFP4P || fmtA != fmtB)) {

@@ -17,6 +17,25 @@ __device__ __forceinline__ uint32_t widen4(uint32_t h) {
   return ((x * 0x44u) & 0x0003C03Cu) | ((y * 0x110u) & 0x00F00F00u);
 }
 
+// 32 E2M1 codes -> 32 E2M3 codes by the conversion hardware: every E2M1 number is an E2M3 number (same exponent bias, mantissa m00),
+// so 16 two-element conversions to bf16 and one 32-element conversion to six-bit codes are exact and yield code = nibble << 2
+// at bit 6 i of the lane's 192-bit operand -- about a fifth of the vector instructions of spreading the nibbles by hand.
+__device__ __forceinline__ void widen_e2m3(const uint32_t (&n)[4], uint32_t (&d)[6]) {
+  union { uint32_t u[16]; img_v32bf v; } c;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    union { uint32_t u; img_v2bf v; } c0, c1, c2, c3;
+    c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 0);
+    c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 1);
+    c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 2);
+    c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 3);
+    c.u[4 * j] = c0.u; c.u[4 * j + 1] = c1.u; c.u[4 * j + 2] = c2.u; c.u[4 * j + 3] = c3.u;
+  }
+  const img_u32x6 cv = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(c.v, 1.0f);
+#pragma unroll
+  for (int j = 0; j < 6; ++j) d[j] = cv[j];
+}
+
 // One thread widens one 32-element block into its 24-byte E2M3 operand.  A 256-thread group covers 32 rows x 8
 // consecutive K-blocks (4 k-tiles): thread t takes row t / 8, block t % 8, so the eight lanes of a row read 128
 // contiguous bytes.  The finished blocks are dropped at their lane slots of the four tiles in LDS; the tiles are
@@ -47,21 +66,8 @@ __device__ __forceinline__ void prepack_body(uint32_t wg, uint8_t* tiles, uint8_
     if (PLUS && sbyte != 0u && sbyte != 255u) bm = bm_idx[b] & 31u;
     if (sbyte == 0u) n[0] = n[1] = n[2] = n[3] = 0u;          // flushed block: zero whatever the nibbles say
   }
-  // E2M1 -> E2M3 by the conversion hardware: every E2M1 number is an E2M3 number (same exponent bias, mantissa m00), so
-  // 16 two-element conversions to bf16 and one 32-element conversion to six-bit codes are exact and yield code = nibble << 2
-  // at bit 6 i of the lane's 192-bit operand -- about a fifth of the vector instructions of spreading the nibbles by hand.
-  union { uint32_t u[16]; img_v32bf v; } c;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    union { uint32_t u; img_v2bf v; } c0, c1, c2, c3;
-    c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 0);
-    c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 1);
-    c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 2);
-    c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], 1.0f, 3);
-    c.u[4 * j] = c0.u; c.u[4 * j + 1] = c1.u; c.u[4 * j + 2] = c2.u; c.u[4 * j + 3] = c3.u;
-  }
-  const img_u32x6 cv = __builtin_amdgcn_cvt_scalef32_pk32_fp6_bf16(c.v, 1.0f);
-  uint32_t d[6] = {cv[0], cv[1], cv[2], cv[3], cv[4], cv[5]};
+  uint32_t d[6];
+  widen_e2m3(n, d);
   if (PLUS) {
     // the BM's code is sign | 11 | mmm (E2M3 at exponent e_max, Sec. 4.2) instead of nibble << 2: the difference of the two
     // is XORed onto the six bits at 6 bm, which may straddle two dwords

@@ -2360,6 +2360,41 @@ def test_gemm_decode_canonical_every_launch_class(M, N, K, w_fmt):
     assert torch.equal(mxp.gemm_decode_bf16a(a, mxp.MXFP4P, qw, code, out_dtype=torch.bfloat16), D.to(torch.bfloat16))
 
 
+CANON = {"mxfp4": mxp.MXFP4, "mxfp4p": mxp.MXFP4P, "mxfp4pp": mxp.MXFP4PP, "mxfp6": mxp.MXFP6, "mxfp6p": mxp.MXFP6P}
+
+
+def any_operand(rows, K, fmt, rng):
+    """Canonical arrays with any code, position and step between the two scales; flushed and NaN blocks among them."""
+    bits = 6 if fmt.startswith("mxfp6") else 4
+    s = rng.integers(118, 137, (rows, K // 32)).astype(np.uint8)
+    s[rng.random(s.shape) < 0.03] = 0
+    if rows > 2:
+        s[2, K // 64] = 255
+    return rng.integers(0, 256, (rows, K * bits // 8)).astype(np.uint8), s, rng.integers(0, 256, (rows, K // 32)).astype(np.uint8)
+
+
+@pytest.mark.parametrize("fa,fb", [(a, b) for a in CANON for b in CANON
+                                   if not ("mxfp4pp" in (a, b) and {a, b} & {"mxfp6", "mxfp6p"}) and (a, b) != ("mxfp4pp", "mxfp4pp")])
+def test_gemm_without_images_every_pair(fa, fb):
+    """The products of one round: tiles of 64 x 64, 128 x 64 and 128 x 128 and their ragged edges, one block of K to several
+    steps with a partial last one, either output type, rows of D at any alignment -- against the de-converted operands."""
+    rng = np.random.default_rng(17)
+    for M, N, K, dt, pad in [(1, 33, 32, torch.float32, 0), (65, 64, 288, torch.bfloat16, 0), (64, 129, 1056, torch.float32, 3),
+                             (129, 4100, 544, torch.bfloat16, 1), (1100, 2500, 288, torch.float32, 0), (1153, 3001, 256, torch.bfloat16, 0)]:
+        qa, qb = q_dev(any_operand(M, K, fa, rng)), q_dev(any_operand(N, K, fb, rng))
+        out = torch.full((M, N + pad), 7.0, dtype=dt, device="cuda")
+        D = mxp.gemm(qa, CANON[fa], qb, CANON[fb], out=out[:, :N])
+        a, b = mxp.dequantize(qa, CANON[fa]).double(), mxp.dequantize(qb, CANON[fb]).double()
+        ref, S = a @ b.t(), a.abs() @ b.abs().t()
+        nan = ref.isnan()
+        what = "%s x %s %dx%dx%d" % (fa, fb, M, N, K)
+        assert (D.isnan() == nan).all(), what
+        err = (D.double() - ref).abs().masked_fill(nan, 0.0)
+        bound = (2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)).masked_fill(nan, 0.0)
+        assert (err <= bound).all(), what
+        assert (out[:, N:] == 7.0).all(), what
+
+
 def test_calls_run_on_the_current_stream():
     """The handle that the binding passes, on the default stream, inside and after a side stream's scope."""
     side = torch.cuda.Stream()
