@@ -9,6 +9,8 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmxp.so")
 PROBE_DIR = os.path.join(HERE, "probe")
 PROBE_LIB = os.path.join(PROBE_DIR, "libmxp_probe.so")      # bench-only measurement aid, not part of the product ABI
+BINDING_SRC = os.path.join(CSRC, "mxp_binding.cpp")
+BINDING_LIB = os.path.join(HERE, "_mxp_binding.so")         # host side of the binding's frequent calls (a Python module)
 SOURCES = ["mxp_quantize.hip", "mxp_convert.hip", "mxp_gemm.hip", "mxp_w4a16.hip", "mxp_bf16.hip", "mxp_wide.hip", "mxp_canon.hip"]
 HEADERS = [os.path.join(CSRC, "mxp_common.h"), os.path.join(CSRC, "mxp_decode.h"), os.path.join(CSRC, "mxp_tile.h"), os.path.join(CSRC, "mxp_prepack_body.h"), os.path.join(ROOT, "include", "mxp.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -22,8 +24,21 @@ def _hipcc():
     return "hipcc"
 
 
+def _binding_command():
+    import sysconfig
+    import torch
+    t = os.path.dirname(torch.__file__)
+    inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
+           sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
+    return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + ["-I" + d for d in inc] +
+            [BINDING_SRC, "-o", BINDING_LIB, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ltorch"])
+
+
 def up_to_date():
     if not os.path.exists(LIB):
+        return False
+    if not os.path.exists(BINDING_LIB) or any(os.path.getmtime(d) > os.path.getmtime(BINDING_LIB) for d in (BINDING_SRC, HEADERS[-1])):
         return False
     t = os.path.getmtime(LIB)
     deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [os.path.abspath(__file__)]
@@ -50,11 +65,12 @@ def build(force: bool = True, verbose: bool = False) -> str:
         procs.append((s, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     pcmd = [_hipcc()] + FLAGS + ["-I" + PROBE_DIR, "-shared", os.path.join(PROBE_DIR, "mxp_probe.hip"), "-o", PROBE_LIB]
     procs.append(("mxp_probe.hip", subprocess.Popen(pcmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    procs.append(("mxp_binding.cpp", subprocess.Popen(_binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for s, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("hipcc failed on %s:\n%s" % (s, out))
+            raise RuntimeError("compilation failed on %s:\n%s" % (s, out))
         if out.strip() and verbose:
             print(out)
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs

@@ -2,7 +2,8 @@
 
 Every function here has the name of the C entry point it calls (minus the `mxp_` prefix).  torch supplies device
 memory and the current stream; nothing is computed in Python and there is no fallback path: if libmxp.so is missing
-or a call fails, an exception is raised.
+or a call fails, an exception is raised.  The frequent calls with nothing but their defaults go through _mxp_binding
+(csrc/mxp_binding.cpp), which makes the same call of the same entry point and returns None for whatever it does not take.
 """
 from __future__ import annotations
 
@@ -25,6 +26,9 @@ EXPORTS = ("mxp_quantize", "mxp_quantize_t", "mxp_quantize_gather", "mxp_dequant
            "mxp_gemm_bf16a", "mxp_gemm_w4a16", "mxp_gemm_w4a16_workspace_bytes", "mxp_gemm_w4a16_ws", "mxp_convert_operands", "mxp_gemm_workspace_size", "mxp_gemm_static", "mxp_gemm_static_capacity", "mxp_status_string", "mxp_version")
 
 _lib = None
+_fast = None                                               # _mxp_binding, loaded with the library
+_FAST_ENTRIES = ("mxp_quantize", "mxp_dequantize", "mxp_gemm", "mxp_gemm_workspace_bytes_fmt", "mxp_gemm_bf16a", "mxp_gemm_bf16a_workspace_bytes",
+                 "mxp_gemm_decode_bf16a", "mxp_gemm_w4a16_ws", "mxp_gemm_w4a16_workspace_bytes")
 
 
 class MxpError(RuntimeError):
@@ -32,8 +36,9 @@ class MxpError(RuntimeError):
 
 
 def lib():
-    """Load libmxp.so once (after torch, so both share one HIP runtime) and declare the signatures."""
-    global _lib
+    """Load libmxp.so once (after torch, so both share one HIP runtime), declare the signatures and hand the entry points'
+    addresses to the binding's native part."""
+    global _lib, _fast
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -105,6 +110,12 @@ def lib():
     for n in ("mxp_quantize", "mxp_quantize_t", "mxp_dequantize", "mxp_prepack", "mxp_quantize_image", "mxp_prepack_e2m1", "mxp_prepack_e4m3", "mxp_gemm", "mxp_gemm_prepacked",
               "mxp_gemm_bf16a", "mxp_gemm_decode", "mxp_gemm_decode_bf16a"):
         getattr(L, n).restype = i32
+    try:
+        from . import _mxp_binding
+    except ImportError as e:
+        raise MxpError("_mxp_binding.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` (%s)" % e) from e
+    _mxp_binding.init(*(C.cast(getattr(L, n), vp).value for n in _FAST_ENTRIES))
+    _fast = _mxp_binding
     _lib = L
     return L
 
@@ -133,6 +144,15 @@ def _stream() -> int:
     return _raw_stream(torch.cuda.current_device())
 
 
+_DTYPE_CODE = {torch.float32: F32, torch.bfloat16: BF16}
+
+
+def _native():
+    if _lib is None:
+        lib()
+    return _fast
+
+
 def _dt(t: torch.Tensor) -> int:
     if t.dtype == torch.float32:
         return F32
@@ -155,6 +175,9 @@ def _p(t):
 
 def quantize(x: torch.Tensor, fmt: int = MXFP4P):
     """x [rows, K] fp32/bf16 on the GPU -> (elems [rows, K*bits/8], scales [rows,K/32], bm_idx [rows,K/32]) uint8."""
+    q = _native().quantize(x, fmt)
+    if q is not None:
+        return q
     _dev2d(x)
     rows, K = x.shape
     ld = x.stride(0) if rows > 1 else max(K, 1)
@@ -202,6 +225,10 @@ def quantize_t(xt: torch.Tensor, fmt: int = MXFP4P):
 
 
 def dequantize(q, fmt: int = MXFP4P, dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None):
+    if out is None:
+        out = _native().dequantize(q, fmt, _DTYPE_CODE.get(dtype))
+        if out is not None:
+            return out
     elems, scales, idx = q
     rows, K = elems.shape[0], elems.shape[1] * 8 // _CODE_BITS.get(fmt, 4)
     if out is None:
@@ -381,6 +408,10 @@ def gemm_workspace_size(M: int, N: int, K: int, fmt_a: int = MXFP4P, fmt_b: int 
 def gemm(qa, fmt_a, qb, fmt_b, out_dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None,
          workspace: torch.Tensor | None = None):
     """D[M,N] = deq(A)[M,K] @ deq(B)[N,K]^T from canonical operands."""
+    if out is None and workspace is None and fmt_a <= MXFP6P and fmt_b <= MXFP6P:
+        out = _native().gemm(qa, qb, fmt_a, fmt_b, _DTYPE_CODE.get(out_dtype))
+        if out is not None:
+            return out
     ae, as_, ai = qa
     be, bs, bi = qb
     M, K = ae.shape[0], as_.shape[1] * 32
@@ -445,6 +476,10 @@ def gemm_decode(M, N, K, a_image, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtyp
 def gemm_decode_bf16a(a: torch.Tensor, fmt_a: int, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype = torch.float32,
                       out: torch.Tensor | None = None, workspace: torch.Tensor | None = None):
     """Un-quantized activations (M <= 64 rows), quantized on the fly, x canonical weights."""
+    if out is None and workspace is None:
+        out = _native().gemm_decode_bf16a(a, qw, fmt_a, fmt_w, _DTYPE_CODE.get(out_dtype))
+        if out is not None:
+            return out
     _dev2d(a)
     we, ws, wi = qw
     M, K = a.shape
@@ -480,6 +515,10 @@ def gemm_w4a16(a: torch.Tensor, qw, fmt_w: int = MXFP4P, out_dtype: torch.dtype 
     otherwise tiles on the bf16 MFMA, the weights de-converted inside the kernel or, with room for them as bf16, once ahead of
     it).  workspace: that room (gemm_w4a16_workspace_bytes, at most 256 MiB), kept by the caller; an empty tensor for none.
     Left out, it is allocated per call where it pays and memory is there."""
+    if out is None and workspace is None:
+        out = _native().gemm_w4a16(a, qw, fmt_w, _DTYPE_CODE.get(out_dtype))
+        if out is not None:
+            return out
     _dev2d(a)
     we, ws, wi = qw
     M, K = a.shape
@@ -504,6 +543,10 @@ def gemm_bf16a_workspace_bytes(M: int, K: int) -> int:
 def gemm_bf16a(a: torch.Tensor, fmt_a, b_image, N: int, out_dtype: torch.dtype = torch.float32,
                out: torch.Tensor | None = None, workspace: torch.Tensor | None = None, b_kind: int = IMAGE_E2M3):
     """Activations quantized on the fly, weights given as a prepacked image (fmt_a MXFP4PP: b_kind IMAGE_E4M3)."""
+    if out is None and workspace is None and fmt_a != MXFP4PP:
+        out = _native().gemm_bf16a(a, b_image, fmt_a, N, _DTYPE_CODE.get(out_dtype), b_kind)
+        if out is not None:
+            return out
     _dev2d(a)
     M, K = a.shape
     if out is None:

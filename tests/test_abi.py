@@ -254,6 +254,24 @@ def test_missing_library_is_an_error_not_a_fallback(monkeypatch):
         mxp.image_bytes(64, 64)
 
 
+def test_native_calls_leave_what_they_do_not_take_to_the_general_code():
+    """Wrong counts and types, CPU tensors, unknown formats: None from the native part, the same exceptions as ever from the call."""
+    import torch
+    n = mxp._native()
+    x = torch.zeros((4, 64))
+    q = tuple(torch.zeros((4, k), dtype=torch.uint8) for k in (32, 2, 2))
+    assert n.quantize(x, mxp.MXFP4P) is None and n.quantize(x) is None and n.quantize(None, 1) is None and n.quantize(x, "1") is None
+    assert n.dequantize(q, mxp.MXFP4P, 0) is None and n.dequantize(list(q), 1, 0) is None and n.dequantize(q, 1, None) is None
+    assert n.gemm(q, q, 1, 1, 0) is None and n.gemm(q, q[:2], 1, 1, 0) is None
+    assert n.gemm_bf16a(x, q[0], 1, 4, 0, 3) is None and n.gemm_decode_bf16a(x, q, 1, 1, 0) is None and n.gemm_w4a16(x, q, 1, 0) is None
+    with pytest.raises(TypeError):
+        n.init(1, 2)
+    with pytest.raises(mxp.MxpError):
+        mxp.quantize(x)
+    with pytest.raises(mxp.MxpError):
+        mxp.gemm_w4a16(x, q)
+
+
 def test_stream_handle_without_torchs_private_name(monkeypatch):
     class Stream:
         cuda_stream = 1234

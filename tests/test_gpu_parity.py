@@ -2395,6 +2395,59 @@ def test_gemm_without_images_every_pair(fa, fb):
         assert (out[:, N:] == 7.0).all(), what
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 33, 256), (13, 300, 512), (130, 70, 288)])
+def test_native_calls_equal_the_general_code(M, N, K, monkeypatch):
+    """Each call that the native part of the binding takes, against the same call through the general code: dense rows, rows of
+    a wider tensor, a single row, both dtypes, formats without index bytes (given as None too); refusals raise the same."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    wide = torch.randn((M, K + 64), generator=gen, device="cuda")
+    w = torch.randn((N, K), generator=gen, device="cuda")
+    qw = {f: mxp.quantize(w, f) for f in (mxp.MXFP4, mxp.MXFP4P, mxp.MXFP4PP, mxp.MXFP6, mxp.MXFP8P)}
+    img = mxp.prepack(qw[mxp.MXFP4P])
+    xs = [wide[:, :K], wide[:, :K].contiguous(), wide.bfloat16()[:, :K], wide.bfloat16()[:, :K].contiguous()]
+
+    def calls():
+        for x in xs:
+            for f, q in qw.items():
+                mine = mxp.quantize(x, f)
+                yield mine if f in (mxp.MXFP4P, mxp.MXFP4PP, mxp.MXFP8P) else mine[:2]
+                for dt in (torch.float32, torch.bfloat16):
+                    yield (mxp.dequantize(mine, f, dt), mxp.gemm(mine, f, q, f, dt))
+                    if x.dtype == torch.bfloat16:
+                        yield (mxp.gemm_w4a16(x, q, f, dt),)
+            yield (mxp.gemm_bf16a(x, mxp.MXFP4P, img, N, torch.bfloat16), mxp.gemm_bf16a(x, mxp.MXFP4, img, N))
+            if M <= 64 and K % 256 == 0:
+                yield (mxp.gemm_decode_bf16a(x, mxp.MXFP4P, qw[mxp.MXFP4P]), mxp.gemm_decode_bf16a(x, mxp.MXFP4, qw[mxp.MXFP4], mxp.MXFP4, torch.bfloat16))
+        e, s, _ = qw[mxp.MXFP4]
+        yield (mxp.gemm(qw[mxp.MXFP4P], mxp.MXFP4P, (e, s, None), mxp.MXFP4), mxp.dequantize((e, s, None), mxp.MXFP4))
+
+    def refusals():
+        return [(mxp.MxpError, lambda: mxp.quantize(wide[:, :40])), (mxp.MxpError, lambda: mxp.quantize(wide[0])), (TypeError, lambda: mxp.quantize(wide.half())),
+                (mxp.MxpError, lambda: mxp.quantize(wide.cpu())), (mxp.MxpError, lambda: mxp.quantize(wide, 11)),
+                (mxp.MxpError, lambda: mxp.gemm(mxp.quantize(wide), 1, qw[mxp.MXFP4P], 1)), (TypeError, lambda: mxp.dequantize(qw[mxp.MXFP4P], 1, torch.float16)),
+                (mxp.MxpError, lambda: mxp.gemm_w4a16(w, qw[mxp.MXFP4P])), (mxp.MxpError, lambda: mxp.gemm_bf16a(wide[:, 1:K + 1], 1, img, N))]
+
+    native = list(calls())
+    for kind, f in refusals():
+        with pytest.raises(kind):
+            f()
+
+    class General:
+        def __getattr__(self, name):
+            return lambda *a: None
+
+    monkeypatch.setattr(mxp, "_fast", General())
+    general = list(calls())
+    for kind, f in refusals():
+        with pytest.raises(kind):
+            f()
+    assert len(native) == len(general)
+    for n, g in zip(native, general):
+        for a, b in zip(n, g):
+            assert a.dtype == b.dtype and a.shape == b.shape and a.stride() == b.stride() and torch.equal(a, b)
+
+
 def test_calls_run_on_the_current_stream():
     """The handle that the binding passes, on the default stream, inside and after a side stream's scope."""
     side = torch.cuda.Stream()
