@@ -11,7 +11,7 @@ PROBE_DIR = os.path.join(HERE, "probe")
 PROBE_LIB = os.path.join(PROBE_DIR, "libmxp_probe.so")      # bench-only measurement aid, not part of the product ABI
 BINDING_SRC = os.path.join(CSRC, "mxp_binding.cpp")
 BINDING_LIB = os.path.join(HERE, "_mxp_binding.so")         # host side of the binding's frequent calls (a Python module)
-SOURCES = ["mxp_quantize.hip", "mxp_convert.hip", "mxp_gemm.hip", "mxp_w4a16.hip", "mxp_bf16.hip", "mxp_wide.hip", "mxp_canon.hip"]
+SOURCES = ["mxp_quantize.hip", "mxp_convert.hip", "mxp_gemm.hip", "mxp_w4a16.hip", "mxp_bf16.hip", "mxp_wide.hip", "mxp_canon.hip", "mxp_few_rows.hip"]
 HEADERS = [os.path.join(CSRC, "mxp_common.h"), os.path.join(CSRC, "mxp_decode.h"), os.path.join(CSRC, "mxp_tile.h"), os.path.join(CSRC, "mxp_prepack_body.h"), os.path.join(ROOT, "include", "mxp.h")]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-function", "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]

@@ -408,9 +408,10 @@ namespace mxp {
 // more rounds the conversions repeat (2048 x 4096 x 4096 MXFP4+ pair 43.5 | 63.5, MXFP4++ x MXFP4+ 62.7 | 68.6).  Not taken either:
 //  - few rows x four-bit weights in whole chunks, beyond a short K: the kernel on canonical weights splits K over its wavefronts
 //    (16 x 4096 x 4096 10.4 | 15.9, x 2048 7.3 | 9.6, x 1024 6.8 | 6.5, x 256 6.6 | 4.2; 16 x 8192 x 1024 6.9 | 8.5);
-//  - long K on a part of the chip with one term on either side: the block kernel of the images walks faster
-//    (3 x 543 x 7264 MXFP4 11.2 | 12.4, 366 x 421 x 7936 MXFP4+ 26.6 | 28.2, but 996 x 474 x 8000 27.0 | 25.3), and two
-//    MXFP4+ operands, both of which are widened, in tiles of 128 x 128 (1024 x 4096 x 4096 31.9 | 33.3);
+//  - long K on a small part of the chip: the kernels of the images split K over their wavefronts (one term on either side: 4 x 278 x 4736
+//    MXFP4+ x MXFP4 9.1 | 12.8, 3 x 461 x 1952 MXFP4+ pair 8.5 | 9.6, 366 x 421 x 7936 26.6 | 28.2, but 996 x 474 x 8000 27.0 | 25.3;
+//    two: 7 x 878 x 12288 MXFP4++ x MXFP4+ 32.2 | 40.0, 8 x 4096 x 4128 28.1 | 16.5), and two MXFP4+ operands, both of which are
+//    widened, in tiles of 128 x 128 (1024 x 4096 x 4096 31.9 | 33.3);
 //  - two MXFP4++ operands, whose product has an FP8 image route with its own error bound that mxp_gemm equals bit for bit, and
 //    MXFP4++ next to a six-bit format, which is multiplied as bf16 in whatever room the workspace gives.
 bool canon_gemm_takes(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB) {
@@ -422,7 +423,8 @@ bool canon_gemm_takes(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB) {
   const int64_t tiles = ((M + 127) / 128) * ((N + 63) / 64);  // of 128 x 64
   if (fmtA == MXP_FMT_MXFP4P && fmtB == MXP_FMT_MXFP4P && tiles > kNumCU && K > 3072) return false;
   const bool two_terms = fmtA == MXP_FMT_MXFP4PP || fmtB == MXP_FMT_MXFP4PP || fmtA == MXP_FMT_MXFP6P || fmtB == MXP_FMT_MXFP6P;
-  return K <= 6144 || two_terms || tiles > 160;
+  if (two_terms) return K <= 6144 || tiles > 32;
+  return K <= (tiles < 16 ? 1536 : 6144) || tiles > 160;
 }
 
 int canon_gemm_launch(int64_t M, int64_t N, int64_t K, const uint8_t* ae, const uint8_t* as, const uint8_t* ai, int fmtA, const uint8_t* be,

@@ -53,6 +53,10 @@ bool canon_gemm_takes(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB);
 int canon_gemm_launch(int64_t M, int64_t N, int64_t K, const uint8_t* ae, const uint8_t* as, const uint8_t* ai, int fmtA, const uint8_t* be,
                       const uint8_t* bs, const uint8_t* bi, int fmtB, void* D, int d_dtype, int64_t ldd, hipStream_t s);
 
+// few rows of bf16 x canonical six- or eight-bit weights (mxp_few_rows.hip): M <= 64, rows of A 16-byte aligned; arguments already checked
+int few_rows_launch(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi, int fmtW,
+                    void* D, int d_dtype, int64_t ldd, hipStream_t s);
+
 // the product of two bf16 matrices in memory (mxp_bf16.hip): rows 16-byte aligned, K a multiple of 32
 bool bf16_gemm_takes(int64_t M, int64_t N, int64_t K, int64_t lda);
 int bf16_gemm_launch(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const void* B, int64_t ldb, void* D, int d_dtype,

@@ -610,7 +610,7 @@ namespace {
 // shapes (1 - 4096 rows, N 200 - 60000, K 256 - 30000, six formats; the estimates are off by 9 and 11 %), and W is de-converted
 // once where that is ahead by a margin.  In the kernel -> once, us, bf16 out:
 //   MXFP4+, 14336 x 4096: 160 rows 88.6 -> 60.5, 1024 131 -> 115, 4096 501 -> 363; 4096 x 14336: 160 rows 296 -> 110, 2048 331 -> 205
-//   MXFP8+, 14336 x 4096:  16 rows 162 -> 58.6, 1024 170 -> 119, 4096 668 -> 374; 4096 x 14336:  16 rows 544 -> 105
+//   MXFP8+, 14336 x 4096: 1024 rows 170 -> 119, 4096 668 -> 374
 // and where it stays in the kernel (column tiles fill the chip, few rows of them repeat the work; W in slabs that do not):
 //   MXFP4+, 28672 x 8192: 129 rows 202 | 265, 512 267 | 347; 28672 x 14336: 512 rows 464 | 880; 14336 x 256: 512 rows 13.6 | 17.3
 // Of the 3700 shapes 13 are slower than in the kernel by more than 3 % (11 % at most), 92 would gain more than 5 % (14 % on average).
@@ -634,8 +634,12 @@ double once_us(int64_t M, int64_t n, int64_t K, int fmtW, bool d_vectors) {     
 // Slabs are whole tiles and as even as that allows.  d_vectors: the rows of D start at 16-byte addresses.
 int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d_vectors, size_t bytes) {
   const bool four = fmtW < MXP_FMT_MXFP6;
-  // four-bit W up to 128 rows has the few-row kernel (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60)
-  if ((four && M <= 128) || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
+  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60), wider W up to 64,
+  // above 32 unless the last round of its workgroups (32 columns, one per compute unit) would be nearly empty (64 rows MXFP8+,
+  // 8695 x 3456 in two rounds 45.2 | 39.1, 14336 x 2048 29.2 | 33.3)
+  const int64_t c32 = (N + 31) / 32, rounds = (c32 + mxp::kNumCU - 1) / mxp::kNumCU;
+  const bool few = four ? M <= 128 : M <= 32 || (M <= 64 && (rounds == 1 || 5 * c32 > 3 * rounds * mxp::kNumCU));
+  if (few || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
   int64_t rows = N, n = 1;
   if (bytes / (2 * (size_t)K) < (size_t)N) {
     rows = (int64_t)(bytes / (2 * (size_t)K)) / 256 * 256;
@@ -697,7 +701,9 @@ extern "C" int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A,
     }
     return MXP_OK;
   }
-  // six- and eight-bit weights: the tiled kernel at any number of rows
+  // six- and eight-bit weights: a kernel of their own up to 64 rows (above, W read twice is no faster than W as bf16: 100 rows x
+  // 4096 x 4096 MXFP8+ 38.3 us), the tiled kernel beyond
+  if (wide_w && M <= 64) return few_rows_launch(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
   if (wide_w) return dispatch_tiled(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
   if (M > 64 && M <= 128) {
     // two passes of the few-row kernel read the weights twice and still beat one row of 256 x 256 tiles here

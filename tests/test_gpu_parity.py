@@ -2395,6 +2395,30 @@ def test_gemm_without_images_every_pair(fa, fb):
         assert (out[:, N:] == 7.0).all(), what
 
 
+@pytest.mark.parametrize("fmt", list(WIDE))
+@pytest.mark.parametrize("M,N,K", [(1, 33, 32), (16, 4096, 288), (17, 65, 1056), (13, 4097, 416), (32, 11201, 160), (9, 11300, 256), (33, 100, 1184), (64, 4130, 544)])
+def test_gemm_w4a16_few_rows_wide_weights(fmt, M, N, K):
+    """Few rows x six- and eight-bit weights of any codes, positions and scales (flushed, NaN and beyond the plain range among
+    them), in every launch shape, with a last step of one to four blocks -- against the values that mxp_dequantize gives."""
+    rng = np.random.default_rng(23)
+    code, bits = WIDE[fmt][0], 6 if fmt.startswith("mxfp6") else 8
+    s = rng.integers(100, 150, (N, K // 32)).astype(np.uint8)
+    s[rng.random(s.shape) < 0.03] = 0
+    s[5 % N, 0], s[7 % N, K // 32 - 1], s[9 % N, 0], s[11 % N, 0] = 3, 255, 241, 15
+    qw = q_dev((rng.integers(0, 256, (N, K * bits // 8)).astype(np.uint8), s, rng.integers(0, 256, s.shape).astype(np.uint8)))
+    a = torch.from_numpy(rng.standard_normal((M, K + 8)).astype(np.float32)).cuda().to(torch.bfloat16)[:, :K]
+    w = mxp.dequantize(qw, code, torch.bfloat16).double()
+    ref, S = a.double() @ w.t(), a.double().abs() @ w.abs().t()
+    nan = ref.isnan()
+    assert nan.any()
+    for dt in (torch.float32, torch.bfloat16):
+        out = torch.full((M, N + 3), 7.0, dtype=dt, device="cuda")
+        D = mxp.gemm_w4a16(a, qw, code, out=out[:, :N])
+        assert (D.isnan() == nan).all() and (out[:, N:] == 7.0).all()
+        bound = 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+        assert ((D.double() - ref).abs() <= bound)[~nan].all()
+
+
 @pytest.mark.parametrize("M,N,K", [(1, 33, 256), (13, 300, 512), (130, 70, 288)])
 def test_native_calls_equal_the_general_code(M, N, K, monkeypatch):
     """Each call that the native part of the binding takes, against the same call through the general code: dense rows, rows of
