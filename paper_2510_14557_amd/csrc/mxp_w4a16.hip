@@ -32,64 +32,69 @@ __device__ __forceinline__ v8bf as_v8bf(const uint32_t (&d)[4]) {
   return c.b;
 }
 
-// ---- few activation rows (M <= 64): one workgroup per 32 weight rows, K split over its wavefronts ------------------
+// ---- few activation rows (M <= 64): one workgroup per 32 CT weight rows, K split over its wavefronts ------------------
 // A 32x32x16 bf16 MFMA operand lane l holds row l % 32 and eight k-slots 8 (l / 32) .. +7.  The sum over k does not care
 // which k sits in which slot as long as both operands agree, so the two lane halves take two different MX blocks: in
 // "super-step" t (64 elements of K) lane (n, h) de-converts block 2t + h of weight row n and feeds its 32 values to four
 // MFMAs, eight at a time; the activation lane (m, h) loads the same eight k per MFMA.  The W operand goes first, so
 // accumulator register r of lane l is D[m = l % 32][n = 8 (r / 4) + 4 (l / 32) + r % 4].
-// A wavefront takes groups of 8 blocks (256 elements of K) of the 32 rows: it reads them the way they lie in memory
+// A wavefront takes groups of 8 blocks (256 elements of K) of 32 rows: it reads them the way they lie in memory
 // (8 lanes per row: 128 contiguous bytes), passes them through a private LDS patch, and picks them up in operand order.
 constexpr int kW4RowStride = 144;                            // 8 blocks x 16 B + 16 B padding against bank conflicts
 constexpr int kW4PatchBytes = 32 * kW4RowStride + 256 + 256; // elements, scale bytes [32][8], index bytes [32][8]
 
 // 32 codes -> 32 bf16 (16 dwords of pairs), Eq. 2.  The unpack-convert instruction runs over the whole block with the
-// NBM scale, the BM is overwritten once, and the reserved scale codes are a select (0: zeros, 255: NaN).  Only when some
-// lane of the wavefront holds a block whose values reach below the bf16 normal range (scale byte - delta < 2) does the
-// wavefront take the general de-conversion, which builds those patterns from integer fields.
+// NBM scale; the BM's code is taken out of the codes first (code 0 converts to +0), and its value, an exponent and mantissa in
+// place, is or-ed onto its pair: put at its place in a group of four pairs first, then one and-or per pair with the group's mask
+// (76 vector instructions; compared with and selected into each pair 110).  Only when some lane of the wavefront holds a
+// block whose values are special (scale byte 0: zeros, 255: NaN) or may leave the bf16 normal range does the wavefront take the
+// general de-conversion, which builds the patterns from integer fields.
 template <int MODE>
 __device__ __forceinline__ void decode_block_bf16(const u32x4 q, uint32_t sbyte, uint32_t ib, uint32_t (&w)[16]) {
-  const uint32_t dw[4] = {q.x, q.y, q.z, q.w};
-  const uint32_t delta = MODE == 2 ? ib >> 5 : 0u;
-  const bool tiny = sbyte != 0u && sbyte < 2u + delta;
-  if (__builtin_amdgcn_ballot_w64(tiny) != 0) {
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      uint32_t out[8];
-      decode_group<(MODE >= 1), true>(dw[s], sbyte, MODE >= 1 ? ib & 31u : 64u, (uint32_t)s, out, delta);
-      w[4 * s] = out[0]; w[4 * s + 1] = out[1]; w[4 * s + 2] = out[2]; w[4 * s + 3] = out[3];
-    }
-    return;
+  uint32_t n[4] = {q.x, q.y, q.z, q.w};
+  const uint32_t delta = MODE == 2 ? ib >> 5 : 0u, idx = ib & 31u;
+  const bool plain = sbyte >= 2u + delta && sbyte <= 250u;
+  uint32_t put = 0;
+  if (MODE >= 1) {
+    const uint32_t upper = (uint32_t)((int32_t)(idx << 27) >> 31), sh = 4u * (idx & 15u);
+    const uint32_t lo = upper ? n[2] : n[0], hi = upper ? n[3] : n[1];
+    const uint32_t nib = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 15u;
+    const uint64_t v = (uint64_t)nib << sh;
+    const uint32_t vl = (uint32_t)v, vh = (uint32_t)(v >> 32);
+    n[0] ^= vl & ~upper; n[1] ^= vh & ~upper; n[2] ^= vl & upper; n[3] ^= vh & upper;
+    put = (((nib & 8u) << 12) | ((sbyte + 2u) << 7) | ((nib & 7u) << 4)) << (16u * (idx & 1u));   // 2^e_max * 1.mmm * X
   }
-  const float X = __uint_as_float((sbyte - delta) << 23);
+  const float X = __uint_as_float((plain ? sbyte - delta : 127u) << 23);
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     union { v2bf v; uint32_t u; } c0, c1, c2, c3;
-    c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dw[j], X, 0);
-    c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dw[j], X, 1);
-    c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dw[j], X, 2);
-    c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(dw[j], X, 3);
+    c0.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], X, 0);
+    c1.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], X, 1);
+    c2.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], X, 2);
+    c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], X, 3);
     w[4 * j] = c0.u; w[4 * j + 1] = c1.u; w[4 * j + 2] = c2.u; w[4 * j + 3] = c3.u;
   }
   if (MODE >= 1) {
-    const uint32_t idx = ib & 31u;
-    const uint32_t qd = idx < 8u ? dw[0] : idx < 16u ? dw[1] : idx < 24u ? dw[2] : dw[3];
-    const uint32_t nib = (qd >> (4u * (idx & 7u))) & 15u;
-    const float XB = __uint_as_float(sbyte << 23);
-    const uint32_t bm = ((nib & 8u) << 12) | (__float_as_uint((float)(8u + (nib & 7u)) * (XB * 0.5f)) >> 16);   // exact: 4 bits
-    const uint32_t sh = (idx & 1u) * 16u;
-    const uint32_t keep = ~(0xFFFFu << sh), put = bm << sh;
+    const bool q0 = (idx & 2u) != 0u, q1 = (idx & 4u) != 0u;
+    const uint32_t a = q1 ? 0u : put, b = q1 ? put : 0u;
+    const uint32_t p[4] = {q0 ? 0u : a, q0 ? a : 0u, q0 ? 0u : b, q0 ? b : 0u};
+    const uint32_t g0 = (uint32_t)((int32_t)(idx << 28) >> 31), g1 = (uint32_t)((int32_t)(idx << 27) >> 31);
+    const uint32_t m[4] = {~g0 & ~g1, g0 & ~g1, ~g0 & g1, g0 & g1};
 #pragma unroll
-    for (int j = 0; j < 16; ++j) w[j] = (idx >> 1) == (uint32_t)j ? (w[j] & keep) | put : w[j];
+    for (int j = 0; j < 16; ++j) w[j] |= p[j & 3] & m[j >> 2];
   }
-  if (sbyte == 0u || sbyte == 255u) {                       // reserved codes: an all-zero block, a block that held NaN / Inf
-    const uint32_t v = sbyte == 0u ? 0u : 0x7FC07FC0u;
+  if (__builtin_amdgcn_ballot_w64(!plain) != 0) {
+#pragma unroll 1
+    for (uint32_t s = 0; s < 4; ++s) {                       // (in one loop: four copies cost the kernels their registers)
+      uint32_t out[8];
+      decode_group<(MODE >= 1), true>(s == 0 ? q.x : s == 1 ? q.y : s == 2 ? q.z : q.w, sbyte, MODE >= 1 ? idx : 64u, s, out, delta);
 #pragma unroll
-    for (int j = 0; j < 16; ++j) w[j] = v;
+      for (int j = 0; j < 16; ++j) w[j] = s == (uint32_t)(j >> 2) ? out[j & 3] : w[j];
+    }
   }
 }
 
-template <int MODE, int TMR, bool OUT_BF16, int WAVES>
+template <int MODE, int TMR, int CT, bool OUT_BF16, int WAVES>
 __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t* __restrict__ A, int64_t lda,
                                                                   const u32x4* __restrict__ w_el, const uint8_t* __restrict__ w_sc,
                                                                   const uint8_t* __restrict__ w_ix, int64_t nbk, int64_t M, int64_t N,
@@ -97,49 +102,53 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
   extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  uint8_t* patch = lds_raw + wave * kW4PatchBytes;          // private to this wavefront (LDS operations of a wavefront run in order)
-  uint8_t* p_sc = patch + 32 * kW4RowStride;
-  uint8_t* p_ix = p_sc + 256;
+  uint8_t* patches = lds_raw + wave * (CT * kW4PatchBytes);  // private to this wavefront (LDS operations of a wavefront run in order)
   const int h = lane >> 5, nl = lane & 31;
-  const int64_t n0 = (int64_t)blockIdx.x * 32;
+  const int64_t n0 = (int64_t)blockIdx.x * (32 * CT);
   const int64_t groups = (nbk + 7) / 8;
   const bool meta_dwords = (nbk & 3) == 0;                  // scale / index bytes of 4 blocks can be read as one dword
-  v16f acc[TMR];
+  v16f acc[TMR][CT];
   const uint16_t* a_row[TMR];
   bool a_ok[TMR];
 #pragma unroll
   for (int i = 0; i < TMR; ++i) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][r] = 0.0f;
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.0f;
     a_ok[i] = 32 * i + nl < M;
     a_row[i] = A + (a_ok[i] ? (int64_t)(32 * i + nl) * lda : 0) + h * 32;
   }
 
-  // loads of one group in memory order: elements, 8 lanes per row; scale and index bytes, 2 lanes per row
-  u32x4 q[4];
-  uint32_t sc4, ix4;
+  // loads of one group in memory order: elements, 8 lanes per row; scale and index bytes, 2 lanes per row.  Absent blocks (rows past
+  // N, whose outputs are not stored; past K, where the activations are zero) are zeros with an ordinary scale byte.
+  u32x4 q[CT][4];
+  uint32_t sc4[CT], ix4[CT];
   auto load_group = [&](int64_t g) {
     const int64_t kb0 = 8 * g;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t n = n0 + 8 * i + (lane >> 3), kb = kb0 + (lane & 7);
-      q[i] = (u32x4){0, 0, 0, 0};
-      if (n < N && kb < nbk) q[i] = __builtin_nontemporal_load(w_el + n * nbk + kb);
-    }
-    sc4 = 0;
-    ix4 = 0;
-    const int64_t n = n0 + (lane >> 1), kb = kb0 + 4 * (lane & 1);
-    if (n < N && kb < nbk) {
-      const int64_t b = n * nbk + kb;
-      if (meta_dwords) {
-        sc4 = *reinterpret_cast<const uint32_t*>(w_sc + b);
-        if (MODE >= 1) ix4 = *reinterpret_cast<const uint32_t*>(w_ix + b);
-      } else {
+    for (int j = 0; j < CT; ++j) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          if (kb + j < nbk) {
-            sc4 |= (uint32_t)w_sc[b + j] << (8 * j);
-            if (MODE >= 1) ix4 |= (uint32_t)w_ix[b + j] << (8 * j);
+      for (int i = 0; i < 4; ++i) {
+        const int64_t n = n0 + 32 * j + 8 * i + (lane >> 3), kb = kb0 + (lane & 7);
+        q[j][i] = (u32x4){0, 0, 0, 0};
+        if (n < N && kb < nbk) q[j][i] = __builtin_nontemporal_load(w_el + n * nbk + kb);
+      }
+      sc4[j] = 0x7F7F7F7Fu;
+      ix4[j] = 0;
+      const int64_t n = n0 + 32 * j + (lane >> 1), kb = kb0 + 4 * (lane & 1);
+      if (n < N && kb < nbk) {
+        const int64_t b = n * nbk + kb;
+        if (meta_dwords) {
+          sc4[j] = *reinterpret_cast<const uint32_t*>(w_sc + b);
+          if (MODE >= 1) ix4[j] = *reinterpret_cast<const uint32_t*>(w_ix + b);
+        } else {
+#pragma unroll
+          for (int t = 0; t < 4; ++t) {
+            if (kb + t < nbk) {
+              sc4[j] = (sc4[j] & ~(0xFFu << (8 * t))) | (uint32_t)w_sc[b + t] << (8 * t);
+              if (MODE >= 1) ix4[j] |= (uint32_t)w_ix[b + t] << (8 * t);
+            }
           }
         }
       }
@@ -148,12 +157,16 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
   if (wave < groups) load_group(wave);
   for (int64_t g = wave; g < groups; g += WAVES) {
     const int64_t kb0 = 8 * g;
-    // ---- through the patch into operand order
+    // ---- through the patches into operand order
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<u32x4*>(patch + (8 * i + (lane >> 3)) * kW4RowStride + (lane & 7) * 16) = q[i];
-    *reinterpret_cast<uint32_t*>(p_sc + (lane >> 1) * 8 + 4 * (lane & 1)) = sc4;
-    if (MODE >= 1) *reinterpret_cast<uint32_t*>(p_ix + (lane >> 1) * 8 + 4 * (lane & 1)) = ix4;
+    for (int j = 0; j < CT; ++j) {
+      uint8_t* patch = patches + j * kW4PatchBytes;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<u32x4*>(patch + (8 * i + (lane >> 3)) * kW4RowStride + (lane & 7) * 16) = q[j][i];
+      *reinterpret_cast<uint32_t*>(patch + 32 * kW4RowStride + (lane >> 1) * 8 + 4 * (lane & 1)) = sc4[j];
+      if (MODE >= 1) *reinterpret_cast<uint32_t*>(patch + 32 * kW4RowStride + 256 + (lane >> 1) * 8 + 4 * (lane & 1)) = ix4[j];
+    }
     if (g + WAVES < groups) load_group(g + WAVES);          // the next group's loads fly while this one is multiplied
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -170,37 +183,43 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
           if (ok) a[i][s] = *reinterpret_cast<const u32x4*>(ap + 8 * s);
         }
       }
-      const u32x4 qq = *reinterpret_cast<const u32x4*>(patch + nl * kW4RowStride + bl * 16);
-      const uint32_t sb = p_sc[nl * 8 + bl];
-      const uint32_t ib = MODE >= 1 ? (uint32_t)p_ix[nl * 8 + bl] : 0u;
-      uint32_t w[16];
-      decode_block_bf16<MODE>(qq, sb, ib, w);               // blocks past K or N were loaded as zeros with scale byte 0
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const uint32_t w4[4] = {w[4 * s], w[4 * s + 1], w[4 * s + 2], w[4 * s + 3]};
-        const v8bf wv = as_v8bf(w4);
+      for (int j = 0; j < CT; ++j) {
+        const uint8_t *patch = patches + j * kW4PatchBytes, *p_sc = patch + 32 * kW4RowStride;
+        const u32x4 qq = *reinterpret_cast<const u32x4*>(patch + nl * kW4RowStride + bl * 16);
+        const uint32_t sb = p_sc[nl * 8 + bl];
+        const uint32_t ib = MODE >= 1 ? (uint32_t)p_sc[256 + nl * 8 + bl] : 0u;
+        uint32_t w[16];
+        decode_block_bf16<MODE>(qq, sb, ib, w);
 #pragma unroll
-        for (int i = 0; i < TMR; ++i) {
-          const uint32_t a4[4] = {a[i][s].x, a[i][s].y, a[i][s].z, a[i][s].w};
-          acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, as_v8bf(a4), acc[i], 0, 0, 0);
+        for (int s = 0; s < 4; ++s) {
+          const uint32_t w4[4] = {w[4 * s], w[4 * s + 1], w[4 * s + 2], w[4 * s + 3]};
+          const v8bf wv = as_v8bf(w4);
+#pragma unroll
+          for (int i = 0; i < TMR; ++i) {
+            const uint32_t a4[4] = {a[i][s].x, a[i][s].y, a[i][s].z, a[i][s].w};
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wv, as_v8bf(a4), acc[i][j], 0, 0, 0);
+          }
         }
       }
     }
   }
   __syncthreads();                                          // the patches are dead: the same LDS now collects the partial tiles
-  float (*part)[TMR][16][64] = reinterpret_cast<float (*)[TMR][16][64]>(lds_raw);
+  float (*part)[TMR * CT][16][64] = reinterpret_cast<float (*)[TMR * CT][16][64]>(lds_raw);
 #pragma unroll
   for (int i = 0; i < TMR; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) part[wave][i][r][lane] = acc[i][r];
+    for (int j = 0; j < CT; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) part[wave][i * CT + j][r][lane] = acc[i][j][r];
   __syncthreads();
-  for (int e = tid; e < TMR * 16 * 64; e += 64 * WAVES) {
-    const int l = e & 63, r = (e >> 6) & 15, i = e >> 10;
+  for (int e = tid; e < TMR * CT * 16 * 64; e += 64 * WAVES) {
+    const int l = e & 63, r = (e >> 6) & 15, ij = e >> 10, i = ij / CT, j = ij % CT;
     float v = 0.0f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) v += part[w][i][r][l];
+    for (int w = 0; w < WAVES; ++w) v += part[w][ij][r][l];
     const int64_t row = 32 * i + (l & 31);
-    const int64_t col = n0 + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
+    const int64_t col = n0 + 32 * j + 8 * (r >> 2) + 4 * (l >> 5) + (r & 3);
     if (row < M && col < N) {
       if (OUT_BF16) static_cast<uint16_t*>(Dv)[row * ldd + col] = (uint16_t)f32_to_bf16_rne_bits(v);
       else static_cast<float*>(Dv)[row * ldd + col] = v;
@@ -208,34 +227,42 @@ __global__ void __launch_bounds__(64 * WAVES) w4a16_skinny_kernel(const uint16_t
   }
 }
 
-template <int MODE, int TMR, bool OUT_BF16>
-void launch_skinny(dim3 grid, hipStream_t s, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi,
-                   int64_t nbk, int64_t M, int64_t N, void* D, int64_t ldd) {
-  // two row tiles need more than the 128 registers a lane gets with 16 wavefronts (the compiler spilled ~90): 8 then
-  constexpr int WAVES = TMR == 1 ? 16 : 8;
-  constexpr int lds_part = WAVES * TMR * 16 * 64 * 4, lds_patch = WAVES * kW4PatchBytes;
+template <int MODE, int TMR, int CT, bool OUT_BF16, int WAVES>
+void launch_skinny(hipStream_t s, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi, int64_t nbk, int64_t M,
+                   int64_t N, void* D, int64_t ldd) {
+  constexpr int lds_part = WAVES * TMR * CT * 16 * 64 * 4, lds_patch = WAVES * CT * kW4PatchBytes;
   constexpr int lds = lds_part > lds_patch ? lds_part : lds_patch;
   static_assert(lds <= 160 * 1024, "LDS");
-  allow_dynamic_lds<&w4a16_skinny_kernel<MODE, TMR, OUT_BF16, WAVES>>((int)lds);
-  hipLaunchKernelGGL((w4a16_skinny_kernel<MODE, TMR, OUT_BF16, WAVES>), grid, dim3(64 * WAVES), lds, s,
+  allow_dynamic_lds<&w4a16_skinny_kernel<MODE, TMR, CT, OUT_BF16, WAVES>>((int)lds);
+  hipLaunchKernelGGL((w4a16_skinny_kernel<MODE, TMR, CT, OUT_BF16, WAVES>), dim3((unsigned)((N + 32 * CT - 1) / (32 * CT))), dim3(64 * WAVES), lds, s,
                      static_cast<const uint16_t*>(A), lda, reinterpret_cast<const u32x4*>(we), ws, wi, nbk, M, N, D, ldd);
 }
 
 template <int MODE>
 int dispatch_skinny(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws,
                     const uint8_t* wi, void* D, int d_dtype, int64_t ldd, hipStream_t s) {
-  const int64_t ct = (N + 31) / 32;
+  const int64_t ct = (N + 31) / 32, nbk = K / kBlock;
   if (ct > 2147483647LL) return MXP_ERR_UNSUPPORTED;
-  const dim3 grid((unsigned)ct);
-  const int64_t nbk = K / kBlock;
-  const bool bf = d_dtype == MXP_BF16;
-  if (M <= 32) {
-    if (bf) launch_skinny<MODE, 1, true>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-    else launch_skinny<MODE, 1, false>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+#define MXP_SKINNY(TMR, CT, WAVES)                                                                                  \
+  do {                                                                                                              \
+    if (d_dtype == MXP_BF16) launch_skinny<MODE, TMR, CT, true, WAVES>(s, A, lda, we, ws, wi, nbk, M, N, D, ldd);   \
+    else launch_skinny<MODE, TMR, CT, false, WAVES>(s, A, lda, we, ws, wi, nbk, M, N, D, ldd);                      \
+  } while (0)
+  // What bounds this kernel is the reads of A (every workgroup reads all of it) and the vector instructions of the conversion, at the same
+  // time: 13 x 28672 x 8192 MXFP4+ 64 us, 49 without the reads, 62 without the conversion, 32 without either.  Two column tiles share
+  // the reads from the 257th tile on (us, one tile of sixteen wavefronts -> here: 32 x 10000 x 4096 24.1 -> 17.0, 13 x 14336 x 4096 19.0 ->
+  // 16.0 and MXFP4 17.0 -> 12.9, 64 x 14336 x 4096 41.0 -> 26.5); up to 256 tiles they would leave compute units idle (8 x 4096 x 4096 8.1 |
+  // 13.7), and up to 8 rows one tile of eight wavefronts is ahead (4 x 10000 x 4096 16.2 -> 13.8 | 14.8 with two, x 1024 9.2 -> 5.8 | 6.3).
+  const bool one_round = ct <= kNumCU;
+  if (M > 32) {
+    if (one_round) MXP_SKINNY(2, 1, 8);                      // (sixteen wavefronts would spill)
+    else MXP_SKINNY(2, 2, 8);
   } else {
-    if (bf) launch_skinny<MODE, 2, true>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
-    else launch_skinny<MODE, 2, false>(grid, s, A, lda, we, ws, wi, nbk, M, N, D, ldd);
+    if (one_round) MXP_SKINNY(1, 1, 16);
+    else if (M <= 8) MXP_SKINNY(1, 1, 8);
+    else MXP_SKINNY(1, 2, 8);
   }
+#undef MXP_SKINNY
   return launch_status();
 }
 
@@ -634,7 +661,7 @@ double once_us(int64_t M, int64_t n, int64_t K, int fmtW, bool d_vectors) {     
 // Slabs are whole tiles and as even as that allows.  d_vectors: the rows of D start at 16-byte addresses.
 int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d_vectors, size_t bytes) {
   const bool four = fmtW < MXP_FMT_MXFP6;
-  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 18.6 / 40.5 us against 60), wider W up to 64,
+  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 16 / 26.5 us against 60), wider W up to 64,
   // above 32 unless the last round of its workgroups (32 columns, one per compute unit) would be nearly empty (64 rows MXFP8+,
   // 8695 x 3456 in two rounds 45.2 | 39.1, 14336 x 2048 29.2 | 33.3)
   const int64_t c32 = (N + 31) / 32, rounds = (c32 + mxp::kNumCU - 1) / mxp::kNumCU;

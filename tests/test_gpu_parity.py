@@ -2395,6 +2395,32 @@ def test_gemm_without_images_every_pair(fa, fb):
         assert (out[:, N:] == 7.0).all(), what
 
 
+@pytest.mark.parametrize("fmt", list(FMT))
+@pytest.mark.parametrize("M,N,K", [(32, 8192, 288), (8, 8193, 320), (9, 8225, 2080), (32, 8300, 96), (33, 8192, 160), (64, 8257, 2336)])
+def test_gemm_w4a16_few_rows_launch_shapes(fmt, M, N, K):
+    """Few rows on either side of one round of column tiles: one or two tiles and eight or sixteen wavefronts a workgroup, weights of
+    any code, position and step, scales at both ends of what the unpack-convert instructions take, flushed and NaN blocks."""
+    rng = np.random.default_rng(29)
+    e, s, i = any_operand(N, K, fmt, rng)
+    s[5, 0], s[6, K // 32 - 1], s[7, 0], s[8, 0], s[9, 0] = 1, 2, 8, 9, 3
+    s[10, 0], s[11, 0] = 250, 251
+    if fmt == "mxfp4pp":
+        i[5:10] &= 31                                                  # (no step below the smallest scale)
+        i[7:9] |= 7 << 5
+    qw = q_dev((e, s, i))
+    # activations below 6 * 2^-12: a block of scale 251 sums to less than 32 * 7.5 * 2^124 * 6 * 2^-12 < 2^123, inside fp32
+    a = (torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda().clamp(-6, 6) * 2.0 ** -12).to(torch.bfloat16)
+    w = mxp.dequantize(qw, CANON[fmt], torch.bfloat16).double()
+    ref, S = a.double() @ w.t(), a.double().abs() @ w.abs().t()
+    nan = ref.isnan()
+    assert nan.any()
+    for dt in (torch.float32, torch.bfloat16):
+        D = mxp.gemm_w4a16(a, qw, CANON[fmt], dt)
+        assert (D.isnan() == nan).all()
+        bound = 2.0 ** -16 * S + 1e-37 + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+        assert ((D.double() - ref).abs() <= bound)[~nan].all()
+
+
 @pytest.mark.parametrize("fmt", list(WIDE))
 @pytest.mark.parametrize("M,N,K", [(1, 33, 32), (16, 4096, 288), (17, 65, 1056), (13, 4097, 416), (32, 11201, 160), (9, 11300, 256), (33, 100, 1184), (64, 4130, 544)])
 def test_gemm_w4a16_few_rows_wide_weights(fmt, M, N, K):
