@@ -357,8 +357,8 @@ __global__ void __launch_bounds__(64 * (4 + PW)) canon_tiled_kernel(CanonOperand
   }
   uint8_t* patch = lds + wave * (2 * kPatchBytes);           // the stages are idle
   const int64_t tm = m0 / 32 + wm * WI, tn = n0 / 32 + wn * WJ;
-  if (d_bf16) store_tile_lds<WI, WJ, true, false>(acc, tm, tn, (int)lane, A.rows, B.rows, Dv, ldd, patch);
-  else store_tile_lds<WI, WJ, false, false>(acc, tm, tn, (int)lane, A.rows, B.rows, Dv, ldd, patch);
+  if (d_bf16) store_tile_lds<WI, WJ, true, false, true>(acc, tm, tn, (int)lane, A.rows, B.rows, Dv, ldd, patch);
+  else store_tile_lds<WI, WJ, false, false, true>(acc, tm, tn, (int)lane, A.rows, B.rows, Dv, ldd, patch);
 }
 
 template <int FA, int FB, int PW, int WI, int WJ>

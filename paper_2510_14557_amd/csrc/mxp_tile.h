@@ -24,10 +24,11 @@ __device__ __forceinline__ uint32_t f32_to_bf16_rne(float v) { return pack_bf16x
 // conflicts; LDS operations of one wavefront execute in order, so no wait is needed between the write and the read)
 // and comes back with 8 consecutive lanes holding the 128 contiguous bytes of one row: every store instruction
 // writes 8 full lines.  `patch` is this wavefront's scratch, two patches of kPatchBytes.  STREAM: streaming stores.
+// COLUMNS: a lane per column where rows of D do not start at 16-byte addresses.
 constexpr int kPatchStride = 144;                 // bytes per patch row: 32 floats + 16
 constexpr int kPatchBytes = 32 * kPatchStride;
 
-template <int TWM, int TWN, bool OUT_BF16, bool STREAM = true>
+template <int TWM, int TWN, bool OUT_BF16, bool STREAM = true, bool COLUMNS = false>
 __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int64_t tile_m, int64_t tile_n, int lane, int64_t M,
                                                int64_t N, void* __restrict__ Dv, int64_t ldd, uint8_t* patch) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -83,9 +84,9 @@ __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int6
         f32x4 q = {acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
         *reinterpret_cast<f32x4*>(pb + wr + 32 * g) = q;
       }
-      if (!vec_ok) {
-        // rows of D anywhere: a lane per column, so that a store instruction covers two whole rows of the tile
-        // (2048 x 4097 x 4096 to fp32 43.6 -> 42.3 us)
+      if (COLUMNS && !vec_ok) {
+        // rows of D anywhere: a lane per column, so that a store instruction covers two whole rows of the tile.
+        // (Not in the large kernels, whose loops lose registers to it: the 4096 x 14336 x 4096 step 172 | 181 us.)
         const int64_t col = (tile_n + j) * 32 + (lane & 31);
 #pragma unroll
         for (int k = 0; k < 16; ++k) {
@@ -103,7 +104,7 @@ __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int6
         const f32x4 v = *reinterpret_cast<const f32x4*>(pb + rd + 8 * k * kPatchStride);
         const int64_t row = (tile_m + i) * 32 + 8 * k + (lane >> 3);
         if (row >= M || col >= N) continue;
-        if (col + 3 < N) {
+        if (vec_ok && col + 3 < N) {
           if (OUT_BF16) {
             u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
             put(reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col), o);
