@@ -184,20 +184,6 @@ __device__ __forceinline__ void store_k_split(v16f (&acc)[TMR][CT], uint8_t* blo
   }
   __syncthreads();
   const bool vec_ok = (ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(Dv) & 15u) == 0);
-  if (!vec_ok) {
-    // rows of D anywhere: a lane per column, so that a store instruction still covers 256 (128) contiguous bytes
-    for (int e = tid; e < ROWS * COLS; e += 256) {
-      const int r = e / COLS, c = e % COLS;
-      float v = part[r * STRIDE + c];
-#pragma unroll
-      for (int w = 1; w < PARTS; ++w) v += part[(w * ROWS + r) * STRIDE + c];
-      const int64_t row = rt0 * 32 + r, col = ct0 * 32 + c;
-      if (row >= M || col >= N) continue;
-      if (out_bf16) static_cast<uint16_t*>(Dv)[row * ldd + col] = (uint16_t)f32_to_bf16_rne(v);
-      else static_cast<float*>(Dv)[row * ldd + col] = v;
-    }
-    return;
-  }
   constexpr int QUADS = COLS / 4;                                           // 16-byte pieces per row
   for (int e = tid; e < ROWS * QUADS; e += 256) {
     const int r = e / QUADS, q = e % QUADS;
@@ -206,7 +192,7 @@ __device__ __forceinline__ void store_k_split(v16f (&acc)[TMR][CT], uint8_t* blo
     for (int w = 1; w < PARTS; ++w) v += *reinterpret_cast<const f32x4*>(part + ((size_t)w * ROWS + r) * STRIDE + 4 * q);
     const int64_t row = rt0 * 32 + r, col = ct0 * 32 + 4 * q;
     if (row >= M || col >= N) continue;
-    if (col + 3 < N) {
+    if (vec_ok && col + 3 < N) {
       if (out_bf16) {
         const u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
         __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
