@@ -2395,6 +2395,26 @@ def test_gemm_without_images_every_pair(fa, fb):
         assert (out[:, N:] == 7.0).all(), what
 
 
+@pytest.mark.parametrize("fa,fb", [("mxfp4p", "mxfp4p"), ("mxfp4p", "mxfp4"), ("mxfp4", "mxfp4")])
+@pytest.mark.parametrize("M,N,K", [(150, 300, 256), (520, 1700, 320), (1100, 2500, 192)])
+def test_block_kernel_on_images(fa, fb, M, N, K):
+    """Images of one round of blocks (64 x 64, 128 x 64, 128 x 128), which mxp_gemm itself multiplies without images."""
+    rng = np.random.default_rng(31)
+    qa, qb = q_dev(any_operand(M, K, fa, rng)), q_dev(any_operand(N, K, fb, rng))
+    plain_a, plain_b = fa == "mxfp4", fb == "mxfp4"
+    ia = mxp.prepack_e2m1(qa) if plain_a else mxp.prepack(qa, CANON[fa])
+    ib = mxp.prepack_e2m1(qb) if plain_b else mxp.prepack(qb, CANON[fb])
+    a, b = mxp.dequantize(qa, CANON[fa]).double(), mxp.dequantize(qb, CANON[fb]).double()
+    ref, S = a @ b.t(), a.abs() @ b.abs().t()
+    nan = ref.isnan()
+    for dt in (torch.float32, torch.bfloat16):
+        D = mxp.gemm_prepacked(M, N, K, ia, ib, dt, a_kind=mxp.IMAGE_E2M1 if plain_a else mxp.IMAGE_E2M3,
+                               b_kind=mxp.IMAGE_E2M1 if plain_b else mxp.IMAGE_E2M3)
+        assert (D.isnan() == nan).all()
+        bound = 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+        assert ((D.double() - ref).abs() <= bound)[~nan].all()
+
+
 @pytest.mark.parametrize("fmt", list(FMT))
 @pytest.mark.parametrize("M,N,K", [(32, 8192, 288), (8, 8193, 320), (9, 8225, 2080), (32, 8300, 96), (33, 8192, 160), (64, 8257, 2336)])
 def test_gemm_w4a16_few_rows_launch_shapes(fmt, M, N, K):
@@ -2422,7 +2442,7 @@ def test_gemm_w4a16_few_rows_launch_shapes(fmt, M, N, K):
 
 
 @pytest.mark.parametrize("fmt", list(WIDE))
-@pytest.mark.parametrize("M,N,K", [(1, 33, 32), (16, 4096, 288), (17, 65, 1056), (13, 4097, 416), (32, 11201, 160), (9, 11300, 256), (33, 100, 1184), (64, 4130, 544)])
+@pytest.mark.parametrize("M,N,K", [(1, 33, 32), (16, 4096, 288), (17, 65, 1056), (13, 4097, 416), (32, 11201, 160), (9, 11300, 256), (20, 4200, 288), (33, 100, 1184), (64, 4130, 544)])
 def test_gemm_w4a16_few_rows_wide_weights(fmt, M, N, K):
     """Few rows x six- and eight-bit weights of any codes, positions and scales (flushed, NaN and beyond the plain range among
     them), in every launch shape, with a last step of one to four blocks -- against the values that mxp_dequantize gives."""
