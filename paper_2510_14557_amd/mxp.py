@@ -408,7 +408,9 @@ def gemm_workspace_size(M: int, N: int, K: int, fmt_a: int = MXFP4P, fmt_b: int 
 def gemm(qa, fmt_a, qb, fmt_b, out_dtype: torch.dtype = torch.float32, out: torch.Tensor | None = None,
          workspace: torch.Tensor | None = None):
     """D[M,N] = deq(A)[M,K] @ deq(B)[N,K]^T from canonical operands."""
-    if out is None and workspace is None and fmt_a <= MXFP6P and fmt_b <= MXFP6P:
+    # pairs that are multiplied as bf16: the room for both operands is optional (A alone, or neither, also does)
+    as_bf16 = fmt_a > MXFP6P or fmt_b > MXFP6P or (fmt_a == MXFP4PP and fmt_b >= MXFP6) or (fmt_b == MXFP4PP and fmt_a >= MXFP6)
+    if out is None and workspace is None and not as_bf16:
         out = _native().gemm(qa, qb, fmt_a, fmt_b, _DTYPE_CODE.get(out_dtype))
         if out is not None:
             return out
@@ -422,9 +424,8 @@ def gemm(qa, fmt_a, qb, fmt_b, out_dtype: torch.dtype = torch.float32, out: torc
         out = torch.empty((M, N), dtype=out_dtype, device=ae.device)
     if workspace is None:
         nbytes = max(gemm_workspace_bytes(M, N, K, fmt_a, fmt_b), 16)
-        pair = (fmt_a, fmt_b)
-        if max(pair) >= MXFP8 or (MXFP4PP in pair and max(pair) >= MXFP6):
-            workspace = _optional_workspace(nbytes, ae.device)   # both operands as bf16; A alone, or neither, also does
+        if as_bf16:
+            workspace = _optional_workspace(nbytes, ae.device)
             nbytes = 2 * M * K
         if workspace is None:
             workspace = torch.empty(max(nbytes, 16), dtype=torch.uint8, device=ae.device)

@@ -2525,3 +2525,28 @@ def test_calls_run_on_the_current_stream():
     with torch.cuda.stream(side):
         assert mxp._stream() == side.cuda_stream
     assert mxp._stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+
+
+@pytest.mark.parametrize("fa,fb", [(mxp.MXFP4PP, mxp.MXFP6P), (mxp.MXFP6, mxp.MXFP4PP), (mxp.MXFP8P, mxp.MXFP4P)])
+def test_gemm_of_deconverted_operands_where_memory_is_short(fa, fb):
+    """The room for both operands as bf16 is optional: where the device cannot give it, the product runs in the room for A (above
+    128 rows to the same bits)."""
+    M, N, K = 2048, 16384, 4096
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(41)
+    qa = mxp.quantize(torch.randn((M, K), generator=gen, device="cuda"), fa)
+    qb = mxp.quantize(torch.randn((N, K), generator=gen, device="cuda"), fb)
+    need, room, result = mxp.gemm_workspace_bytes(M, N, K, fa, fb), 2 * M * K, 2 * M * N
+    assert need >= room + (128 << 20)
+    want = mxp.gemm(qa, fa, qb, fb, torch.bfloat16)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    total = torch.cuda.get_device_properties(0).total_memory
+    torch.cuda.set_per_process_memory_fraction((torch.cuda.memory_reserved() + result + room + (40 << 20)) / total)
+    try:
+        with pytest.raises(torch.cuda.OutOfMemoryError):
+            torch.empty(result + need, dtype=torch.uint8, device="cuda")
+        got = mxp.gemm(qa, fa, qb, fb, torch.bfloat16)
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert torch.equal(got, want)
