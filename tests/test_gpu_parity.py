@@ -2550,3 +2550,39 @@ def test_gemm_of_deconverted_operands_where_memory_is_short(fa, fb):
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert torch.equal(got, want)
+
+
+def us_per_call(call, n=20):
+    """Median over nine replays of a graph of n calls."""
+    call()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        for _ in range(n):
+            call()
+    times = []
+    for _ in range(10):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        g.replay()
+        end.record()
+        end.synchronize()
+        times.append(start.elapsed_time(end) * 1e3 / n)
+    return sorted(times[1:])[4]
+
+
+@pytest.mark.parametrize("fmt", list(FMT))
+def test_few_rows_times_do_not_depend_on_flushed_blocks(fmt):
+    """Few rows x weights with many all-zero blocks (pruned or padded ones) take about as long as without: the wavefronts that meet one
+    stay on the ordinary way (the general one would make these calls 2 to 6 times as long)."""
+    M, N, K = 8, 12288, 4096
+    code = {n: c for n, (c, _) in {**FMT, **WIDE}.items()}[fmt]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(43)
+    a = torch.randn((M, K), generator=gen, device="cuda").bfloat16()
+    w = torch.randn((N, K), generator=gen, device="cuda").bfloat16()
+    holes = w.view(N, K // 32, 32).clone()
+    holes[torch.rand((N, K // 32), generator=gen, device="cuda") < 0.1] = 0
+    out = torch.empty((M, N), device="cuda")
+    t = [us_per_call(lambda q=mxp.quantize(x, code): mxp.gemm_w4a16(a, q, code, out=out)) for x in (w, holes.view(N, K))]
+    assert t[1] <= 1.5 * t[0], t
