@@ -2571,7 +2571,7 @@ def us_per_call(call, n=20):
     return sorted(times[1:])[4]
 
 
-@pytest.mark.parametrize("fmt", list(FMT))
+@pytest.mark.parametrize("fmt", list(FMT) + list(WIDE))
 def test_few_rows_times_do_not_depend_on_flushed_blocks(fmt):
     """Few rows x weights with many all-zero blocks (pruned or padded ones) take about as long as without: the wavefronts that meet one
     stay on the ordinary way (the general one would make these calls 2 to 6 times as long)."""
