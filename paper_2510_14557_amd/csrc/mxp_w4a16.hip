@@ -254,16 +254,21 @@ int dispatch_skinny(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
   } while (0)
   // What bounds this kernel is the reads of A (every workgroup reads all of it) and the vector instructions of the conversion, at the same
   // time: 13 x 28672 x 8192 MXFP4+ 64 us, 49 without the reads, 62 without the conversion, 32 without either.  Two column tiles share
-  // the reads from the 257th tile on (us, one tile of sixteen wavefronts -> here: 32 x 10000 x 4096 24.1 -> 17.0, 13 x 14336 x 4096 19.0 ->
-  // 16.0 and MXFP4 17.0 -> 12.9, 64 x 14336 x 4096 41.0 -> 26.5); up to 256 tiles they would leave compute units idle (8 x 4096 x 4096 8.1 |
+  // the reads from the 257th tile on (us, one tile of sixteen wavefronts -> here: 32 x 10000 x 4096 24.1 -> 17.0, 13 x 14336 x 4096 17.1 ->
+  // 14.8 and MXFP4 17.0 -> 12.9, 64 x 14336 x 4096 41.0 -> 26.5); up to 256 tiles they would leave compute units idle (8 x 4096 x 4096 8.1 |
   // 13.7), and up to 8 rows one tile of eight wavefronts is ahead (4 x 10000 x 4096 16.2 -> 13.8 | 14.8 with two, x 1024 9.2 -> 5.8 | 6.3).
+  // So it is where the last round of pairs of tiles would be nearly empty, up to 2^16 values of A (11 x 18389 x 4512 MXFP4+ 32.0 with one
+  // of sixteen, 41.0 with two; 9 - 32 rows, 459 shapes of 513 - 768 tiles, geometric means against one of sixteen 0.78 with one of
+  // eight, 1.03 with two); above that sixteen are (158 shapes, 1.01 and 1.11).
+  const int64_t pairs = (ct + 1) / 2;
   const bool one_round = ct <= kNumCU;
+  const bool last_empty = (pairs > kNumCU && 2 * pairs <= 3 * kNumCU) || (pairs > 2 * kNumCU && 4 * pairs <= 9 * kNumCU);
   if (M > 32) {
     if (one_round) MXP_SKINNY(2, 1, 8);                      // (sixteen wavefronts would spill)
     else MXP_SKINNY(2, 2, 8);
   } else {
-    if (one_round) MXP_SKINNY(1, 1, 16);
-    else if (M <= 8) MXP_SKINNY(1, 1, 8);
+    if (one_round || (last_empty && M * K > 65536)) MXP_SKINNY(1, 1, 16);
+    else if (M <= 8 || last_empty) MXP_SKINNY(1, 1, 8);
     else MXP_SKINNY(1, 2, 8);
   }
 #undef MXP_SKINNY

@@ -2586,3 +2586,20 @@ def test_few_rows_times_do_not_depend_on_flushed_blocks(fmt):
     out = torch.empty((M, N), device="cuda")
     t = [us_per_call(lambda q=mxp.quantize(x, code): mxp.gemm_w4a16(a, q, code, out=out)) for x in (w, holes.view(N, K))]
     assert t[1] <= 1.5 * t[0], t
+
+
+@pytest.mark.parametrize("fmt", list(FMT))
+@pytest.mark.parametrize("M,N,K", [(9, 16385, 160), (32, 24576, 96), (32, 16400, 2080), (11, 32769, 288), (8, 18000, 8224), (20, 24577, 64), (9, 36865, 64)])
+def test_gemm_w4a16_few_rows_last_round_nearly_empty(fmt, M, N, K):
+    """Few rows on either side of the numbers of column tiles whose pairs leave the last round of workgroups nearly empty."""
+    rng = np.random.default_rng(47)
+    qw = q_dev(any_operand(N, K, fmt, rng))
+    a = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda().to(torch.bfloat16)
+    w = mxp.dequantize(qw, CANON[fmt], torch.bfloat16).double()
+    ref, S = a.double() @ w.t(), a.double().abs() @ w.abs().t()
+    nan = ref.isnan()
+    for dt in (torch.float32, torch.bfloat16):
+        D = mxp.gemm_w4a16(a, qw, CANON[fmt], dt)
+        assert (D.isnan() == nan).all()
+        bound = 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+        assert ((D.double() - ref).abs() <= bound)[~nan].all()
