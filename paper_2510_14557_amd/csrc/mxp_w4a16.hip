@@ -666,16 +666,35 @@ double once_us(int64_t M, int64_t n, int64_t K, int fmtW, bool d_vectors) {     
   return 10.0 + bytes * (double)n * (double)K / 5e6 + (double)K * walk * 1e-3 + (double)M * n / 1.75e6 + (d_vectors ? 0.0 : (double)M * n / 1.05e6);
 }
 
+// Six- and eight-bit W next to 33 to 64 rows: rounds of the few-row kernel's workgroups (32 columns, one per compute unit), and the
+// workgroups of the last one.
+struct FewRounds {
+  int64_t rounds, last;
+  explicit FewRounds(int64_t N) : rounds(((N + 31) / 32 + mxp::kNumCU - 1) / mxp::kNumCU), last((N + 31) / 32 - (rounds - 1) * mxp::kNumCU) {}
+};
+// Where W as bf16 is ahead of that kernel: many of those rows, its last round up to two fifths full, and K between what a second launch
+// and pass over W cost and what the last-level cache holds of it (us, few-row kernel | W once: MXFP6+ 57 x 8950 x 7424 92.2 | 73.1,
+// 52 x 18895 x 3968 73.1 | 60.7, but MXFP6 58 x 8526 x 320 8.9 | 12.0; over 17000 shapes of 4096 - 32768 columns this choice is 0.4 % behind
+// the better of the two, the kernel alone 0.7 %, W once below three fifths of a second round 8 %).
+bool once_beats_few_rows(int64_t M, int64_t N, int64_t K, int fmtW) {
+  const FewRounds r(N);
+  const bool plus = fmtW == MXP_FMT_MXFP6P || fmtW == MXP_FMT_MXFP8P;
+  return M > (plus ? 44 : 52) && r.rounds >= 2 && 5 * r.last <= 2 * mxp::kNumCU && K * (r.rounds - 1) >= 3072 && K * r.rounds <= 16384;
+}
+// Where the tiled kernel is: three and more rounds of it, each a step or two of K that one of its eight wavefronts takes (MXFP6+
+// 50 x 24923 x 64 16.3 | 10.4, x 128 at 24600 - 32768 columns a fifth slower; at 192 the same).
+bool tiles_beat_few_rows(int64_t M, int64_t N, int64_t K) {
+  const FewRounds r(N);
+  return M > 32 && K <= 192 && K <= 64 * (r.rounds - 2);
+}
+
 // Rows of W that are de-converted at a time, given room for so many bytes of them; 0: de-conversion stays in the kernel.
 // Slabs are whole tiles and as even as that allows.  d_vectors: the rows of D start at 16-byte addresses.
 int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d_vectors, size_t bytes) {
   const bool four = fmtW < MXP_FMT_MXFP6;
-  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 16 / 26.5 us against 60), wider W up to 64,
-  // above 32 unless the last round of its workgroups (32 columns, one per compute unit) would be nearly empty (64 rows MXFP8+,
-  // 8695 x 3456 in two rounds 45.2 | 39.1, 14336 x 2048 29.2 | 33.3)
-  const int64_t c32 = (N + 31) / 32, rounds = (c32 + mxp::kNumCU - 1) / mxp::kNumCU;
-  const bool few = four ? M <= 128 : M <= 32 || (M <= 64 && (rounds == 1 || 5 * c32 > 3 * rounds * mxp::kNumCU));
-  if (few || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
+  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 16 / 26.5 us against 60), wider W up to 64
+  if ((four && M <= 128) || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
+  if (!four && M <= 64) return once_beats_few_rows(M, N, K, fmtW) && bytes / (2 * (size_t)K) >= (size_t)N ? N : 0;
   int64_t rows = N, n = 1;
   if (bytes / (2 * (size_t)K) < (size_t)N) {
     rows = (int64_t)(bytes / (2 * (size_t)K)) / 256 * 256;
@@ -738,8 +757,9 @@ extern "C" int mxp_gemm_w4a16_ws(int64_t M, int64_t N, int64_t K, const void* A,
     return MXP_OK;
   }
   // six- and eight-bit weights: a kernel of their own up to 64 rows (above, W read twice is no faster than W as bf16: 100 rows x
-  // 4096 x 4096 MXFP8+ 38.3 us), the tiled kernel beyond
-  if (wide_w && M <= 64) return few_rows_launch(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
+  // 4096 x 4096 MXFP8+ 38.3 us), the tiled kernel beyond and for many columns of the shortest K
+  if (wide_w && M <= 64 && !tiles_beat_few_rows(M, N, K))
+    return few_rows_launch(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
   if (wide_w) return dispatch_tiled(M, N, K, A, lda, W_elems, W_scales, W_idx, fmtW, D, d_dtype, ldd, s);
   if (M > 64 && M <= 128) {
     // two passes of the few-row kernel read the weights twice and still beat one row of 256 x 256 tiles here

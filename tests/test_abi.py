@@ -298,6 +298,19 @@ def test_room_for_deconverted_weights_is_bounded_and_whole_tiles(fmt):
     assert mxp.gemm_w4a16_workspace_bytes(4096, 256, (1 << 21) + 32, fmt) == 0          # longer than a product takes
 
 
+@pytest.mark.parametrize("fmt", [mxp.MXFP6, mxp.MXFP6P, mxp.MXFP8, mxp.MXFP8P])
+def test_room_for_weights_next_to_33_to_64_rows(fmt):
+    """Six- and eight-bit weights are de-converted ahead of 33 to 64 rows only where that is ahead of the few-row kernel: many rows, a
+    last round of its workgroups that is nearly empty, K in between, all of W in the room."""
+    need = lambda M, N, K: mxp.gemm_w4a16_workspace_bytes(M, N, K, fmt)
+    for N, K in ((9000, 4096), (8193, 7680), (18895, 3968), (25000, 1536)):
+        assert need(64, N, K) == (2 * N * K + 255) // 256 * 256
+        assert need(32, N, K) == need(33, N, K) == 0
+    for N, K in ((9000, 512), (9000, 2048), (9000, 12288), (9000, 30000), (8192, 4096), (14336, 4096), (18895, 1024), (18895, 8192), (300, 4096)):
+        for M in (1, 33, 48, 64):
+            assert need(M, N, K) == 0, (M, N, K)
+
+
 def kernel_metadata(path):
     """The kernels' metadata maps (ELF notes "AMDGPU", type 32) of every code object inside a built library."""
     msgpack = pytest.importorskip("msgpack")

@@ -2603,3 +2603,27 @@ def test_gemm_w4a16_few_rows_last_round_nearly_empty(fmt, M, N, K):
         assert (D.isnan() == nan).all()
         bound = 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
         assert ((D.double() - ref).abs() <= bound)[~nan].all()
+
+
+@pytest.mark.parametrize("fmt", list(WIDE))
+@pytest.mark.parametrize("M,N,K", [(33, 16385, 64), (64, 16384, 64), (50, 24577, 128), (40, 24600, 160), (64, 8225, 3104), (64, 8225, 3040), (53, 17000, 1536)])
+def test_gemm_w4a16_33_to_64_rows_routes(fmt, M, N, K):
+    """33 to 64 rows x six- and eight-bit weights on either side of where the few-row kernel gives way, to tiles (the shortest K) and to
+    weights de-converted ahead; half the room for those is none."""
+    rng = np.random.default_rng(53)
+    code, bits = WIDE[fmt][0], 6 if fmt.startswith("mxfp6") else 8
+    s = rng.integers(100, 150, (N, K // 32)).astype(np.uint8)
+    s[rng.random(s.shape) < 0.03] = 0
+    s[5, 0], s[7, K // 32 - 1], s[9, 0] = 3, 255, 241
+    qw = q_dev((rng.integers(0, 256, (N, K * bits // 8)).astype(np.uint8), s, rng.integers(0, 256, s.shape).astype(np.uint8)))
+    a = torch.from_numpy(rng.standard_normal((M, K)).astype(np.float32)).cuda().to(torch.bfloat16)
+    w = mxp.dequantize(qw, code, torch.bfloat16).double()
+    ref, S = a.double() @ w.t(), a.double().abs() @ w.abs().t()
+    nan = ref.isnan()
+    need = mxp.gemm_w4a16_workspace_bytes(M, N, K, code)
+    runs = [(need, need > 0), (need // 2, False)]
+    for room, use in runs:
+        D, used = w4a16_in(room, a, qw, code, torch.float32)
+        assert used == use
+        assert (D.isnan() == nan).all()
+        assert ((D.double() - ref).abs() <= 2.0 ** -16 * S)[~nan].all()
