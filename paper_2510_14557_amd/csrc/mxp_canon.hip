@@ -377,12 +377,17 @@ int launch_canon_shape(const CanonOperand& A, const CanonOperand& B, int64_t K, 
   return launch_status();
 }
 
+// Tiles of the workgroups: 64 x 64 while that is one round of the chip, then 128 x 64, and 128 x 128 where either takes two full
+// rounds.  A workgroup takes as long as its tile is large (us, 128 x 128 | 128 x 64 | 64 x 64: 40 x 15641 x 4096 MXFP4++ x MXFP4+
+// 31.4 | 23.5 | 18.4 in 245 tiles of 64 x 64, 437 x 3847 x 4288 35.2 | 28.0 | 35.2 in 427 of them, 242 x 11225 x 3936
+// 37.2 | 48.4 | 49.6 in 704), but 257 to 512 of 64 x 64 are ahead of two rounds of 128 x 64 (216 shapes, against the best of the three
+// 1.20 | 1.46 | 1.00).  Over 35500 shapes of all pairs 0.2 % behind the best.
 template <int FA, int FB>
 int launch_canon_pair(const CanonOperand& A, const CanonOperand& B, int64_t K, void* D, bool bf, int64_t ldd, hipStream_t s) {
-  const int64_t rg128 = (A.rows + 127) / 128, cg64 = (B.rows + 63) / 64;
-  if (rg128 * cg64 > kNumCU) return launch_canon_shape<FA, FB, 8, 2, 2>(A, B, K, D, bf, ldd, s);
-  if (rg128 * cg64 >= kNumCU / 2) return launch_canon_shape<FA, FB, 8, 2, 1>(A, B, K, D, bf, ldd, s);
-  return launch_canon_shape<FA, FB, 8, 1, 1>(A, B, K, D, bf, ldd, s);
+  const int64_t cg64 = (B.rows + 63) / 64, t64 = (A.rows + 63) / 64 * cg64, t128 = (A.rows + 127) / 128 * cg64;
+  if (t64 <= kNumCU || (t128 > kNumCU && t64 <= 2 * kNumCU)) return launch_canon_shape<FA, FB, 8, 1, 1>(A, B, K, D, bf, ldd, s);
+  if (t128 <= kNumCU) return launch_canon_shape<FA, FB, 8, 2, 1>(A, B, K, D, bf, ldd, s);
+  return launch_canon_shape<FA, FB, 8, 2, 2>(A, B, K, D, bf, ldd, s);
 }
 
 template <int FA>

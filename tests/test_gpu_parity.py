@@ -2627,3 +2627,50 @@ def test_gemm_w4a16_33_to_64_rows_routes(fmt, M, N, K):
         assert used == use
         assert (D.isnan() == nan).all()
         assert ((D.double() - ref).abs() <= 2.0 ** -16 * S)[~nan].all()
+
+
+NO_IMAGES = [(a, b) for a in CANON for b in CANON
+             if not ("mxfp4pp" in (a, b) and {a, b} & {"mxfp6", "mxfp6p"}) and (a, b) != ("mxfp4pp", "mxfp4pp")]
+
+
+def close_to_deconverted(D, qa, fa, qb, fb, dt):
+    """D against the product of the de-converted operands in 64 bits."""
+    a, b = mxp.dequantize(qa, CANON[fa]).double(), mxp.dequantize(qb, CANON[fb]).double()
+    ref, S = a @ b.t(), a.abs() @ b.abs().t()
+    nan = ref.isnan()
+    if not (D.isnan() == nan).all():
+        return False
+    bound = 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+    return bool(((D.double() - ref).abs() <= bound)[~nan].all())
+
+
+@pytest.mark.parametrize("fa,fb", NO_IMAGES)
+@pytest.mark.parametrize("M,N,K,dt", [(64, 16384, 96, torch.bfloat16), (300, 3300, 288, torch.float32), (1025, 1921, 96, torch.float32), (129, 8321, 160, torch.bfloat16),
+                                      (200, 16350, 96, torch.float32)])
+def test_gemm_without_images_every_tile_shape(fa, fb, M, N, K, dt):
+    """Numbers of tiles on either side of where 64 x 64 ones give way to 128 x 64 and 128 x 128."""
+    rng = np.random.default_rng(59)
+    qa, qb = q_dev(any_operand(M, K, fa, rng)), q_dev(any_operand(N, K, fb, rng))
+    assert close_to_deconverted(mxp.gemm(qa, CANON[fa], qb, CANON[fb], dt), qa, fa, qb, fb, dt)
+
+
+@pytest.mark.parametrize("fa,fb", NO_IMAGES)
+def test_gemm_without_images_scales_at_both_ends(fa, fb):
+    """Scale bytes from 1 on next to ones up to 251 (7.5 * 2^124 is still finite), either way round, and MXFP4++ steps as large as the
+    scale byte and larger, which count as one less than it."""
+    rng = np.random.default_rng(61)
+    for M, N, K, low_a in [(70, 200, 544, True), (200, 70, 544, False)]:
+        qs = []
+        for rows, f, low in ((M, fa, low_a), (N, fb, not low_a)):
+            e, s, i = any_operand(rows, K, f, rng)
+            s = rng.integers(1, 10, s.shape).astype(np.uint8) if low else rng.integers(240, 252, s.shape).astype(np.uint8)
+            s[1, 1], s[2, 2] = 0, 255
+            qs.append((e, s, i))
+        dev = [q_dev(q) for q in qs]
+        counted = []
+        for (e, s, i), f in zip(qs, (fa, fb)):
+            step = np.minimum(i >> 5, np.maximum(s, 1) - 1)
+            counted.append(q_dev((e, s, (i & 31) | (step << 5).astype(np.uint8) if f == "mxfp4pp" else i)))
+        D = mxp.gemm(dev[0], CANON[fa], dev[1], CANON[fb])
+        assert D.isfinite().any()
+        assert close_to_deconverted(D, counted[0], fa, counted[1], fb, torch.float32)
