@@ -409,14 +409,19 @@ int launch_canon_a(int fmtB, const CanonOperand& A, const CanonOperand& B, int64
 namespace mxp {
 // Which products go without images: those of one round of 128 x 128 tiles (us per call, replayed from a graph, images -> without:
 // MXFP4++ x MXFP4+ 1037 x 3001 x 4128 54.2 -> 40.0, 512 x 4096 x 4096 40.2 -> 26.1, 8 x 4096 x 4128 28.1 -> 16.5; MXFP6+ pair
-// 200 x 1000 x 4096 44.2 -> 19.2; MXFP4+ pair 16 x 256 x 256 6.5 -> 4.2; geometric mean of 300 sizes over all pairs 1.8).  With
-// more rounds the conversions repeat (2048 x 4096 x 4096 MXFP4+ pair 43.5 | 63.5, MXFP4++ x MXFP4+ 62.7 | 68.6).  Not taken either:
-//  - few rows x four-bit weights in whole chunks, beyond a short K: the kernel on canonical weights splits K over its wavefronts
-//    (16 x 4096 x 4096 10.4 | 15.9, x 2048 7.3 | 9.6, x 1024 6.8 | 6.5, x 256 6.6 | 4.2; 16 x 8192 x 1024 6.9 | 8.5);
-//  - long K on a small part of the chip: the kernels of the images split K over their wavefronts (one term on either side: 4 x 278 x 4736
-//    MXFP4+ x MXFP4 9.1 | 12.8, 3 x 461 x 1952 MXFP4+ pair 8.5 | 9.6, 366 x 421 x 7936 26.6 | 28.2, but 996 x 474 x 8000 27.0 | 25.3;
-//    two: 7 x 878 x 12288 MXFP4++ x MXFP4+ 32.2 | 40.0, 8 x 4096 x 4128 28.1 | 16.5), and two MXFP4+ operands, both of which are
-//    widened, in tiles of 128 x 128 (1024 x 4096 x 4096 31.9 | 33.3);
+// 200 x 1000 x 4096 44.2 -> 19.2; MXFP4+ pair 16 x 256 x 256 6.5 -> 4.2).  With more rounds the conversions repeat (2048 x 4096 x 4096
+// MXFP4+ pair 43.5 | 63.5, MXFP4++ x MXFP4+ 62.7 | 68.6).  The lines below come from both sides' times at 42500 shapes of all pairs
+// (1 - 4096 rows, 64 - 16384 columns, K 64 - 16384); of 34950 that they take 43 are slower than through images by more than 3 %,
+// 13 % at most.  Not taken:
+//  - few rows x four-bit weights in whole chunks beyond a short K: the kernel on canonical weights splits K over its wavefronts
+//    (without images / that, geometric means up to 4096 columns, 1 - 32 rows: K = 256 0.70, 1024 0.89, 1536 1.01, 2048 1.17; 33 - 64
+//    rows: 256 0.65, 1024 0.84, 2048 1.07);
+//  - few rows x few columns of long K, and long K on a small part of the chip: the kernels of the images split K too (us, images | without:
+//    MXFP4+ x MXFP4 4 x 278 x 4736 9.1 | 12.8, 366 x 421 x 7936 26.6 | 28.2, but 996 x 474 x 8000 27.0 | 25.3; MXFP4++ x MXFP4+
+//    7 x 878 x 12288 32.2 | 40.0, 8 x 165 x 6016 18.1 | 22.4; MXFP6 x MXFP6+ 4 x 163 x 5984 15.7 | 19.7; MXFP6 x MXFP4+
+//    2 x 1622 x 6080 14.9 | 19.0).  Two terms on both sides, or codes that go in as they are, pay up to a longer K;
+//  - two MXFP4+ operands, both of which are widened, beyond a shorter K still (1 x 1075 x 5792 12.8 | 21.7, 13 x 1112 x 4256 12.3 | 17.0,
+//    1575 x 828 x 14688 53.5 | 75.2), in tiles of 128 x 128 beyond 3072 (1024 x 4096 x 4096 31.9 | 33.3);
 //  - two MXFP4++ operands, whose product has an FP8 image route with its own error bound that mxp_gemm equals bit for bit, and
 //    MXFP4++ next to a six-bit format, which is multiplied as bf16 in whatever room the workspace gives.
 bool canon_gemm_takes(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB) {
@@ -424,11 +429,22 @@ bool canon_gemm_takes(int64_t M, int64_t N, int64_t K, int fmtA, int fmtB) {
   if (fmtA == MXP_FMT_MXFP4PP ? fmtB >= MXP_FMT_MXFP4PP : fmtB == MXP_FMT_MXFP4PP && fmtA >= MXP_FMT_MXFP4PP) return false;
   if (((M + 127) / 128) * ((N + 127) / 128) > kNumCU) return false;
   const bool four_a = fmtA <= MXP_FMT_MXFP4P, four_b = fmtB <= MXP_FMT_MXFP4P;
-  if (M <= 64 && four_a && four_b && K % 256 == 0 && (fmtB == MXP_FMT_MXFP4P || fmtA != fmtB)) return K <= (N <= 4096 || M > 32 ? 1024 : 256);
+  if (M <= 64 && four_a && four_b && K % 256 == 0 && (fmtB == MXP_FMT_MXFP4P || fmtA != fmtB)) return K <= 1024;
   const int64_t tiles = ((M + 127) / 128) * ((N + 63) / 64);  // of 128 x 64
-  if (fmtA == MXP_FMT_MXFP4P && fmtB == MXP_FMT_MXFP4P && tiles > kNumCU && K > 3072) return false;
-  const bool two_terms = fmtA == MXP_FMT_MXFP4PP || fmtB == MXP_FMT_MXFP4PP || fmtA == MXP_FMT_MXFP6P || fmtB == MXP_FMT_MXFP6P;
-  if (two_terms) return K <= 6144 || tiles > 32;
+  const bool a_two = fmtA == MXP_FMT_MXFP4PP || fmtA == MXP_FMT_MXFP6P, b_two = fmtB == MXP_FMT_MXFP4PP || fmtB == MXP_FMT_MXFP6P;
+  if (a_two || b_two) {
+    const bool widened = (a_two != b_two) && fmtA != MXP_FMT_MXFP4 && fmtB != MXP_FMT_MXFP4;
+    if (widened && M <= 32 && tiles < 16) return K <= 3584;
+    return K <= 6144 || tiles > 32;
+  }
+  if (fmtA == MXP_FMT_MXFP4P && fmtB == MXP_FMT_MXFP4P) {
+    if (tiles > kNumCU) return K <= 3072;
+    if (tiles > 160) return K <= 9216;
+    return K <= (tiles < (M <= 64 ? 64 : 16) ? 1536 : tiles < 32 ? 4096 : 6144);
+  }
+  const bool codes = fmtA != MXP_FMT_MXFP4P && fmtB != MXP_FMT_MXFP4P && (fmtA == MXP_FMT_MXFP4 || fmtB == MXP_FMT_MXFP4);
+  if (!codes && tiles > 160) return K <= 9216;
+  if (!codes && M <= 32 && tiles >= 16 && tiles < 32) return K <= 2560;
   return K <= (tiles < 16 ? 1536 : 6144) || tiles > 160;
 }
 

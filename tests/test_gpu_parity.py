@@ -2674,3 +2674,28 @@ def test_gemm_without_images_scales_at_both_ends(fa, fb):
         D = mxp.gemm(dev[0], CANON[fa], dev[1], CANON[fb])
         assert D.isfinite().any()
         assert close_to_deconverted(D, counted[0], fa, counted[1], fb, torch.float32)
+
+
+def gemm_in_marked_room(qa, fa, qb, fb, dt=torch.float32):
+    """mxp_gemm in a marked workspace, and whether it was written to."""
+    M, N, K = qa[0].shape[0], qb[0].shape[0], qa[1].shape[1] * 32
+    ws = torch.full((mxp.gemm_workspace_bytes(M, N, K, CANON[fa], CANON[fb]),), 0xA5, dtype=torch.uint8, device="cuda")
+    D = mxp.gemm(qa, CANON[fa], qb, CANON[fb], dt, workspace=ws)
+    return D, bool((ws != 0xA5).any())
+
+
+@pytest.mark.parametrize("fa,fb,M,N,K,images", [
+    ("mxfp4p", "mxfp4p", 13, 1112, 4256, True), ("mxfp4p", "mxfp4p", 64, 4000, 1568, True), ("mxfp4p", "mxfp4p", 64, 4000, 1504, False),
+    ("mxfp4p", "mxfp4p", 65, 1200, 4128, True), ("mxfp4p", "mxfp4p", 65, 1200, 4064, False), ("mxfp4p", "mxfp4p", 764, 1771, 9248, True),
+    ("mxfp4p", "mxfp4p", 764, 1771, 9184, False), ("mxfp4p", "mxfp4p", 1400, 2500, 3104, True), ("mxfp6", "mxfp4p", 2, 1622, 2592, True),
+    ("mxfp6", "mxfp4p", 2, 1622, 2528, False), ("mxfp4p", "mxfp6", 745, 1868, 9248, True), ("mxfp4p", "mxfp6", 745, 1868, 9184, False),
+    ("mxfp6", "mxfp6p", 4, 163, 3616, True), ("mxfp6", "mxfp6p", 4, 163, 3552, False), ("mxfp4pp", "mxfp4p", 8, 165, 3616, True),
+    ("mxfp4p", "mxfp4pp", 8, 165, 3616, True), ("mxfp4pp", "mxfp4", 8, 165, 3616, False), ("mxfp6p", "mxfp6p", 4, 163, 3616, False),
+    ("mxfp4p", "mxfp4", 16, 300, 1024, False), ("mxfp4p", "mxfp4", 16, 300, 1280, True)])
+def test_gemm_with_and_without_images_lines_of_the_choice(fa, fb, M, N, K, images):
+    """Few rows, or a small part of the chip, by long K: the side of the line that the product is on, and its result."""
+    rng = np.random.default_rng(67)
+    qa, qb = q_dev(any_operand(M, K, fa, rng)), q_dev(any_operand(N, K, fb, rng))
+    for dt in (torch.float32, torch.bfloat16):
+        D, used = gemm_in_marked_room(qa, fa, qb, fb, dt)
+        assert used == images and close_to_deconverted(D, qa, fa, qb, fb, dt)
