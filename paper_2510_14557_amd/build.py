@@ -31,22 +31,37 @@ def _binding_command():
     inc = [os.path.join(t, "include"), os.path.join(t, "include", "torch", "csrc", "api", "include"), "/opt/rocm/include",
            sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
     return ([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
-             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)] + ["-I" + d for d in inc] +
+             "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), '-DMXP_TORCH_VERSION="%s"' % torch.__version__] +
+            ["-I" + d for d in inc] +
             [BINDING_SRC, "-o", BINDING_LIB, "-L" + os.path.join(t, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-ltorch"])
 
 
+def _newer(target, deps):
+    return os.path.exists(target) and all(os.path.getmtime(d) <= os.path.getmtime(target) for d in deps)
+
+
 def up_to_date():
-    if not os.path.exists(LIB):
-        return False
-    if not os.path.exists(BINDING_LIB) or any(os.path.getmtime(d) > os.path.getmtime(BINDING_LIB) for d in (BINDING_SRC, HEADERS[-1])):
-        return False
-    t = os.path.getmtime(LIB)
-    deps = [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [os.path.abspath(__file__)]
-    if not os.path.exists(PROBE_LIB):
-        return False
-    tp = os.path.getmtime(PROBE_LIB)
-    pdeps = [os.path.join(PROBE_DIR, f) for f in ("mxp_probe.hip", "mxp_probe.h")] + HEADERS
-    return all(os.path.getmtime(d) <= t for d in deps) and all(os.path.getmtime(d) <= tp for d in pdeps)
+    """The libraries and the binding's native part, the latter also against torch."""
+    import torch
+    torch_version = os.path.join(os.path.dirname(torch.__file__), "version.py")
+    return (_newer(LIB, [os.path.join(CSRC, s) for s in SOURCES] + HEADERS + [os.path.abspath(__file__)]) and
+            _newer(PROBE_LIB, [os.path.join(PROBE_DIR, f) for f in ("mxp_probe.hip", "mxp_probe.h")] + HEADERS) and
+            _newer(BINDING_LIB, [BINDING_SRC, HEADERS[-1], torch_version]))
+
+
+def build_binding():
+    """Compile the binding's native part.  The package works without it, with more host time per call: a machine that cannot compile it
+    (no host compiler, no headers of torch or Python) gets a warning, and no file that another torch left."""
+    import warnings
+    if os.path.exists(BINDING_LIB):
+        os.remove(BINDING_LIB)
+    try:
+        p = subprocess.run(_binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        failed, why = p.returncode != 0, p.stdout
+    except OSError as e:
+        failed, why = True, str(e)
+    if failed:
+        warnings.warn("_mxp_binding.so was not built, calls will take the slower general code:\n" + why, RuntimeWarning)
 
 
 def build(force: bool = True, verbose: bool = False) -> str:
@@ -65,12 +80,12 @@ def build(force: bool = True, verbose: bool = False) -> str:
         procs.append((s, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     pcmd = [_hipcc()] + FLAGS + ["-I" + PROBE_DIR, "-shared", os.path.join(PROBE_DIR, "mxp_probe.hip"), "-o", PROBE_LIB]
     procs.append(("mxp_probe.hip", subprocess.Popen(pcmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
-    procs.append(("mxp_binding.cpp", subprocess.Popen(_binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
+    build_binding()                                          # (beside the compilations above)
     for s, p in procs:
         out, _ = p.communicate()
         out = "\n".join(l for l in out.splitlines() if "packed-fp32-ops" not in l)
         if p.returncode != 0:
-            raise RuntimeError("compilation failed on %s:\n%s" % (s, out))
+            raise RuntimeError("hipcc failed on %s:\n%s" % (s, out))
         if out.strip() and verbose:
             print(out)
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs

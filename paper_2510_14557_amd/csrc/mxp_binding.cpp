@@ -217,4 +217,8 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_mxp_binding", nullptr, -1, method
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__mxp_binding() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__mxp_binding() {
+  PyObject* m = PyModule_Create(&module);
+  if (m && PyModule_AddStringConstant(m, "torch_version", MXP_TORCH_VERSION) != 0) Py_CLEAR(m);   // of the headers it was compiled with
+  return m;
+}

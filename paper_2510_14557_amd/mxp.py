@@ -3,12 +3,14 @@
 Every function here has the name of the C entry point it calls (minus the `mxp_` prefix).  torch supplies device
 memory and the current stream; nothing is computed in Python and there is no fallback path: if libmxp.so is missing
 or a call fails, an exception is raised.  The frequent calls with nothing but their defaults go through _mxp_binding
-(csrc/mxp_binding.cpp), which makes the same call of the same entry point and returns None for whatever it does not take.
+(csrc/mxp_binding.cpp), which makes the same call of the same entry point and returns None for whatever it does not take;
+where that module is missing or was built against another torch, a warning says so and every call takes the general code.
 """
 from __future__ import annotations
 
 import ctypes as C
 import os
+import warnings
 
 import torch
 
@@ -26,7 +28,7 @@ EXPORTS = ("mxp_quantize", "mxp_quantize_t", "mxp_quantize_gather", "mxp_dequant
            "mxp_gemm_bf16a", "mxp_gemm_w4a16", "mxp_gemm_w4a16_workspace_bytes", "mxp_gemm_w4a16_ws", "mxp_convert_operands", "mxp_gemm_workspace_size", "mxp_gemm_static", "mxp_gemm_static_capacity", "mxp_status_string", "mxp_version")
 
 _lib = None
-_fast = None                                               # _mxp_binding, loaded with the library
+_fast = None                                               # _mxp_binding or _NoNative, loaded with the library
 _FAST_ENTRIES = ("mxp_quantize", "mxp_dequantize", "mxp_gemm", "mxp_gemm_workspace_bytes_fmt", "mxp_gemm_bf16a", "mxp_gemm_bf16a_workspace_bytes",
                  "mxp_gemm_decode_bf16a", "mxp_gemm_w4a16_ws", "mxp_gemm_w4a16_workspace_bytes")
 
@@ -110,14 +112,32 @@ def lib():
     for n in ("mxp_quantize", "mxp_quantize_t", "mxp_dequantize", "mxp_prepack", "mxp_quantize_image", "mxp_prepack_e2m1", "mxp_prepack_e4m3", "mxp_gemm", "mxp_gemm_prepacked",
               "mxp_gemm_bf16a", "mxp_gemm_decode", "mxp_gemm_decode_bf16a"):
         getattr(L, n).restype = i32
-    try:
-        from . import _mxp_binding
-    except ImportError as e:
-        raise MxpError("_mxp_binding.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` (%s)" % e) from e
-    _mxp_binding.init(*(C.cast(getattr(L, n), vp).value for n in _FAST_ENTRIES))
-    _fast = _mxp_binding
+    _fast = _load_native(L)
     _lib = L
     return L
+
+
+class _NoNative:
+    """In the place of _mxp_binding: takes no call, which leaves each to the general code."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(L):
+    """The binding's native part, given the library's entry points.  It is tied to the torch that it was compiled against; without
+    a fitting one the same calls of the library are made from Python (2 to 7 us more each)."""
+    try:
+        from . import _mxp_binding as native
+        built_for = getattr(native, "torch_version", None)
+        if built_for != torch.__version__:
+            raise ImportError("compiled against torch %s, this is %s" % (built_for, torch.__version__))
+    except ImportError as e:
+        warnings.warn("_mxp_binding.so cannot be used (%s): calls take the slower general code; `python -c 'import __graft_entry__ as g; "
+                      "g.build()'` builds it" % e, RuntimeWarning, stacklevel=3)
+        return _NoNative()
+    native.init(*(C.cast(getattr(L, n), C.c_void_p).value for n in _FAST_ENTRIES))
+    return native
 
 
 def status_string(rc: int) -> str:

@@ -272,6 +272,60 @@ def test_native_calls_leave_what_they_do_not_take_to_the_general_code():
         mxp.gemm_w4a16(x, q)
 
 
+@pytest.mark.parametrize("other", ["missing", "another torch"])
+def test_library_without_a_fitting_native_part(monkeypatch, other):
+    """The binding's native part is a second binary tied to one torch: without it, or with one for another torch, the library is there
+    all the same and every call takes the general code."""
+    import sys
+    import types
+    import paper_2510_14557_amd as package
+    name = package.__name__ + "._mxp_binding"
+    stand_in = types.ModuleType(name)
+    stand_in.torch_version = "0.0.1"
+    stand_in.init = lambda *a: pytest.fail("entered")
+    monkeypatch.delattr(package, "_mxp_binding", raising=False)
+    monkeypatch.setitem(sys.modules, name, None if other == "missing" else stand_in)
+    monkeypatch.setattr(mxp, "_lib", None)
+    monkeypatch.setattr(mxp, "_fast", None)
+    with pytest.warns(RuntimeWarning, match="_mxp_binding"):
+        assert mxp.image_bytes(64, 64) > 0
+    assert mxp._native().quantize(None, 1) is None and mxp._native().gemm_w4a16() is None
+    import torch
+    with pytest.raises(mxp.MxpError):
+        mxp.quantize(torch.zeros((4, 64)))
+
+
+def test_build_without_a_host_compiler(monkeypatch, tmp_path):
+    """The native part alone is left out, with a warning, and none that another torch left stays behind."""
+    from paper_2510_14557_amd import build as b
+    old = tmp_path / "_mxp_binding.so"
+    old.write_bytes(b"")
+    monkeypatch.setattr(b, "BINDING_LIB", str(old))
+    for cxx in ("no-such-compiler", "false"):
+        monkeypatch.setenv("CXX", cxx)
+        if cxx == "false":
+            monkeypatch.setattr(b, "BINDING_SRC", str(tmp_path / "missing.cpp"))
+        with pytest.warns(RuntimeWarning, match="not built"):
+            b.build_binding()
+        assert not old.exists()
+
+
+def test_native_part_older_than_torch_is_not_up_to_date(monkeypatch, tmp_path):
+    import shutil
+    import torch
+    from paper_2510_14557_amd import build as b
+    if not b.up_to_date():
+        pytest.skip("the sources are newer than the build")
+    binding = tmp_path / "_mxp_binding.so"
+    shutil.copy(b.BINDING_LIB, binding)
+    monkeypatch.setattr(b, "BINDING_LIB", str(binding))
+    version = os.path.getmtime(os.path.join(os.path.dirname(torch.__file__), "version.py"))
+    os.utime(binding, (version + 1e9, version + 1e9))
+    assert b.up_to_date()
+    os.utime(binding, (version - 1, version - 1))
+    assert not b.up_to_date()
+
+
 def test_stream_handle_without_torchs_private_name(monkeypatch):
     class Stream:
         cuda_stream = 1234
