@@ -66,11 +66,13 @@ at::Tensor output(const at::Tensor& like, int64_t M, int64_t N, int64_t d) {
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 int64_t integer(PyObject* o) { return PyLong_AsLongLong(o); }
 
-// `n` arguments, those from `first` on small integers
+// `n` arguments, those from `first` on integers of 64 bits (a longer one would leave an error set)
 bool arguments(PyObject* const* a, Py_ssize_t given, Py_ssize_t n, Py_ssize_t first) {
   if (given != n) return false;
-  for (Py_ssize_t i = first; i < n; ++i)
-    if (!PyLong_CheckExact(a[i])) return false;
+  for (Py_ssize_t i = first; i < n; ++i) {
+    int overflow = 0;
+    if (!PyLong_CheckExact(a[i]) || (PyLong_AsLongLongAndOverflow(a[i], &overflow), overflow != 0)) return false;
+  }
   return true;
 }
 template <class F>

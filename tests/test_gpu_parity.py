@@ -2699,3 +2699,16 @@ def test_gemm_with_and_without_images_lines_of_the_choice(fa, fb, M, N, K, image
     for dt in (torch.float32, torch.bfloat16):
         D, used = gemm_in_marked_room(qa, fa, qb, fb, dt)
         assert used == images and close_to_deconverted(D, qa, fa, qb, fb, dt)
+
+
+def test_native_calls_with_integers_beyond_64_bits():
+    """Left to the general code like any other call that the native part does not take, with no error of its own behind them."""
+    x = torch.randn((4, 256), device="cuda").bfloat16()
+    q = mxp.quantize(x)
+    img = mxp.prepack(q)
+    big, n = 1 << 70, mxp._native()
+    assert n.quantize(x, big) is None and n.dequantize(q, big, 0) is None and n.dequantize(q, 1, big) is None
+    assert n.gemm(q, q, 1, big, 0) is None and n.gemm_bf16a(x, img, 1, big, 0, 0) is None and n.gemm_bf16a(x, img, 1, -big, 0, 0) is None
+    assert n.gemm_decode_bf16a(x, q, big, 1, 0) is None and n.gemm_w4a16(x, q, big, 0) is None
+    with pytest.raises((TypeError, RuntimeError, OverflowError)):
+        mxp.gemm_bf16a(x, 1, img, big)
