@@ -2712,3 +2712,130 @@ def test_native_calls_with_integers_beyond_64_bits():
     assert n.gemm_decode_bf16a(x, q, big, 1, 0) is None and n.gemm_w4a16(x, q, big, 0) is None
     with pytest.raises((TypeError, RuntimeError, OverflowError)):
         mxp.gemm_bf16a(x, 1, img, big)
+
+
+NATIVE = ("quantize", "dequantize", "gemm", "gemm_bf16a", "gemm_decode_bf16a", "gemm_w4a16")
+
+
+class Recorder:
+    """The native part of the binding, with a note of each call: was it taken."""
+
+    def __init__(self, native):
+        self.native, self.taken = native, []
+
+    def __getattr__(self, name):
+        def call(*args):
+            out = getattr(self.native, name)(*args)
+            self.taken.append((name, out is not None))
+            return out
+        return call
+
+
+def test_native_part_takes_the_ordinary_calls_and_no_others(monkeypatch):
+    """Every call with nothing but its defaults is taken, in both dtypes, for rows of a wider tensor and a single row; one that is given
+    an output or a workspace, or is multiplied in optional room, does not come to it; what it cannot do it leaves."""
+    rec = Recorder(mxp._native())
+    monkeypatch.setattr(mxp, "_fast", rec)
+
+    def took(name, f, taken=True):
+        rec.taken.clear()
+        f()
+        assert rec.taken == [(name, taken)], (name, rec.taken)
+
+    def left(f):
+        rec.taken.clear()
+        f()
+        assert rec.taken == [], rec.taken
+
+    for M in (1, 13):
+        wide = torch.randn((M, 320), device="cuda")
+        for x in (wide[:, :256], wide[:, :256].contiguous(), wide.bfloat16()[:, :256]):
+            for f in range(7):
+                took("quantize", lambda: mxp.quantize(x, f))
+                q = mxp.quantize(x, f)
+                for dt in (torch.float32, torch.bfloat16):
+                    took("dequantize", lambda: mxp.dequantize(q, f, dt))
+                    if f <= mxp.MXFP6P:
+                        took("gemm", lambda: mxp.gemm(q, f, q, f, dt))
+                    if x.dtype == torch.bfloat16:
+                        took("gemm_w4a16", lambda: mxp.gemm_w4a16(x, q, f, dt))
+            q = mxp.quantize(x)
+            e, s, _ = mxp.quantize(x, mxp.MXFP4)
+            img = mxp.prepack(q)
+            took("gemm", lambda: mxp.gemm(q, 1, (e, s, None), 0))
+            took("dequantize", lambda: mxp.dequantize((e, s, None), 0))
+            took("gemm_bf16a", lambda: mxp.gemm_bf16a(x, 1, img, M))
+            took("gemm_decode_bf16a", lambda: mxp.gemm_decode_bf16a(x, 1, q))
+            out = torch.empty((M, M), device="cuda")
+            left(lambda: mxp.gemm(q, 1, q, 1, out=out))
+            left(lambda: mxp.gemm_bf16a(x, 1, img, M, out=out))
+            left(lambda: mxp.dequantize(q, 1, out=torch.empty((M, 256), device="cuda")))
+            q8, q6, qpp = mxp.quantize(x, mxp.MXFP8), mxp.quantize(x, mxp.MXFP6), mxp.quantize(x, mxp.MXFP4PP)
+            for (qa, fa), (qb, fb) in (((q8, 5), (q, 1)), ((q, 1), (q8, 5)), ((qpp, 2), (q6, 3)), ((q6, 3), (qpp, 2))):
+                left(lambda: mxp.gemm(qa, fa, qb, fb))
+    x = torch.randn((4, 256), device="cuda")
+    q = mxp.quantize(x)
+    for name, kind, f in (("quantize", TypeError, lambda: mxp.quantize(x.half())), ("quantize", mxp.MxpError, lambda: mxp.quantize(x.cpu())),
+                          ("quantize", mxp.MxpError, lambda: mxp.quantize(x[:, ::2])), ("quantize", mxp.MxpError, lambda: mxp.quantize(x[:, :40])),
+                          ("dequantize", TypeError, lambda: mxp.dequantize(q, 1, torch.float16)), ("gemm_w4a16", mxp.MxpError, lambda: mxp.gemm_w4a16(x, q))):
+        def refused():
+            with pytest.raises(kind):
+                f()
+        took(name, refused, False)
+
+
+def test_native_calls_run_on_the_current_stream(monkeypatch):
+    """Captured on a side stream, each native call is part of the graph: it has not run when the capture ends, and each replay runs it
+    on the inputs as they are then."""
+    rec = Recorder(mxp._native())
+    monkeypatch.setattr(mxp, "_fast", rec)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(71)
+    x = torch.randn((8, 256), generator=gen, device="cuda").bfloat16()
+    qw = mxp.quantize(torch.randn((128, 256), generator=gen, device="cuda"))
+    img = mxp.prepack(qw)
+
+    def calls():
+        q = mxp.quantize(x)
+        return [*q, mxp.dequantize(q), mxp.gemm(q, 1, qw, 1), mxp.gemm_bf16a(x, 1, img, 128), mxp.gemm_decode_bf16a(x, 1, qw), mxp.gemm_w4a16(x, qw)]
+
+    calls()
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    rec.taken.clear()
+    with torch.cuda.stream(side):
+        with torch.cuda.graph(g, stream=side):
+            outs = calls()
+    assert rec.taken == [(n, True) for n in NATIVE]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        x.copy_(torch.randn((8, 256), generator=gen, device="cuda"))
+        for t in outs:
+            t.fill_(0)
+        g.replay()
+        torch.cuda.synchronize()
+        for got, want in zip(outs, calls()):
+            assert torch.equal(got, want)
+        torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("fa,fb", [(a, b) for a in CANON for b in CANON if not ("mxfp4pp" in (a, b) and {a, b} & {"mxfp6", "mxfp6p"})])
+@pytest.mark.parametrize("M,N,K,pad", [(2100, 2200, 160, 3), (33, 100, 6176, 0), (4200, 1056, 64, 1), (3, 70, 12320, 4)])
+def test_gemm_through_images_every_pair(fa, fb, M, N, K, pad):
+    """Products that go through images: just over one round of 128 x 128 tiles, and few of them by long K, each pair either way round
+    (two MXFP4++ operands to the FP8 route's own bound), both output types, rows of D with gaps."""
+    rng = np.random.default_rng(73)
+    qa, qb = q_dev(any_operand(M, K, fa, rng)), q_dev(any_operand(N, K, fb, rng))
+    a, b = mxp.dequantize(qa, CANON[fa]).double(), mxp.dequantize(qb, CANON[fb]).double()
+    ref, S = a @ b.t(), a.abs() @ b.abs().t()
+    nan = ref.isnan()
+    ws = torch.full((mxp.gemm_workspace_bytes(M, N, K, CANON[fa], CANON[fb]),), 0xA5, dtype=torch.uint8, device="cuda")
+    for dt in (torch.float32, torch.bfloat16):
+        out = torch.full((M, N + pad), 7.0, dtype=dt, device="cuda")
+        D = mxp.gemm(qa, CANON[fa], qb, CANON[fb], out=out[:, :N], workspace=ws)
+        assert (D.isnan() == nan).all() and (out[:, N:] == 7.0).all()
+        bound = (7 * 2.0 ** -13 if fa == fb == "mxfp4pp" else 0.0) * S + 2.0 ** -16 * S + (2.0 ** -8 * ref.abs() if dt == torch.bfloat16 else 0.0)
+        assert ((D.double() - ref).abs() <= bound)[~nan].all()
+    assert (ws != 0xA5).any()
