@@ -24,6 +24,7 @@
 //   MXFP6+   the codes with BM_H in the BM's place (E2M3) | BM_L alone (E2M3)
 // A pair of blocks takes as many MFMAs as the product of their numbers of terms.
 #include "mxp_common.h"
+#include "mxp_decode.h"
 #include "mxp_prepack_body.h"
 #include "mxp_tile.h"
 #include <type_traits>
@@ -81,41 +82,6 @@ __device__ __forceinline__ Block<FMT> load_block(const uint8_t* el, const uint8_
   r.ib = Kind<FMT>::PLUS ? (uint32_t)ix[b] : 0u;
   return r;
 }
-
-// The six bits at bit 6 i of a 192-bit string.  Eight elements are 48 bits: group i / 8 starts at bit 0 or 16 of dword 3 (i / 16).
-struct SixAt {
-  uint32_t sh, odd, upper;                                   // odd, upper: all ones or zero
-  __device__ __forceinline__ explicit SixAt(uint32_t i)
-      : sh(6u * (i & 7u)), odd((uint32_t)((int32_t)(i << 28) >> 31)), upper((uint32_t)((int32_t)(i << 27) >> 31)) {}
-  // d ^= the string that holds `code` there and zeros elsewhere
-  __device__ __forceinline__ void put(uint32_t code, uint32_t (&d)[6]) const {
-    const uint64_t v = (uint64_t)code << sh;
-    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-    const uint32_t t0 = lo & ~odd, t1 = odd ? lo << 16 : hi, t2 = __builtin_amdgcn_alignbit(hi, lo, 16) & odd;
-    d[0] ^= t0 & ~upper; d[1] ^= t1 & ~upper; d[2] ^= t2 & ~upper;
-    d[3] ^= t0 & upper; d[4] ^= t1 & upper; d[5] ^= t2 & upper;
-  }
-  __device__ __forceinline__ uint32_t get(const uint32_t (&d)[6]) const {
-    const uint32_t e0 = upper ? d[3] : d[0], e1 = upper ? d[4] : d[1], e2 = upper ? d[5] : d[2];
-    const uint32_t lo = odd ? __builtin_amdgcn_alignbit(e2, e1, 16) : e0, hi = odd ? e2 >> 16 : e1;
-    return (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 0x3Fu;
-  }
-};
-
-// The four bits at bit 4 i of a 128-bit string
-struct FourAt {
-  uint32_t sh, upper;
-  __device__ __forceinline__ explicit FourAt(uint32_t i) : sh(4u * (i & 15u)), upper((uint32_t)((int32_t)(i << 27) >> 31)) {}
-  __device__ __forceinline__ uint32_t get(const uint32_t (&d)[4]) const {
-    const uint32_t lo = upper ? d[2] : d[0], hi = upper ? d[3] : d[1];
-    return (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 15u;
-  }
-  __device__ __forceinline__ void put(uint32_t nib, uint32_t (&d)[4]) const {
-    const uint64_t v = (uint64_t)nib << sh;
-    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
-    d[0] ^= lo & ~upper; d[1] ^= hi & ~upper; d[2] ^= lo & upper; d[3] ^= hi & upper;
-  }
-};
 
 // Block -> terms t0, t1 (four dwords count of an E2M1 term, six of an E2M3 one) and their scale bytes.  A block outside the
 // matrix (!ok) counts as a flushed one: scale byte 0, zeros whatever its codes say.

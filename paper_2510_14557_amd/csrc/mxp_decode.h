@@ -23,6 +23,53 @@ __device__ __forceinline__ uint32_t make_f32(uint32_t sign, uint32_t M, int sbyt
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 
+// The six bits at bit 6 i of a 192-bit string.  Eight elements are 48 bits: group i / 8 starts at bit 0 or 16 of dword 3 (i / 16).
+struct SixAt {
+  uint32_t sh, odd, upper;                                   // odd, upper: all ones or zero
+  __device__ __forceinline__ explicit SixAt(uint32_t i)
+      : sh(6u * (i & 7u)), odd((uint32_t)((int32_t)(i << 28) >> 31)), upper((uint32_t)((int32_t)(i << 27) >> 31)) {}
+  // d ^= the string that holds `code` there and zeros elsewhere
+  __device__ __forceinline__ void put(uint32_t code, uint32_t (&d)[6]) const {
+    const uint64_t v = (uint64_t)code << sh;
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    const uint32_t t0 = lo & ~odd, t1 = odd ? lo << 16 : hi, t2 = __builtin_amdgcn_alignbit(hi, lo, 16) & odd;
+    d[0] ^= t0 & ~upper; d[1] ^= t1 & ~upper; d[2] ^= t2 & ~upper;
+    d[3] ^= t0 & upper; d[4] ^= t1 & upper; d[5] ^= t2 & upper;
+  }
+  __device__ __forceinline__ uint32_t get(const uint32_t (&d)[6]) const {
+    const uint32_t e0 = upper ? d[3] : d[0], e1 = upper ? d[4] : d[1], e2 = upper ? d[5] : d[2];
+    const uint32_t lo = odd ? __builtin_amdgcn_alignbit(e2, e1, 16) : e0, hi = odd ? e2 >> 16 : e1;
+    return (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 0x3Fu;
+  }
+};
+
+// The four bits at bit 4 i of a 128-bit string
+struct FourAt {
+  uint32_t sh, upper;
+  __device__ __forceinline__ explicit FourAt(uint32_t i) : sh(4u * (i & 15u)), upper((uint32_t)((int32_t)(i << 27) >> 31)) {}
+  __device__ __forceinline__ uint32_t get(const uint32_t (&d)[4]) const {
+    const uint32_t lo = upper ? d[2] : d[0], hi = upper ? d[3] : d[1];
+    return (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 15u;
+  }
+  __device__ __forceinline__ void put(uint32_t nib, uint32_t (&d)[4]) const {
+    const uint64_t v = (uint64_t)nib << sh;
+    const uint32_t lo = (uint32_t)v, hi = (uint32_t)(v >> 32);
+    d[0] ^= lo & ~upper; d[1] ^= hi & ~upper; d[2] ^= lo & upper; d[3] ^= hi & upper;
+  }
+};
+
+// `put`, a bf16 in either half of a dword, or-ed onto pair i / 2 of 16: at its place in a group of four pairs first, then one and-or
+// per pair with the group's mask.
+__device__ __forceinline__ void or_onto_pair(uint32_t i, uint32_t put, uint32_t (&w)[16]) {
+  const bool q0 = (i & 2u) != 0u, q1 = (i & 4u) != 0u;
+  const uint32_t a = q1 ? 0u : put, b = q1 ? put : 0u;
+  const uint32_t p[4] = {q0 ? 0u : a, q0 ? a : 0u, q0 ? 0u : b, q0 ? b : 0u};
+  const uint32_t g0 = (uint32_t)((int32_t)(i << 28) >> 31), g1 = (uint32_t)((int32_t)(i << 27) >> 31);
+  const uint32_t m[4] = {~g0 & ~g1, g0 & ~g1, ~g0 & g1, g0 & g1};
+#pragma unroll
+  for (int j = 0; j < 16; ++j) w[j] |= p[j & 3] & m[j >> 2];
+}
+
 // Eight elements (one dword of nibbles) per lane.  Common case: the E2M1 elements go through the CDNA4 unpack-convert
 // instruction with X = 2^shared_exp as the scale (exact: at most 2 significant bits times a power of two), and the lane
 // that holds the BM overwrites that one element with 2^e_max * 1.mmm * X (Eq. 2, first case).  Blocks whose results

@@ -81,15 +81,9 @@ __device__ __forceinline__ void decode(const uint32_t (&raw)[Few<FMT>::DW], uint
   if constexpr (PLUS) {
     uint32_t code;
     if constexpr (BITS == 6) {
-      const uint32_t sh = 6u * (idx & 7u), odd = (uint32_t)((int32_t)(idx << 28) >> 31), upper = (uint32_t)((int32_t)(idx << 27) >> 31);
-      const uint32_t e0 = upper ? n[3] : n[0], e1 = upper ? n[4] : n[1], e2 = upper ? n[5] : n[2];
-      const uint32_t lo = odd ? __builtin_amdgcn_alignbit(e2, e1, 16) : e0, hi = odd ? e2 >> 16 : e1;
-      code = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 0x3Fu;
-      const uint64_t v = (uint64_t)code << sh;
-      const uint32_t vl = (uint32_t)v, vh = (uint32_t)(v >> 32);
-      const uint32_t t0 = vl & ~odd, t1 = odd ? vl << 16 : vh, t2 = __builtin_amdgcn_alignbit(vh, vl, 16) & odd;
-      n[0] ^= t0 & ~upper; n[1] ^= t1 & ~upper; n[2] ^= t2 & ~upper;
-      n[3] ^= t0 & upper; n[4] ^= t1 & upper; n[5] ^= t2 & upper;
+      const SixAt at(idx);
+      code = at.get(n);
+      at.put(code, n);
       put = ((code & 0x20u) << 10) | ((sb + EMAX) << 7) | ((code & 0x1Fu) << 2);
     } else {
       uint32_t d = n[0];
@@ -126,15 +120,7 @@ __device__ __forceinline__ void decode(const uint32_t (&raw)[Few<FMT>::DW], uint
       w[2 * j] = c0.u; w[2 * j + 1] = c1.u;
     }
   }
-  if constexpr (PLUS) {
-    const bool q0 = (idx & 2u) != 0u, q1 = (idx & 4u) != 0u;
-    const uint32_t a = q1 ? 0u : put, b = q1 ? put : 0u;
-    const uint32_t p[4] = {q0 ? 0u : a, q0 ? a : 0u, q0 ? 0u : b, q0 ? b : 0u};
-    const uint32_t g0 = (uint32_t)((int32_t)(idx << 28) >> 31), g1 = (uint32_t)((int32_t)(idx << 27) >> 31);
-    const uint32_t m[4] = {~g0 & ~g1, g0 & ~g1, ~g0 & g1, g0 & g1};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) w[j] |= p[j & 3] & m[j >> 2];
-  }
+  if constexpr (PLUS) or_onto_pair(idx, put, w);
   if (__builtin_amdgcn_ballot_w64(!plain) == 0) return;
   const bool reserved = sb == 0u || sb == 255u;              // zeros, NaN
   const uint32_t special = sb == 0u ? 0u : 0x7FC07FC0u;

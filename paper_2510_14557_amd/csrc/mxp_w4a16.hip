@@ -58,12 +58,9 @@ __device__ __forceinline__ void decode_block_bf16(const u32x4 q, uint32_t sbyte,
   const bool plain = sbyte >= 2u + delta && sbyte <= 250u, flushed = sbyte == 0u;
   uint32_t put = 0;
   if (MODE >= 1) {
-    const uint32_t upper = (uint32_t)((int32_t)(idx << 27) >> 31), sh = 4u * (idx & 15u);
-    const uint32_t lo = upper ? n[2] : n[0], hi = upper ? n[3] : n[1];
-    const uint32_t nib = (uint32_t)((((uint64_t)hi << 32) | lo) >> sh) & 15u;
-    const uint64_t v = (uint64_t)nib << sh;
-    const uint32_t vl = (uint32_t)v, vh = (uint32_t)(v >> 32);
-    n[0] ^= vl & ~upper; n[1] ^= vh & ~upper; n[2] ^= vl & upper; n[3] ^= vh & upper;
+    const FourAt at(idx);
+    const uint32_t nib = at.get(n);
+    at.put(nib, n);
     put = (((nib & 8u) << 12) | ((sbyte + 2u) << 7) | ((nib & 7u) << 4)) << (16u * (idx & 1u));   // 2^e_max * 1.mmm * X
   }
   const uint32_t keep = flushed ? 0u : ~0u;                  // a flushed block is zero whatever its codes say
@@ -78,15 +75,7 @@ __device__ __forceinline__ void decode_block_bf16(const u32x4 q, uint32_t sbyte,
     c3.v = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(n[j], X, 3);
     w[4 * j] = c0.u; w[4 * j + 1] = c1.u; w[4 * j + 2] = c2.u; w[4 * j + 3] = c3.u;
   }
-  if (MODE >= 1) {
-    const bool q0 = (idx & 2u) != 0u, q1 = (idx & 4u) != 0u;
-    const uint32_t a = q1 ? 0u : put, b = q1 ? put : 0u;
-    const uint32_t p[4] = {q0 ? 0u : a, q0 ? a : 0u, q0 ? 0u : b, q0 ? b : 0u};
-    const uint32_t g0 = (uint32_t)((int32_t)(idx << 28) >> 31), g1 = (uint32_t)((int32_t)(idx << 27) >> 31);
-    const uint32_t m[4] = {~g0 & ~g1, g0 & ~g1, ~g0 & g1, g0 & g1};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) w[j] |= p[j & 3] & m[j >> 2];
-  }
+  if (MODE >= 1) or_onto_pair(idx, put, w);
   if (__builtin_amdgcn_ballot_w64(!plain && !flushed) != 0) {
 #pragma unroll 1
     for (uint32_t s = 0; s < 4; ++s) {                       // (in one loop: four copies cost the kernels their registers)
