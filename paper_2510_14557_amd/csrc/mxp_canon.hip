@@ -34,6 +34,7 @@ namespace {
 using namespace mxp;
 typedef int v8i __attribute__((ext_vector_type(8)));
 
+constexpr int kConverting = 8;                               // converting wavefronts of a workgroup (four: 36 -> 45 us, head of this file)
 constexpr int kE2M3 = 2, kE2M1 = 4;                          // element format codes of the f8f6f4 MFMA
 
 // Element formats of the terms and bytes of a canonical block, by format code (MXP_FMT_*)
@@ -159,10 +160,10 @@ struct CanonOperand {
   int64_t rows;
 };
 
-// 2 x 2 wavefronts of WI x WJ MFMA tiles each multiply; PW more convert.  The B tile goes in as the MFMA's first operand:
+// 2 x 2 wavefronts of WI x WJ MFMA tiles each multiply; kConverting more convert.  The B tile goes in as the MFMA's first operand:
 // accumulator register r of lane l is D[m = l % 32][n = 8 (r / 4) + 4 (l / 32) + r % 4] of the 32 x 32 tile.
-template <int FA, int FB, int PW, int WI, int WJ, int KS>
-__global__ void __launch_bounds__(64 * (4 + PW)) canon_tiled_kernel(CanonOperand A, CanonOperand B, int nbk, void* __restrict__ Dv, int64_t ldd,
+template <int FA, int FB, int WI, int WJ, int KS>
+__global__ void __launch_bounds__(64 * (4 + kConverting)) canon_tiled_kernel(CanonOperand A, CanonOperand B, int nbk, void* __restrict__ Dv, int64_t ldd,
                                                                     int d_bf16, int n_rg, int n_cg) {
   constexpr int TR = 2 * WI, TC = 2 * WJ;
   static_assert(TR <= 4 && TC <= 4, "a scale dword has four tiles");
@@ -185,7 +186,7 @@ __global__ void __launch_bounds__(64 * (4 + PW)) canon_tiled_kernel(CanonOperand
   auto meet = [] { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); };
 
   if (wave >= 4) {                                           // ---- convert
-    constexpr int ROWS_PER_PASS = 64 * PW / KS, UA = 32 * TR / ROWS_PER_PASS, UB = 32 * TC / ROWS_PER_PASS;
+    constexpr int ROWS_PER_PASS = 64 * kConverting / KS, UA = 32 * TR / ROWS_PER_PASS, UB = 32 * TC / ROWS_PER_PASS;
     static_assert(UA >= 1 && UB >= 1, "every converting thread owns a block of either operand");
     // this thread's blocks; offsets count blocks from the tile's first one (a tile of 128 rows has fewer than 2^24)
     const uint32_t t = threadIdx.x - 256u, kb = t % KS, r0 = t / KS;
@@ -327,7 +328,7 @@ __global__ void __launch_bounds__(64 * (4 + PW)) canon_tiled_kernel(CanonOperand
   else store_tile_lds<WI, WJ, false, false, true>(acc, tm, tn, (int)lane, A.rows, B.rows, Dv, ldd, patch);
 }
 
-template <int FA, int FB, int PW, int WI, int WJ>
+template <int FA, int FB, int WI, int WJ>
 int launch_canon_shape(const CanonOperand& A, const CanonOperand& B, int64_t K, void* D, bool bf, int64_t ldd, hipStream_t s) {
   constexpr int TR = 2 * WI, TC = 2 * WJ;
   // steps of eight blocks, of four where two stages of eight do not fit LDS (128 x 128 tiles of four terms)
@@ -337,8 +338,8 @@ int launch_canon_shape(const CanonOperand& A, const CanonOperand& B, int64_t K, 
   static_assert(lds <= 160 * 1024, "LDS");
   const int64_t n_rg = (A.rows + 32 * TR - 1) / (32 * TR), n_cg = (B.rows + 32 * TC - 1) / (32 * TC);
   if (n_rg * n_cg > 2147483647LL) return MXP_ERR_UNSUPPORTED;
-  allow_dynamic_lds<&canon_tiled_kernel<FA, FB, PW, WI, WJ, KS>>(lds);
-  hipLaunchKernelGGL((canon_tiled_kernel<FA, FB, PW, WI, WJ, KS>), dim3((unsigned)(n_rg * n_cg)), dim3(64 * (4 + PW)), lds, s, A, B,
+  allow_dynamic_lds<&canon_tiled_kernel<FA, FB, WI, WJ, KS>>(lds);
+  hipLaunchKernelGGL((canon_tiled_kernel<FA, FB, WI, WJ, KS>), dim3((unsigned)(n_rg * n_cg)), dim3(64 * (4 + kConverting)), lds, s, A, B,
                      (int)(K / kBlock), D, ldd, bf ? 1 : 0, (int)n_rg, (int)n_cg);
   return launch_status();
 }
@@ -351,9 +352,9 @@ int launch_canon_shape(const CanonOperand& A, const CanonOperand& B, int64_t K, 
 template <int FA, int FB>
 int launch_canon_pair(const CanonOperand& A, const CanonOperand& B, int64_t K, void* D, bool bf, int64_t ldd, hipStream_t s) {
   const int64_t cg64 = (B.rows + 63) / 64, t64 = (A.rows + 63) / 64 * cg64, t128 = (A.rows + 127) / 128 * cg64;
-  if (t64 <= kNumCU || (t128 > kNumCU && t64 <= 2 * kNumCU)) return launch_canon_shape<FA, FB, 8, 1, 1>(A, B, K, D, bf, ldd, s);
-  if (t128 <= kNumCU) return launch_canon_shape<FA, FB, 8, 2, 1>(A, B, K, D, bf, ldd, s);
-  return launch_canon_shape<FA, FB, 8, 2, 2>(A, B, K, D, bf, ldd, s);
+  if (t64 <= kNumCU || (t128 > kNumCU && t64 <= 2 * kNumCU)) return launch_canon_shape<FA, FB, 1, 1>(A, B, K, D, bf, ldd, s);
+  if (t128 <= kNumCU) return launch_canon_shape<FA, FB, 2, 1>(A, B, K, D, bf, ldd, s);
+  return launch_canon_shape<FA, FB, 2, 2>(A, B, K, D, bf, ldd, s);
 }
 
 template <int FA>

@@ -23,6 +23,8 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 
+constexpr int kWaves = 8;                                    // wavefronts of a workgroup, which split K
+
 template <int FMT>
 struct Few {
   static constexpr bool PLUS = FMT == MXP_FMT_MXFP6P || FMT == MXP_FMT_MXFP8P;
@@ -136,8 +138,8 @@ __device__ __forceinline__ void decode(const uint32_t (&raw)[Few<FMT>::DW], uint
   }
 }
 
-template <int FMT, int MT, int CT, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES) few_rows_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint8_t* __restrict__ w_el,
+template <int FMT, int MT, int CT>
+__global__ void __launch_bounds__(64 * kWaves) few_rows_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint8_t* __restrict__ w_el,
                                                               const uint8_t* __restrict__ w_sc, const uint8_t* __restrict__ w_ix, int nbk,
                                                               int M, int64_t N, void* __restrict__ Dv, int64_t ldd, int d_bf16) {
   using F = Few<FMT>;
@@ -193,7 +195,7 @@ __global__ void __launch_bounds__(64 * WAVES) few_rows_kernel(const uint16_t* __
   };
   const int n_chunks = (nbk + 4 * STEPS - 1) / (4 * STEPS);
   const int first = (int)((blockIdx.x * 5u) % (uint32_t)n_chunks);   // (workgroups start their walk at different chunks)
-  for (int ci = wave; ci < n_chunks; ci += WAVES) {
+  for (int ci = wave; ci < n_chunks; ci += kWaves) {
     const int q = ci + first < n_chunks ? ci + first : ci + first - n_chunks;
     Chunk c;
     load_w(q, c);
@@ -233,7 +235,7 @@ __global__ void __launch_bounds__(64 * WAVES) few_rows_kernel(const uint16_t* __
   }
   // partial tiles: register r of a tile 66 floats on, so that the four columns of a lane lie on different banks
   constexpr int TILE = 4 * 66;
-  float* part = reinterpret_cast<float*>(lds_raw);          // [WAVES][MT * CT][TILE]
+  float* part = reinterpret_cast<float*>(lds_raw);          // [kWaves][MT * CT][TILE]
 #pragma unroll
   for (int i = 0; i < MT; ++i)
 #pragma unroll
@@ -242,12 +244,12 @@ __global__ void __launch_bounds__(64 * WAVES) few_rows_kernel(const uint16_t* __
       for (int q = 0; q < 4; ++q) part[(wave * MT * CT + i * CT + j) * TILE + q * 66 + lane] = acc[i][j][q];
   __syncthreads();
   constexpr int COLS = 16 * CT;
-  for (int e = tid; e < MT * 16 * COLS; e += 64 * WAVES) {
+  for (int e = tid; e < MT * 16 * COLS; e += 64 * kWaves) {
     const int row = e / COLS, c = e % COLS, i = row >> 4, j = c >> 4;
     const float* p = part + (i * CT + j) * TILE + (c & 3) * 66 + (row & 15) + 16 * ((c & 15) >> 2);
     float v = 0.0f;
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) v += p[w * MT * CT * TILE];
+    for (int w = 0; w < kWaves; ++w) v += p[w * MT * CT * TILE];
     const int64_t col = n0 + c;
     if (row < M && col < N) {
       if (d_bf16) {
@@ -261,15 +263,15 @@ __global__ void __launch_bounds__(64 * WAVES) few_rows_kernel(const uint16_t* __
   }
 }
 
-template <int FMT, int MT, int CT, int WAVES>
+template <int FMT, int MT, int CT>
 int launch_few(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi, void* D,
                int d_dtype, int64_t ldd, hipStream_t s) {
-  constexpr int lds = WAVES * MT * CT * 4 * 66 * 4;
+  constexpr int lds = kWaves * MT * CT * 4 * 66 * 4;
   static_assert(lds <= 160 * 1024, "LDS");
   const int64_t grid = (N + 16 * CT - 1) / (16 * CT);
   if (grid > 2147483647LL) return MXP_ERR_UNSUPPORTED;
-  allow_dynamic_lds<&few_rows_kernel<FMT, MT, CT, WAVES>>(lds);
-  hipLaunchKernelGGL((few_rows_kernel<FMT, MT, CT, WAVES>), dim3((unsigned)grid), dim3(64 * WAVES), lds, s, static_cast<const uint16_t*>(A), lda, we, ws,
+  allow_dynamic_lds<&few_rows_kernel<FMT, MT, CT>>(lds);
+  hipLaunchKernelGGL((few_rows_kernel<FMT, MT, CT>), dim3((unsigned)grid), dim3(64 * kWaves), lds, s, static_cast<const uint16_t*>(A), lda, we, ws,
                      wi, (int)(K / kBlock), (int)M, N, D, ldd, d_dtype == MXP_BF16 ? 1 : 0);
   return launch_status();
 }
@@ -280,7 +282,7 @@ int launch_few(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, cons
 template <int FMT>
 int launch_few_format(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda, const uint8_t* we, const uint8_t* ws, const uint8_t* wi,
                       void* D, int d_dtype, int64_t ldd, hipStream_t s) {
-#define MXP_FEW(MT, CT) return launch_few<FMT, MT, CT, 8>(M, N, K, A, lda, we, ws, wi, D, d_dtype, ldd, s)
+#define MXP_FEW(MT, CT) return launch_few<FMT, MT, CT>(M, N, K, A, lda, we, ws, wi, D, d_dtype, ldd, s)
   const int64_t c16 = (N + 15) / 16;
   if (M <= 16) {
     if (c16 <= kNumCU) MXP_FEW(1, 1);

@@ -125,91 +125,6 @@ __device__ __forceinline__ void store_tile_lds(const v16f (&acc)[TWM][TWN], int6
   }
 }
 
-// Epilogue of the kernels whose four wavefronts split K: every wavefront holds a partial 32 TMR x 32 CT block, and the sum is stored.
-// A 128 x 128 block has four partial blocks of 64 KiB, more than LDS holds: wavefronts 2 and 3 first hand theirs to
-// wavefronts 0 and 1 in the accumulators' own layout (lane-contiguous 16-byte pieces, no transposition), which add them
-// to their own; the two sums then go through the row layout like the four partials of the smaller blocks.  The partial blocks lie
-// in LDS as rows of the output (padded by 16 bytes against bank conflicts), so the summing pass reads and stores 16-byte pieces of
-// full 128- or 256-byte rows.  rt0, ct0: the block's first row and column tile.  All 256 threads; LDS that others read is idle.
-template <int TMR, int CT>
-constexpr int k_split_lds() {
-  constexpr int rows_l = (TMR * CT == 16 ? 2 : 4) * 32 * TMR * (32 * CT + 4) * 4, stage_l = TMR * CT == 16 ? 2 * 16 * 4 * 64 * 16 : 0;
-  return rows_l > stage_l ? rows_l : stage_l;
-}
-template <int TMR, int CT>
-__device__ __forceinline__ void store_k_split(v16f (&acc)[TMR][CT], uint8_t* block_lds, int tid, int wave, int64_t rt0, int64_t ct0, int64_t M,
-                                              int64_t N, void* __restrict__ Dv, int64_t ldd, bool out_bf16) {
-  typedef float f32x4 __attribute__((ext_vector_type(4)));
-  constexpr bool BIG = TMR * CT == 16;
-  constexpr int PARTS = BIG ? 2 : 4, ROWS = 32 * TMR, COLS = 32 * CT, STRIDE = COLS + 4;   // partial blocks in the row layout
-  const int lane = tid & 63;
-  float* part = reinterpret_cast<float*>(block_lds);                        // [PARTS][ROWS][STRIDE]
-  if constexpr (BIG) {
-    f32x4* stage = reinterpret_cast<f32x4*>(block_lds) + (size_t)(wave & 1) * (TMR * CT * 4 * 64) + lane;
-    if (wave >= 2) {
-#pragma unroll
-      for (int i = 0; i < TMR; ++i)
-#pragma unroll
-        for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-          for (int g = 0; g < 4; ++g)
-            stage[((i * CT + jj) * 4 + g) * 64] = (f32x4){acc[i][jj][4 * g], acc[i][jj][4 * g + 1], acc[i][jj][4 * g + 2], acc[i][jj][4 * g + 3]};
-    }
-    __syncthreads();
-    if (wave < 2) {
-#pragma unroll
-      for (int i = 0; i < TMR; ++i)
-#pragma unroll
-        for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            const f32x4 o = stage[((i * CT + jj) * 4 + g) * 64];
-            acc[i][jj][4 * g] += o[0]; acc[i][jj][4 * g + 1] += o[1]; acc[i][jj][4 * g + 2] += o[2]; acc[i][jj][4 * g + 3] += o[3];
-          }
-    }
-    __syncthreads();                                                        // the staging area is read: it becomes the row layout
-  }
-  // partial blocks to LDS as output rows: accumulator quad g of lane l is row l % 32, columns 8 g + 4 (l / 32) .. + 3 of its tile
-  if (wave < PARTS) {
-    float* mine = part + (size_t)wave * ROWS * STRIDE;
-#pragma unroll
-    for (int i = 0; i < TMR; ++i)
-#pragma unroll
-      for (int jj = 0; jj < CT; ++jj)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x4 q4 = {acc[i][jj][4 * g], acc[i][jj][4 * g + 1], acc[i][jj][4 * g + 2], acc[i][jj][4 * g + 3]};
-          *reinterpret_cast<f32x4*>(mine + (32 * i + (lane & 31)) * STRIDE + 32 * jj + 8 * g + 4 * (lane >> 5)) = q4;
-        }
-  }
-  __syncthreads();
-  const bool vec_ok = (ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(Dv) & 15u) == 0);
-  constexpr int QUADS = COLS / 4;                                           // 16-byte pieces per row
-  for (int e = tid; e < ROWS * QUADS; e += 256) {
-    const int r = e / QUADS, q = e % QUADS;
-    f32x4 v = *reinterpret_cast<const f32x4*>(part + r * STRIDE + 4 * q);
-#pragma unroll
-    for (int w = 1; w < PARTS; ++w) v += *reinterpret_cast<const f32x4*>(part + ((size_t)w * ROWS + r) * STRIDE + 4 * q);
-    const int64_t row = rt0 * 32 + r, col = ct0 * 32 + 4 * q;
-    if (row >= M || col >= N) continue;
-    if (vec_ok && col + 3 < N) {
-      if (out_bf16) {
-        const u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        __builtin_nontemporal_store(o, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(Dv) + row * ldd + col));
-      } else {
-        __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(static_cast<float*>(Dv) + row * ldd + col));
-      }
-    } else {
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-        if (col + t < N) {
-          if (out_bf16) static_cast<uint16_t*>(Dv)[row * ldd + col + t] = (uint16_t)f32_to_bf16_rne(v[t]);
-          else static_cast<float*>(Dv)[row * ldd + col + t] = v[t];
-        }
-    }
-  }
-}
-
 constexpr int kBand = 4;
 
 __device__ __forceinline__ void band_decode(int p, int rows, int cols, int& r, int& c, int band_cols = kBand) {
