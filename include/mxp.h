@@ -246,7 +246,10 @@ int mxp_convert_operands(const void* A, int a_dtype, int64_t M, int64_t K, int64
  * canonical storage, formats chosen per operand (Sec. 5: activations MXFP4+ with weights MXFP4 or MXFP4+).
  * The result is the matrix product of the de-converted operands accumulated in fp32 (Sec. 5.1).
  * D is MXP_F32 or MXP_BF16 with row stride ldd.  workspace must hold mxp_gemm_workspace_bytes(M, N, K) bytes; it is
- * scratch for the two images and may be reused after the call's work on `stream` has finished.  With one MXFP4++ operand
+ * scratch for the two images and may be reused after the call's work on `stream` has finished.  Products of at most one
+ * round of 128 x 128 tiles over the chip are mostly multiplied from the canonical bytes and leave it alone: its size is
+ * asked for all the same (a smaller one returns MXP_ERR_WORKSPACE), so that what a caller provides does not depend on
+ * which of the two runs.  With one MXFP4++ operand
  * (Sec. 4.3) the product is formed exactly over two K segments (see mxp_prepack_seg; workspace:
  * mxp_gemm_workspace_size(M, N, K, fmtA, fmtB)); with two, both operands go through E4M3 images (see MXP_IMAGE_E4M3 for
  * what that costs and how exact it is) and the workspace must hold mxp_gemm_workspace_bytes_e4m3(M, N, K) bytes. */
@@ -272,7 +275,8 @@ int mxp_gemm(int64_t M, int64_t N, int64_t K,
  * device array built into the library instead of a caller workspace.  Neither this call nor anything it runs allocates
  * or frees memory.  The array holds mxp_gemm_static_capacity() bytes (64 MiB, resident on every GPU the library is used
  * on until the process ends); a product whose images need more -- mxp_gemm_workspace_size(M, N, K, fmtA, fmtB) bytes --
- * returns MXP_ERR_SCRATCH and enqueues nothing (the Llama-8B prefill-MLP product, 4096 x 14336 x 4096, needs 56.3 MiB).
+ * returns MXP_ERR_SCRATCH and enqueues nothing, also where mxp_gemm would leave its workspace alone (the Llama-8B
+ * prefill-MLP product, 4096 x 14336 x 4096, needs 56.3 MiB).
  * Pairs that are multiplied from de-converted operands, whose workspace is optional, are not refused: they use the array
  * for A and slabs of B where A fits, and otherwise leave it alone.
  * All calls on one GPU share that array, which keeps the previous call's images: every byte a product reads is
@@ -321,16 +325,18 @@ int mxp_gemm_decode_bf16a(int64_t M, int64_t N, int64_t K, const void* A, int a_
  * quantized, blocks are de-converted to a wider type inside the kernel): D[M][N] = A[M][K] x deq(W)^T with A left as
  * it is (MXP_BF16, row stride lda; MXP_F32 returns MXP_ERR_UNSUPPORTED) and W[N][K] in canonical MXFP4, MXFP4+ or
  * MXFP4++ storage, de-converted by Eq. 2 to bf16 (exact) and multiplied on the bf16 MFMA with fp32 accumulation.
- * M <= 64 (up to 128 in two passes): a kernel bound by reading the 4-bit weights once.  Larger M (prefill with
+ * M <= 64 (4-bit weights: up to 128 in two passes): kernels that read the weights once.  Larger M (prefill with
  * weight-only quantization): 256 x 256 output tiles, the weights de-converted once per tile and 64-element step of K
- * on their way into LDS.  The tiled kernel also takes MXFP6(+) and MXFP8(+) weights (any M).  D is MXP_F32 or MXP_BF16
+ * on their way into LDS.  Both take MXFP6(+) and MXFP8(+) weights too (these in tiles from M = 33 on where K is at most
+ * 192 and N large).  They sum along K in different orders, hence to different last bits.  D is MXP_F32 or MXP_BF16
  * with row stride ldd.  No workspace; mxp_gemm_w4a16_ws is faster where it has a use for one. */
 int mxp_gemm_w4a16(int64_t M, int64_t N, int64_t K, const void* A, int a_dtype, int64_t lda,
                    const uint8_t* W_elems, const uint8_t* W_scales, const uint8_t* W_idx, int fmtW,
                    void* D, int d_dtype, int64_t ldd, void* stream);
 /* The same with room for W as bf16: W is then de-converted once, ahead of a plain bf16 product (in even slabs of as many
- * rows of W as fit; the same products in the same order), where that is estimated to be faster than de-conversion inside
- * the product: 4-bit W above 128 rows of A, wider W at any number of rows, K >= 256, lda < 2^23.
+ * rows of W as fit), where that is estimated to be faster: 4-bit W above 128 rows of A, wider W above 64 and, with room
+ * for all of W, for some numbers of columns above 44, K >= 256, lda < 2^23.  Above 128 rows the same products are summed
+ * in the same order as without room (identical bits).
  * mxp_gemm_w4a16_workspace_bytes: the room worth giving, at most 256 MiB; 0 where it would not be used (for rows of A and D
  * without gaps).  workspace may be NULL or smaller: the call then uses smaller slabs or runs as mxp_gemm_w4a16 does; larger
  * room is used too. */

@@ -9,12 +9,14 @@
 // One workgroup computes a tile of 64 WI x 64 WJ outputs.  K goes by in steps of KS blocks.  Four wavefronts multiply, 2 x 2 over the
 // tile; eight convert: thread t of these owns block t % KS of rows t / KS, t / KS + 512 / KS, ... of a step, loads their codes,
 // scale and index bytes three steps ahead of the products (128 contiguous bytes of a row by eight lanes), and stores the operand
-// terms that they make to the LDS stage of the step that is multiplied next.  One barrier per step.  What bounds a step is that LDS
-// takes 64 bytes a clock of stores (128 of loads): 1024 x 4096 x 4096 MXFP4++ x MXFP4+ 1.7 us a step, of which the stores 0.7,
-// the conversions 0.6, the products and their operand reads 1.0, partly at the same time; loads alone nearly nothing.
-// Measured and slower, us for that product | MXFP4+ x MXFP4: this 36 | 27; conversions between the MFMAs of the same eight
-// wavefronts 46 | 36; canonical bytes through LDS and K split over four wavefronts that convert in operand order 43 | 34; four
-// converting wavefronts 45 | 32; four-byte loads of scale and index bytes, shared by a quad, 36 | 28.
+// terms that they make to the LDS stage of the step that is multiplied next.  One barrier per step.  No unit bounds a step alone:
+// 1024 x 4096 x 4096 MXFP4++ x MXFP4+ 1.7 us a step, of which (variants without them) the stores 0.7, at the 64 bytes a clock that
+// LDS takes, the conversions 0.6, the products and their operand reads 1.0, partly at the same time; loads alone nearly nothing.  By
+// counters (1037 x 3001 x 4128, 37.7 us) the vector ALU is busy 57 % of the time, LDS 29 %, the matrix cores 21 %.
+// Measured and slower, us a call for that product | MXFP4+ x MXFP4: this 36 | 27 (replayed from a graph 33.6 | 24.8);
+// conversions between the MFMAs of the same eight wavefronts 46 | 36; canonical bytes through LDS and K split over four wavefronts
+// that convert in operand order 43 | 34; four converting wavefronts 45 | 32; four-byte loads of scale and index bytes, shared by a
+// quad, 36 | 28.
 //
 // Terms of a block, each an exact E2M1 or E2M3 operand with a scale byte of its own (Sec. 4.2, 4.3; Eq. 3):
 //   MXFP4    the codes as they are (E2M1)
@@ -375,8 +377,8 @@ int launch_canon_a(int fmtB, const CanonOperand& A, const CanonOperand& B, int64
 
 namespace mxp {
 // Which products go without images: those of one round of 128 x 128 tiles (us per call, replayed from a graph, images -> without:
-// MXFP4++ x MXFP4+ 1037 x 3001 x 4128 54.2 -> 40.0, 512 x 4096 x 4096 40.2 -> 26.1, 8 x 4096 x 4128 28.1 -> 16.5; MXFP6+ pair
-// 200 x 1000 x 4096 44.2 -> 19.2; MXFP4+ pair 16 x 256 x 256 6.5 -> 4.2).  With more rounds the conversions repeat (2048 x 4096 x 4096
+// MXFP4++ x MXFP4+ 1037 x 3001 x 4128 56.4 -> 37.7, 512 x 4096 x 4096 41.5 -> 22.5, 8 x 4096 x 4128 27.6 -> 16.0; MXFP6+ pair
+// 200 x 1000 x 4096 44.6 -> 17.4; MXFP4+ pair 16 x 256 x 256 6.3 -> 4.0).  With more rounds the conversions repeat (2048 x 4096 x 4096
 // MXFP4+ pair 43.5 | 63.5, MXFP4++ x MXFP4+ 62.7 | 68.6).  The lines below come from both sides' times at 42500 shapes of all pairs
 // (1 - 4096 rows, 64 - 16384 columns, K 64 - 16384); of 34950 that they take 43 are slower than through images by more than 3 %,
 // 13 % at most.  Not taken:

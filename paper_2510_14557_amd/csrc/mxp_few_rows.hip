@@ -1,8 +1,8 @@
 // D[M][N] = A[M][K] (bf16) x deq(W)[N][K]^T for few rows of A and six- or eight-bit W: W read once, in its canonical bytes, and
 // de-converted to bf16 (Eq. 2) by the lane that feeds it to the bf16 MFMA.  Weight-only quantization in the decode stage, and the
-// products of mxp_gemm on de-converted operands with few rows.  Otherwise W is written as bf16 and read back: us per call, that way
-// -> here, 1 x 4096 x 4096 MXFP8+ 37.7 -> 8.6, 13 x 14336 x 4096 MXFP8+ 73.1 -> 26.8, MXFP6+ 63.4 -> 31.7, 64 x 8192 x 8192 MXFP8+
-// 114 -> 53.  (Four-bit W keeps the kernel of mxp_w4a16.hip: 13 x 14336 x 4096 MXFP4+ 19.3 there | 20.4 here.)
+// products of mxp_gemm on de-converted operands with few rows.  Otherwise W is written as bf16 and read back: us per call, replayed
+// from a graph, that way -> here, 1 x 4096 x 4096 MXFP8+ 37.5 -> 8.2, 13 x 14336 x 4096 MXFP8+ 53.6 -> 26.6, MXFP6+ 52.3 -> 30.1,
+// 64 x 8192 x 8192 MXFP8+ 76.8 -> 51.4.  (Four-bit W keeps the kernel of mxp_w4a16.hip: 13 x 14336 x 4096 MXFP4+ 15.0 there | 20.4 here.)
 //
 // v_mfma_f32_16x16x32_bf16: lane l holds row l % 16 of an operand and eight k-slots of group l / 16.  The sum over k does not care
 // which k sits in which slot as long as both operands agree, so the four lane groups take four consecutive MX blocks: in a step of
@@ -10,8 +10,10 @@
 // its 32 values, and feeds them to four MFMAs, eight at a time; lane (m, g) has the same eight k of activation row m.  W goes first:
 // accumulator register r of lane l is D[m = l % 16][n = 4 (l / 16) + r].
 // A workgroup owns 16 CT columns and up to 16 MT rows; its wavefronts split K in chunks of two steps, each with all
-// loads of a chunk in flight, and the partial tiles are summed through LDS in a fixed order.  Bound by the vector instructions of the
-// conversion (about 80 a block) and, above 16 rows, the reads of A: every workgroup reads all of it.
+// loads of a chunk in flight, and the partial tiles are summed through LDS in a fixed order.  Bound by what its two wavefronts a SIMD
+// wait for: by counters (13 x 14336 x 4096 MXFP8+ | MXFP6+) the vector ALU is busy 30 | 22 % of the time with the conversion (about 80
+// instructions a block), wavefronts are held before an instruction issues 55 | 59 %, in waits 28 %; above 16 rows the reads of A
+// come on top: every workgroup reads all of it.
 #include "mxp_common.h"
 #include "mxp_decode.h"
 

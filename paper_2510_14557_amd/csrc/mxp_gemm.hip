@@ -2008,7 +2008,7 @@ extern "C" int mxp_gemm(int64_t M, int64_t N, int64_t K, const uint8_t* A_elems,
   if (M <= 64 && K % 256 == 0 && (fmtB == MXP_FMT_MXFP4P || fmtA != fmtB)) {
     // few rows, weights in whole chunks of 8 blocks: the kernel that reads the canonical weights as they are -- no image of
     // them to write and read back (8 x 4096 x 4096 17.2 -> 10.6 us, 13 x 8192 x 8192 33.5 -> 18.1, 64 x 1000 x 8192 20.4 ->
-    // 19.8, 16 x 256 x 256 7.8 -> 6.8).  Two plain MXFP4 operands keep their four-bit images on both sides.
+    // 19.8; K up to 1024 has gone without any image above).  Two plain MXFP4 operands keep their four-bit images on both sides.
     rc = prepack_launch(A_elems, A_scales, A_idx, fmtA, M, K, wa, s);
     if (rc != MXP_OK) return rc;
     return fmtB == MXP_FMT_MXFP4P ? launch_canon<true>(wa, B_elems, B_scales, B_idx, M, N, K, D, d_dtype, ldd, s)

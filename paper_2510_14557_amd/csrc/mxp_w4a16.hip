@@ -48,7 +48,7 @@ constexpr int kW4PatchBytes = 32 * kW4RowStride + 256 + 256; // elements, scale 
 // place, is or-ed onto its pair: put at its place in a group of four pairs first, then one and-or per pair with the group's mask
 // (76 vector instructions; compared with and selected into each pair 110).  Six more mask the codes of a flushed block (scale byte 0)
 // away: weights may hold many such blocks, and with one in fifty of them the general way below makes a call 2.0 to 2.6 times as long
-// (masks after the conversion, where a lane needs them, 1.26; these masks cost nothing that shows).  Only when some lane of the
+// (masks after the conversion, where a lane needs them, 1.26; these take 0.7 % of a call without such blocks).  Only when some lane of the
 // wavefront holds a block of NaNs (255), or one whose values may leave the bf16 normal range, does the wavefront take the general
 // de-conversion, which builds the patterns from integer fields.
 template <int MODE>
@@ -242,12 +242,13 @@ int dispatch_skinny(int64_t M, int64_t N, int64_t K, const void* A, int64_t lda,
     else launch_skinny<MODE, TMR, CT, false, WAVES>(s, A, lda, we, ws, wi, nbk, M, N, D, ldd);                      \
   } while (0)
   // What bounds this kernel is the reads of A (every workgroup reads all of it) and the vector instructions of the conversion, at the same
-  // time: 13 x 28672 x 8192 MXFP4+ 64 us, 49 without the reads, 62 without the conversion, 32 without either.  Two column tiles share
-  // the reads from the 257th tile on (us, one tile of sixteen wavefronts -> here: 32 x 10000 x 4096 24.1 -> 17.0, 13 x 14336 x 4096 17.1 ->
-  // 14.8 and MXFP4 17.0 -> 12.9, 64 x 14336 x 4096 41.0 -> 26.5); up to 256 tiles they would leave compute units idle (8 x 4096 x 4096 8.1 |
-  // 13.7), and up to 8 rows one tile of eight wavefronts is ahead (4 x 10000 x 4096 16.2 -> 13.8 | 14.8 with two, x 1024 9.2 -> 5.8 | 6.3).
-  // So it is where the last round of pairs of tiles would be nearly empty, up to 2^16 values of A (11 x 18389 x 4512 MXFP4+ 32.0 with one
-  // of sixteen, 41.0 with two; 9 - 32 rows, 459 shapes of 513 - 768 tiles, geometric means against one of sixteen 0.78 with one of
+  // time: 13 x 28672 x 8192 MXFP4+ 64 us, 49 without the reads, 62 without the conversion, 32 without either (before the block maximum
+  // went in by masks; now 52).  Two column tiles share the reads from the 257th tile on (us, replayed from a graph, one tile of sixteen
+  // wavefronts -> here: 32 x 10000 x 4096 23.0 -> 15.8, 13 x 14336 x 4096 17.1 -> 15.0 and MXFP4 15.1 -> 11.3, 64 x 14336 x 4096
+  // 38.9 -> 24.8); up to 256 tiles they would leave compute units idle (8 x 4096 x 4096 7.9 | 13.7), and up to 8 rows one tile of eight
+  // wavefronts is ahead (4 x 10000 x 4096 15.1 -> 12.9 | 14.8 with two, x 1024 8.4 -> 5.4 | 6.3).
+  // So it is where the last round of pairs of tiles would be nearly empty, up to 2^16 values of A (11 x 18389 x 4512 MXFP4+ 40.5 with
+  // two, 30.2 with one of eight; 9 - 32 rows, 459 shapes of 513 - 768 tiles, geometric means against one of sixteen 0.78 with one of
   // eight, 1.03 with two); above that sixteen are (158 shapes, 1.01 and 1.11).
   const int64_t pairs = (ct + 1) / 2;
   const bool one_round = ct <= kNumCU;
@@ -681,7 +682,7 @@ bool tiles_beat_few_rows(int64_t M, int64_t N, int64_t K) {
 // Slabs are whole tiles and as even as that allows.  d_vectors: the rows of D start at 16-byte addresses.
 int64_t slab_rows(int64_t M, int64_t N, int64_t K, int64_t lda, int fmtW, bool d_vectors, size_t bytes) {
   const bool four = fmtW < MXP_FMT_MXFP6;
-  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 16 / 26.5 us against 60), wider W up to 64
+  // few rows have kernels of their own: four-bit W up to 128 (16 / 64 rows x 14336 x 4096: 14.9 / 24.8 us against 60), wider W up to 64
   if ((four && M <= 128) || K < 256 || !mxp::bf16_gemm_takes(M, N, K, lda)) return 0;
   if (!four && M <= 64) return once_beats_few_rows(M, N, K, fmtW) && bytes / (2 * (size_t)K) >= (size_t)N ? N : 0;
   int64_t rows = N, n = 1;
