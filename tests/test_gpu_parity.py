@@ -2691,7 +2691,8 @@ def gemm_in_marked_room(qa, fa, qb, fb, dt=torch.float32):
     ("mxfp6", "mxfp4p", 2, 1622, 2528, False), ("mxfp4p", "mxfp6", 745, 1868, 9248, True), ("mxfp4p", "mxfp6", 745, 1868, 9184, False),
     ("mxfp6", "mxfp6p", 4, 163, 3616, True), ("mxfp6", "mxfp6p", 4, 163, 3552, False), ("mxfp4pp", "mxfp4p", 8, 165, 3616, True),
     ("mxfp4p", "mxfp4pp", 8, 165, 3616, True), ("mxfp4pp", "mxfp4", 8, 165, 3616, False), ("mxfp6p", "mxfp6p", 4, 163, 3616, False),
-    ("mxfp4p", "mxfp4", 16, 300, 1024, False), ("mxfp4p", "mxfp4", 16, 300, 1280, True)])
+    ("mxfp4p", "mxfp4", 16, 300, 1024, False), ("mxfp4p", "mxfp4", 16, 300, 1280, True), ("mxfp4pp", "mxfp4p", 700, 1500, 9248, False),
+    ("mxfp6p", "mxfp6", 300, 1000, 8224, False), ("mxfp6p", "mxfp6", 256, 1000, 6176, True), ("mxfp6p", "mxfp6", 256, 1000, 6112, False)])
 def test_gemm_with_and_without_images_lines_of_the_choice(fa, fb, M, N, K, images):
     """Few rows, or a small part of the chip, by long K: the side of the line that the product is on, and its result."""
     rng = np.random.default_rng(67)
